@@ -97,10 +97,10 @@ int cns_set_workspace(cns_plan *plan, void *ws_dev, size_t bytes);
  * Results do not depend on these values (bitwise). */
 int cns_set_tiles(cns_plan *plan, int32_t seg_x, int32_t seg_y, int32_t seg_z, int32_t block);
 
-/* x-direction sweep kernel: 0 = periodic rows staged in LDS, one thread per interface
- * (default: whole rows, several per block, when nx <= 256; longer rows walked in chunks of
- * 256 interfaces by one block each), 1 = the marching kernel used for y and z.  Results
- * agree to round-off. */
+/* x-direction sweep kernel: 0 = periodic rows staged in LDS
+ * (default: whole rows, several per block, when nx <= 512 (mixed: 256); longer rows walked in
+ * chunks by one block each), 1 = the marching kernel used for y and z.  Results agree to
+ * round-off. */
 int cns_set_x_kernel(cns_plan *plan, int32_t kind);
 
 /* Sec. 2.1 equation of state: u = [rho, rho v, p/(gamma-1) + rho|v|^2/2] from device
@@ -239,10 +239,11 @@ int cns_ensemble_get_launch(const cns_ensemble *ens, int32_t box, int32_t *rows_
  * box; 0: the default; a count that does not fit gives CNS_EINVAL), and the launched blocks
  * of the marching sweeps and of the tiled kernels (0: one per virtual block; any positive
  * count: a persistent launch whose blocks loop over the virtual blocks).  Results do not
- * depend on the launched blocks (bitwise), nor on the rows as long as the points per
- * thread of the x rows kernel (rows * nx / 256, rounded up, the largest over the boxes)
- * stay the same; another count of points per thread runs another instantiation of the
- * kernel, whose results agree to round-off. */
+ * depend on the launched blocks (bitwise), nor in FP64 on the rows (a count above what a
+ * block's threads hold runs as that many); in the mixed form not on the rows as long as
+ * the points per thread of its x rows kernel (rows * nx / 256, rounded up, the largest over
+ * the boxes) stay the same; another count of points per thread runs another instantiation
+ * of the kernel, whose results agree to round-off. */
 int cns_ensemble_set_launch(cns_ensemble *ens, int32_t box, int32_t rows, int64_t sweep_grid, int64_t tile_grid);
 /* nsteps steps (RK4 unless cns_ensemble_set_integrator chose TVD-RK3) of every box with its own dt; diag_dev (may be NULL) receives
  * [nbox][nsteps][CNS_NDIAG].  use_graph != 0 captures the whole run once and

@@ -16,6 +16,7 @@
 
 #include "cns_adjoint.h"
 #include "cns_internal.h"
+#include "cns_mixed.h"
 
 using namespace cns;
 
@@ -152,17 +153,8 @@ struct Core {
         b.nx = g.nx;
         b.ny = g.ny;
         b.nz = g.nz;
-        // default marching-segment length: 16, doubled (up to 128) while the launch still
-        // has at least 2^19 threads (four rounds of two waves per SIMD over 256 CUs); longer
-        // segments recompute fewer halo interfaces, shorter ones fill the chip (512^3:
-        // 128 points, 0.4 % faster per step than 64 with the same bits)
-        const long long nlen[3] = {g.nx, g.ny, g.nz};
-        for (int d = 0; d < 3; ++d) {
-            const long long lines = (long long)g.nx * g.ny * g.nz / nlen[d];
-            int seg = 16;
-            while (seg < 128 && lines * ((nlen[d] + 2 * seg - 1) / (2 * seg)) >= (1ll << 19)) seg *= 2;
-            b.seg[d] = seg;
-        }
+        b.seg[0] = b.seg[1] = b.seg[2] = 16;
+        b.vsz = diag_planes(g.nx, g.ny, g.nz);
         b.n3 = (size_t)g.nx * g.ny * g.nz;
         b.inv_h[0] = g.nx / g.lx;
         b.inv_h[1] = g.ny / g.ly;
@@ -174,6 +166,51 @@ struct Core {
         b.delta = ph.harten_delta;
         b.dt = dt;
         return b;
+    }
+
+    // Default marching-segment lengths, from the whole batch.  A thread of a sweep runs seg + 2
+    // cell steps and a start of about one and a half, and the chip holds 2^17 threads at once
+    // (two waves per SIMD over 256 CUs): up to 16 points, the length with the least steps per
+    // round times rounds (32^3: 1 point, 0.02 against 0.06 ms per sweep with 16); 16 is doubled
+    // up to 128 while the launch still has 2^19 threads (longer segments form fewer cells
+    // twice; 512^3: 128 points).
+    void default_segs() {
+        for (int d = 0; d < 3; ++d) {
+            auto threads = [&](int seg) {
+                double t = 0.0;
+                for (const BoxDesc &b : boxes) {
+                    const int n = d == 0 ? b.nx : (d == 1 ? b.ny : b.nz);
+                    t += (double)(b.n3 / n) * ((n + seg - 1) / seg);
+                }
+                return t;
+            };
+            int best = 16;
+            double least = 1e300;
+            for (int seg : {16, 8, 4, 2, 1}) {
+                const double cost = std::max(1.0, threads(seg) / (1 << 17)) * (seg + 3.5);
+                if (cost < least) {
+                    least = cost;
+                    best = seg;
+                }
+            }
+            if (d == 0) best = 16;  // the optional marching x sweep
+            while (best >= 16 && best < 128 && threads(2 * best) >= (1 << 19)) best *= 2;
+            for (BoxDesc &b : boxes) b.seg[d] = best;
+        }
+        // planes per block of the viscous kernel: 16, or less while that does not make two
+        // blocks for each CU (the two extra planes on either side of a block cost a long
+        // batch more than the idle CUs of a short one)
+        auto tiles = [&](int cap) {
+            long long t = 0;
+            for (const BoxDesc &b : boxes) {
+                const int v = std::max(diag_planes(b.nx, b.ny, b.nz), cap);
+                t += (long long)((b.nx + kViscTX - 1) / kViscTX) * ((b.ny + kViscTY - 1) / kViscTY) * ((b.nz + v - 1) / v);
+            }
+            return t;
+        };
+        int cap = 16;
+        while (cap > 4 && tiles(cap) < 512) cap /= 2;
+        for (BoxDesc &b : boxes) b.vsz = std::max(diag_planes(b.nx, b.ny, b.nz), cap);
     }
 
     // fill pointers, shapes and prefixes; upload the device table (synchronous)
@@ -202,13 +239,18 @@ struct Core {
             b.acc = (double *)take(5 * n3 * sizeof(double));
             b.part = (double *)take(diag_part_slots(b.nx, b.ny, b.nz) * CNS_NDIAG * sizeof(double));
             b.u = ustate[i];
-            int P = 1;
-            b.rows = rows_ov[i] > 0 && rows_fit(b.nx, rows_ov[i], esz, nullptr) ? rows_ov[i] : rows_for(b.nx);
-            // rows longer than a block go through the chunked rows kernel
-            b.xrows = !xrows_pref ? 0 : (b.nx > kRowThreads ? 2 : (rows_fit(b.nx, b.rows, esz, &P) ? 1 : 0));
-            if (b.xrows == 1) {
-                rowP = std::max(rowP, P);
-                rowLds = std::max(rowLds, (size_t)14 * b.rows * b.nx * esz);
+            // rows longer than a block's threads hold go through the chunked kernel
+            if (prec == CNS_FP64) {  // two points per thread
+                b.rows = rows_ov[i] > 0 ? std::min(rows_ov[i], rows_max(b.nx)) : rows_max(b.nx);
+                b.xrows = !xrows_pref ? 0 : (b.nx > 2 * kRowThreads ? 2 : 1);
+                if (b.xrows == 1) rowLds = std::max(rowLds, xrows_lds(b.nx, b.rows, esz));
+            } else {
+                b.rows = rows_ov[i] > 0 ? rows_ov[i] : mixed::rows_for(b.nx);
+                b.xrows = !xrows_pref ? 0 : (b.nx > kRowThreads ? 2 : 1);
+                if (b.xrows == 1) {
+                    rowP = std::max(rowP, mixed::rows_points(b.nx, b.rows));
+                    rowLds = std::max(rowLds, (size_t)14 * b.rows * b.nx * esz);
+                }
             }
             for (int d = 0; d < 3; ++d) {
                 const int nl = d == 0 ? b.nx : (d == 1 ? b.ny : b.nz);
@@ -249,9 +291,10 @@ struct Core {
             bt.total[f] = total[f];
         }
         bt.rowP = rowP;
-        // with one point per thread the rows kernel lays its fields 256 points apart
-        bt.rowLds = rowP == 1 && rowLds > 0 ? (size_t)14 * kRowThreads * esz : rowLds;
+        // with one point per thread the mixed form's rows kernel lays its fields 256 points apart
+        bt.rowLds = prec != CNS_FP64 && rowP == 1 && rowLds > 0 ? (size_t)14 * kRowThreads * esz : rowLds;
         bt.esz = esz;
+        bt.n3_0 = boxes[0].n3;
         for (int f = 0; f < F_N; ++f) bt.grid[f] = grid[f];
         bt.stream = stream;
         bt.prof = prof.on ? &prof : nullptr;
@@ -433,7 +476,7 @@ static int autotune(Core &c, const char *cache_path) {
             c.active[i] = std::find(members.begin(), members.end(), i) != members.end();
     };
     // 1. segment length of the marching y/z sweeps per size class
-    const int segs[] = {4, 8, 16, 32, 64};
+    const int segs[] = {2, 4, 8, 16, 32, 64};
     for (auto &kv : cls) {
         const std::string key = pre + kv.first + "|seg";
         int best = -1;
@@ -464,27 +507,31 @@ static int autotune(Core &c, const char *cache_path) {
         for (int i : kv.second) saved[i].seg[1] = saved[i].seg[2] = best;
     }
     c.boxes = saved;
-    // 2. rows per block of the x rows kernel per size class: the default (a power of two)
-    // and every count with the same points per thread that keeps at least 90 % of the
-    // block's threads busy and fits.  The points per thread are a template parameter of
-    // the kernel, and another instantiation may contract multiplies and adds into fused
-    // operations differently, so only counts with the default's points per thread keep
-    // results bitwise independent of the choice.
+    // 2. rows per block of the x rows kernel per size class.  FP64: the default (as many as a
+    // block holds) and a half, a quarter and an eighth of it, whose blocks spread a small box
+    // over more CUs.  Mixed: the default (a power of two) and every count with the same points
+    // per thread that keeps at least 90 % of the block's threads busy and fits; the points per
+    // thread are a template parameter of that kernel, and another instantiation may contract
+    // multiplies and adds into fused operations differently, so only counts with the default's
+    // points per thread keep results bitwise independent of the choice.
     for (auto &kv : cls) {
         const int nx = c.boxes[kv.second[0]].nx;
         const std::string key = pre + kv.first + "|rows";
         auto it = cache.find(key);
         int best = 0;
-        if (it != cache.end() && it->second >= 0 && (it->second == 0 || rows_fit(nx, it->second, c.esz, nullptr))) {
+        if (it != cache.end() && it->second >= 0 && (it->second == 0 || rows_fit(nx, it->second, c.esz))) {
             best = it->second;
-        } else if (c.xrows_pref && nx <= kRowThreads && rows_fit(nx, rows_for(nx), c.esz, nullptr)) {
+        } else if (c.xrows_pref && nx <= (c.prec == CNS_FP64 ? 2 : 1) * kRowThreads) {
             std::vector<int> cand = {0};
-            int P0 = 0;
-            rows_fit(nx, rows_for(nx), c.esz, &P0);
-            for (int r = 1; r <= 1024 / nx && (int)cand.size() < 6; ++r) {
-                int P = 0;
-                if (r == rows_for(nx) || !rows_fit(nx, r, c.esz, &P) || P != P0) continue;
-                if ((double)r * nx / (kRowThreads * P) >= 0.9) cand.push_back(r);
+            if (c.prec == CNS_FP64) {
+                for (int q : {2, 4, 8})
+                    if (rows_max(nx) / q >= 1 && rows_fit(nx, rows_max(nx) / q, c.esz)) cand.push_back(rows_max(nx) / q);
+            } else {
+                const int P0 = mixed::rows_points(nx, mixed::rows_for(nx));
+                for (int r = 1; r <= 1024 / nx && (int)cand.size() < 6; ++r) {
+                    if (r == mixed::rows_for(nx) || !rows_fit(nx, r, c.esz) || mixed::rows_points(nx, r) != P0) continue;
+                    if ((double)r * nx / (kRowThreads * P0) >= 0.9) cand.push_back(r);
+                }
             }
             float best_ms = 1e30f;
             for (int r : cand) {
@@ -609,6 +656,7 @@ int cns_plan_create(cns_plan **out, const cns_grid *grid, const cns_physics *phy
     p->c.esz = precision == CNS_FP64 ? sizeof(double) : sizeof(float);
     p->c.stream = (hipStream_t)stream;
     p->c.add_box(*grid, *phys, 0.0, nullptr);
+    p->c.default_segs();
     p->c.layout();
     *out = p;
     return CNS_OK;
@@ -856,6 +904,7 @@ int cns_ensemble_create(cns_ensemble **out, int32_t nbox, const cns_grid *grids,
         }
         e->c.add_box(grids[i], phys[i], dt[i], u);
     }
+    e->c.default_segs();
     e->c.layout();
     *out = e;
     return CNS_OK;
@@ -909,7 +958,7 @@ int cns_ensemble_get_launch(const cns_ensemble *ens, int32_t box, int32_t *rows,
     if (!ens || !rows || !sweep_grid || !tile_grid) return set_err(CNS_EINVAL, "null argument");
     if (box < 0 || box >= ens->c.nbox()) return set_err(CNS_EINVAL, "box index out of range");
     const BoxDesc &b = ens->c.boxes[box];
-    *rows = ens->c.ws && b.xrows == 1 ? b.rows : 0;
+    *rows = ens->c.ws && b.xrows == 1 ? (ens->c.rows_ov[box] > 0 ? ens->c.rows_ov[box] : b.rows) : 0;
     *sweep_grid = ens->c.grid[F_SWEEP_Y];
     *tile_grid = ens->c.grid[F_VISC];
     return CNS_OK;
@@ -921,7 +970,7 @@ int cns_ensemble_set_launch(cns_ensemble *ens, int32_t box, int32_t rows, int64_
     if (rows < 0 || sweep_grid < 0 || tile_grid < 0) return set_err(CNS_EINVAL, "launch shapes must be >= 0");
     for (int i = 0; i < ens->c.nbox(); ++i) {
         if (box >= 0 && i != box) continue;
-        if (rows > 0 && !rows_fit(ens->c.boxes[i].nx, rows, ens->c.esz, nullptr))
+        if (rows > 0 && !rows_fit(ens->c.boxes[i].nx, rows, ens->c.esz))
             return set_err(CNS_EINVAL, "box %d: %d rows of %d points do not fit a block of the x rows kernel", i, rows,
                            ens->c.boxes[i].nx);
     }

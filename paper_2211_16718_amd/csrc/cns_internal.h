@@ -10,6 +10,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <vector>
@@ -22,22 +23,30 @@ namespace cns {
 constexpr int kPointThreads = 256;    // threads per block of point-wise kernels
 constexpr int kDiagThreads = 256;
 constexpr int kDiagBlocksMax = 1024;  // partial-sum blocks per box of the diagnostics
-constexpr int kRowThreads = 256;      // threads per block of the x rows kernel
+constexpr int kRowThreads = 256;      // threads per block of the x kernels (two cells each)
 constexpr int kRowLdsMax = 64 * 1024;
-constexpr int kViscTX = 32, kViscTY = 8;  // (x, y) tile of the viscous-flux kernel (kPointThreads threads)
-constexpr int kViscSZ = 16;               // planes per block of the viscous-flux kernel (and its adjoint)
-// Planes per tile of the viscous-flux and diagnostics kernels: 32 in boxes at least 256
-// deep, where the +-2-plane halo of a tile then costs 1.125x its reads instead of 1.25x
-// (512^3: fetch 9.45 -> 8.58 GB per launch), else 16, which keeps small boxes in
-// enough tiles to fill the GPU.
-__host__ __device__ __forceinline__ int visc_planes(int nz) { return nz >= 256 ? 2 * kViscSZ : kViscSZ; }
+constexpr int kViscTX = 32, kViscTY = 8;  // (x, y) tile of the viscous, diagnostics and adjoint viscous kernels
+constexpr int kViscSZ = 16;               // planes per block of the tiled kernels
+// Planes per group of the diagnostics: a partial sum covers one (x, y) tile and one group, so
+// the sums do not depend on how many groups a block of the viscous kernel marches over.
+// 32 in boxes at least 256 deep and 16 where that still makes 512 tiles, which keeps the
+// partials few and the +-2-plane halo of a block small; else 4, so that a small box can be
+// cut into many short blocks.
+__host__ __device__ __forceinline__ int diag_planes(int nx, int ny, int nz) {
+    if (nz >= 256) return 2 * kViscSZ;
+    const long long t16 = (long long)((nx + kViscTX - 1) / kViscTX) * ((ny + kViscTY - 1) / kViscTY) * ((nz + 15) / 16);
+    return t16 >= 512 ? kViscSZ : 4;
+}
+// tiles (one per (x, y) tile and group) of a box: of the diagnostics kernel, and of the FP64
+// viscous kernel's fused diagnostics
+__host__ __device__ __forceinline__ long long diag_tiles(int nx, int ny, int nz) {
+    const int g = diag_planes(nx, ny, nz);
+    return (long long)((nx + kViscTX - 1) / kViscTX) * ((ny + kViscTY - 1) / kViscTY) * ((nz + g - 1) / g);
+}
 // Partial-sum slots of a box's diagnostics: one per block of the diagnostics kernel (at
-// most kDiagBlocksMax) or one per viscous-flux tile when the diagnostics ride on that
-// kernel.
+// most kDiagBlocksMax) or one per tile when the diagnostics ride on the viscous kernel.
 inline size_t diag_part_slots(int nx, int ny, int nz) {
-    const size_t tiles = (size_t)((nx + kViscTX - 1) / kViscTX) * ((ny + kViscTY - 1) / kViscTY) *
-                         ((nz + visc_planes(nz) - 1) / visc_planes(nz));
-    return tiles > (size_t)kDiagBlocksMax ? tiles : (size_t)kDiagBlocksMax;
+    return std::max<size_t>((size_t)diag_tiles(nx, ny, nz), kDiagBlocksMax);
 }
 
 // buffer roles of a box
@@ -46,12 +55,13 @@ enum Buf { BUF_U = 0, BUF_A = 1, BUF_B = 2 };
 struct BoxDesc {
     int nx, ny, nz;
     int seg[3];  // marching-sweep segment length per direction
-    int xrows;   // x sweep kernel: 1 whole rows in LDS, 2 rows in chunks, 0 marching
+    int xrows;   // x sweep kernel: 1 whole rows in LDS (up to 512 points), 2 rows in chunks, 0 marching
     int rows;    // rows per block of the x rows kernel
+    int vsz;     // planes per block of the viscous kernel (a multiple of diag_planes, or the whole box)
     size_t n3;
     double inv_h[3];  // 1/dx, 1/dy, 1/dz
     double gamma, prandtl, mu, eps, delta, dt;
-    void *u, *A, *B, *rhs, *G;  // state and scratch (element type of the plan)
+    void *u, *A, *B, *rhs, *G;  // state and scratch (element type of the plan); G: viscous terms [4][n3]
     double *acc, *part;             // RK4 accumulator [5][n3], diagnostics partials
 };
 
@@ -82,7 +92,8 @@ struct Launch {
     // single-box overrides (used when non-null / positive)
     const void *u_ov;  // replaces the box's state u
     void *a_ov, *b_ov;  // replace the box's stage buffers A, B
-    void *out_ov;      // replaces rhs as the output of WRITE/ACCUM sweeps and viscous kernels
+    void *out_ov;      // replaces rhs as the output of WRITE/ACCUM sweeps
+    void *v_ov;        // replaces G as the output of the viscous kernel
     double dt_ov;      // replaces the box's dt
     double *diag;      // diagnostics output base (may be null)
     long long diag_box_stride;  // records between consecutive boxes in `diag`
@@ -131,9 +142,10 @@ struct Batch {
     const BoxDesc *d_boxes = nullptr;  // device table
     const long long *d_off[F_N] = {};  // device prefixes
     long long total[F_N] = {};
-    int rowP = 1;       // points per thread of the rows kernel (max over boxes)
+    int rowP = 1;       // points per thread of the mixed form's rows kernel (max over boxes)
     size_t rowLds = 0;  // LDS bytes of the rows kernel (max over boxes)
     size_t esz = 8;     // bytes per state element
+    size_t n3_0 = 0;    // points of the first box (single-box calls)
     hipStream_t stream = nullptr;
     Prof *prof = nullptr;
     const GraphParams *gp = nullptr;  // set while a run is captured for graph replay
@@ -141,10 +153,10 @@ struct Batch {
 };
 
 // host-side helpers (cns_kernels.hip)
-int rows_for(int nx);
-// rows per block of the x rows kernel fit (at most 4 points per thread, 64 KiB of LDS);
-// *P receives the points per thread
-bool rows_fit(int nx, int rows, size_t esz, int *P);
+int rows_max(int nx);  // rows per block of the x rows kernel: the default, and the most a block takes
+size_t xrows_lds(int nx, int rows, size_t esz);  // its LDS bytes
+// rows per block that cns_ensemble_set_launch accepts; above rows_max a block takes rows_max
+bool rows_fit(int nx, int rows, size_t esz);
 long long family_blocks(const BoxDesc &b, int fam, int block);
 
 // launchers (cns_kernels.hip); all enqueue on bt.stream

@@ -2,136 +2,29 @@
 //
 // Data layout in HBM: SoA state u[v][k][j][i] (x fastest) per box.  One RHS
 // evaluation of a batch of boxes is
-//   1. k_visc_flux  : u -> viscous fluxes G = (tau_xx, tau_yy, tau_zz, tau_xy,
-//                     tau_xz, tau_yz, E_x, E_y, E_z), E_d = v.tau_d - q_d       [9][N3]
-//                     (primitives formed in the kernel; skipped when mu_eff = 0)
-//   2. x sweep      : u, G -> rhs (write).  Whole periodic rows staged in LDS, one
-//                     thread per interface (k_sweep_x_rows); the marching kernel
-//                     when a row does not fit.
-//   3. k_sweep<y>   : u, G -> rhs (accumulate)
-//   4. k_sweep<z>   : u, G -> rhs (accumulate), or the fused Runge-Kutta stage update.
-// A marching thread owns a segment of one grid line and walks along it with a
-// six-point state window: every point flux is computed once, every interface
-// flux once per segment, the flux difference is formed in registers.  The viscous
-// term along d enters through the interface flux (-G_{j-1} + 7 G_j + 7 G_{j+1} -
-// G_{j+2}) / 12, whose difference is the 5-point central derivative of G.
+//   1. k_visc       : u -> the viscous and heat-flux terms sum_d D_d G_d of the momentum
+//                     and energy equations [4][N3] (skipped when mu_eff = 0)
+//   2. x sweep      : u, viscous terms -> rhs (write).  Rows staged in LDS, two cells per
+//                     thread (k_sweep_x_rows; k_sweep_x_chunks for rows above 512 points)
+//   3. k_sweep<y>   : u -> rhs (accumulate)
+//   4. k_sweep<z>   : u -> rhs (accumulate), or the fused Runge-Kutta stage update.
+// A marching thread owns a segment of one grid line and walks along it cell by cell:
+// every point flux, every cell's face values and every interface flux is formed once
+// per segment, the flux difference in registers.  FP64; the mixed form has its own
+// kernels for 1 to 4 (cns_mixed.hip).
 // Periodic boundaries wrap the line index; there are no ghost cells.
 //
 // Every kernel takes a Launch over a batch of boxes (see cns_internal.h) and loops
 // over virtual blocks, so one launch advances every box of an ensemble.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
-#include <algorithm>
-
-#include "cns_internal.h"
+#include "cns_batch.h"
+#include "cns_mixed.h"
 
 namespace cns {
-
-__device__ __forceinline__ int wrapi(int j, int n) { return j < 0 ? j + n : (j >= n ? j - n : j); }
-// the same for any j >= -n (tile halos can reach several periods past a short line);
-// the division only runs for lines shorter than the halo
-__device__ __forceinline__ int wrapm(int j, int n) {
-    int r = j < 0 ? j + n : j;
-    r = r >= n ? r - n : r;
-    return r >= n ? r % n : r;
-}
-
-// box owning virtual block vb: the last i with off[i] <= vb
-__device__ __forceinline__ int find_box(const long long *off, int nbox, long long vb) {
-    int lo = 0, hi = nbox;
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (off[mid] <= vb) lo = mid;
-        else hi = mid;
-    }
-    return lo;
-}
-
-// The virtual blocks a launched block runs.  Workgroups are dispatched to the 8 XCDs of
-// the chip round-robin (block b on XCD b % 8), and each XCD has its own L2.  The
-// virtual blocks are cut into one contiguous range per XCD, and the launched blocks of
-// XCD x walk range x with a stride of their number, so blocks that touch neighbouring
-// data (stencil halos) share an L2.  With one launched block per virtual block each
-// runs exactly one; with fewer (a persistent launch, its grid sized to the blocks the
-// chip holds at once) each loops over several.  Every virtual block runs exactly once
-// for any grid size.
-struct VbRange {
-    long long vb, end, stride;
-};
-__device__ __forceinline__ VbRange vb_range(long long total) {
-    const long long G = gridDim.x, b = blockIdx.x;
-    const long long X = G < 8 ? G : 8;  // ranges: one per XCD that has blocks
-    const long long x = b % X, l = b / X;
-    const long long nbx = G / X + (x < G % X ? 1 : 0);
-    const long long q = total / X, r = total % X;
-    const long long lo = x * q + (x < r ? x : r), hi = lo + q + (x < r ? 1 : 0);
-    return VbRange{lo + l, hi, nbx};
-}
-
-// Classical RK4 keeps u^n, the stage state and an FP64 accumulator of
-// u^n + dt sum_s b_s k_s.  With FP64 stage states (U2 = u + dt k1/2, U4 = u + dt k3)
-// the terms of k1 and k3 are recovered from them when the accumulator is next
-// touched, so it is written in stage 2 and read in stage 4 only; FP32 stage states
-// could not give those terms back to FP64 accuracy, so the mixed form updates it in
-// every stage.
-template <typename T>
-constexpr bool kFp64Stages = std::is_same<T, double>::value;
-
-// the launch with the per-call record of a graph replay applied (read once per kernel)
-__device__ __forceinline__ Launch with_params(Launch L) {
-    if (L.gp) {
-        L.u_ov = L.gp->u;
-        L.dt_ov = L.gp->dt;
-        L.diag = L.gp->diag;
-    }
-    return L;
-}
-
-// Pointers into HBM taken from the device tables are generic (flat) pointers to the
-// compiler, and accesses through them become FLAT instructions, which count against
-// the LDS counter as well as the vector-memory counter: every wait for an LDS read then
-// also waits for all HBM loads in flight, which undoes the loads issued ahead of the
-// arithmetic.  The kernels cast them to the global address space (HBM), whose
-// accesses count against the vector-memory counter only.
-template <typename T>
-using gptr = __attribute__((address_space(1))) T *;
-template <typename T>
-__device__ __forceinline__ gptr<T> glob(T *p) {
-    return (gptr<T>)p;
-}
-
-// A value all lanes hold alike (read from the box table) moved into scalar registers.
-// The compiler cannot prove that table reads are the same on every lane; marked
-// uniform, the pointers stay in scalar registers across the loops instead of being
-// copied back from vector registers before each access.
-__device__ __forceinline__ uint64_t uni64(uint64_t v) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
-template <typename T>
-__device__ __forceinline__ gptr<T> uni(gptr<T> p) {
-    return (gptr<T>)uni64((uint64_t)p);
-}
-
-// Component c of a component-major array (component c at element c * n3) at a lane's
-// byte offset: the array base and the component offset are uniform and stay in scalar
-// registers, and every load and store of a point shares the lane's one 32-bit offset
-// register (global memory instructions with a scalar base address).  Needs
-// n3 * 8 < 2^32, which plan and ensemble creation check.
-template <typename T>
-__device__ __forceinline__ gptr<T> elem(gptr<T> a, size_t n3, int c, uint32_t boff) {
-    using Byte = typename std::conditional<std::is_const<T>::value, const char, char>::type;
-    return (gptr<T>)((gptr<Byte>)(a + (size_t)c * n3) + boff);
-}
-
-__device__ __forceinline__ const void *state_ptr(const BoxDesc &b, const Launch &L, int which) {
-    if (which == BUF_U) return L.u_ov ? L.u_ov : b.u;
-    if (which == BUF_A) return L.a_ov ? L.a_ov : b.A;
-    return L.b_ov ? L.b_ov : b.B;
-}
 
 // ----------------------------------------------------------------------------
 // state from primitives (Sec. 2.1 equation of state); single box
@@ -157,384 +50,347 @@ __global__ void k_fill(size_t n, T *out) {
 // ----------------------------------------------------------------------------
 // viscous terms: primitives, then viscous fluxes at points
 // ----------------------------------------------------------------------------
-// primitives (u, v, w, T = gamma p / rho) of the state at linear index i
+// The 5-point central difference (times 12 h): the viscous kernel states every fused
+// multiply-add itself (contraction off), so that its variant that also accumulates the
+// diagnostics (extra uses of the gradients) gives the same bits.
+__device__ __forceinline__ double vfma(double a, double b, double c) { return fma(a, b, c); }
+__device__ __forceinline__ float vfma(float a, float b, float c) { return fmaf(a, b, c); }
 template <typename T>
-__device__ __forceinline__ void prim_at(gptr<const T> u, size_t n3, size_t i, T gamma, T W[4]) {
+__device__ __forceinline__ T dcen12(T m2, T m1, T p1, T p2) {
 #pragma clang fp contract(off)
-    const T r = u[i], mx = u[n3 + i], my = u[2 * n3 + i], mz = u[3 * n3 + i], e = u[4 * n3 + i];
-    const T inv = rcp(r);
-    W[0] = mx * inv;
-    W[1] = my * inv;
-    W[2] = mz * inv;
-    const T p = (gamma - T(1)) * (e - T(0.5) * (mx * W[0] + my * W[1] + mz * W[2]));
+    return vfma(T(8), p1 - m1, m2 - p2);
+}
+
+// primitives (u, v, w, T = gamma p / rho) of a loaded state
+template <typename T>
+__device__ __forceinline__ void prim_of(const T s[5], T gamma, T W[4]) {
+#pragma clang fp contract(off)
+    const T inv = rcp(s[0]);
+    W[0] = s[1] * inv;
+    W[1] = s[2] * inv;
+    W[2] = s[3] * inv;
+    const T p = (gamma - T(1)) * (s[4] - T(0.5) * (s[1] * W[0] + s[2] * W[1] + s[3] * W[2]));
     W[3] = gamma * p * inv;
 }
 
-// The halo ring of a kViscTX x kViscTY tile in its (kViscTX + 4) x (kViscTY + 4) staging
-// plane: rows 0, 1, kViscTY + 2, kViscTY + 3 in full, then columns 0, 1, kViscTX + 2,
-// kViscTX + 3 of the rows between.  Thread t < kViscRing owns ring position t.
-constexpr int kViscRingRows = 4 * (kViscTX + 4);
-constexpr int kViscRing = kViscRingRows + 4 * kViscTY;
-static_assert(kViscRing <= kPointThreads && kViscRing <= kDiagThreads, "one halo point per thread");
-__device__ __forceinline__ void ring_pos(int t, int &hx, int &hy) {
-    if (t < kViscRingRows) {
-        const int r = t / (kViscTX + 4);
-        hx = t % (kViscTX + 4);
-        hy = r < 2 ? r : kViscTY + r;
-    } else {
-        const int q = t - kViscRingRows, c = q & 3;
-        hy = 2 + (q >> 2);
-        hx = c < 2 ? c : kViscTX + c;
-    }
-}
-
-// The 5-point central difference (times h) rounded as written (no fused multiply-add):
-// the viscous-flux kernel forms every value of G with contraction off, so that the
-// variant that also accumulates the diagnostics (extra uses of the gradients) gives the
-// same bits.
-template <typename T>
-__device__ __forceinline__ T dcen_nc(T m2, T m1, T p1, T p2) {
+// The point quantities of the diagnostics of a loaded state with primitives W: kinetic
+// energy, mass, momentum, energy, the largest wave speed and the bad-point count in acc;
+// returns whether the point is valid (finite, rho > 0, p > 0).
+__device__ __forceinline__ bool prim_stats(const double s[5], const double W[4], double gamma, double acc[CNS_NDIAG]) {
 #pragma clang fp contract(off)
-    return (T(8) * (p1 - m1) - (p2 - m2)) * (T(1) / T(12));
-}
-
-// Primitives of the state at linear index i, as prim_at, and (FP64 only) the point
-// quantities of the diagnostics when `count`: kinetic energy, mass, momentum, energy,
-// the largest wave speed and the bad-point count in acc, `good` set when the point is
-// valid (finite, rho > 0, p > 0).  The primitives are the same bits as prim_at's.
-__device__ __forceinline__ void prim_stats(gptr<const double> u, size_t n3, size_t i, double gamma, double W[4],
-                                           bool count, double acc[CNS_NDIAG], bool &good) {
-#pragma clang fp contract(off)
-    const double r = u[i], mx = u[n3 + i], my = u[2 * n3 + i], mz = u[3 * n3 + i], e = u[4 * n3 + i];
+    const double r = s[0], mx = s[1], my = s[2], mz = s[3], e = s[4];
     const double inv = rcp(r);
-    W[0] = mx * inv;
-    W[1] = my * inv;
-    W[2] = mz * inv;
     const double ke = 0.5 * (mx * W[0] + my * W[1] + mz * W[2]);
     const double p = (gamma - 1.0) * (e - ke);
-    W[3] = gamma * p * inv;
-    good = false;
-    if (count) {
-        const bool finite = isfinite(r) && isfinite(mx) && isfinite(my) && isfinite(mz) && isfinite(e);
-        if (!finite || !(r > 0.0) || !(p > 0.0)) {
-            acc[8] += 1.0;
+    const bool finite = isfinite(r) && isfinite(mx) && isfinite(my) && isfinite(mz) && isfinite(e);
+    if (!finite || !(r > 0.0) || !(p > 0.0)) {
+        acc[8] += 1.0;
+        return false;
+    }
+    acc[0] += ke;
+    acc[2] += r;
+    acc[3] += mx;
+    acc[4] += my;
+    acc[5] += mz;
+    acc[6] += e;
+    const double c = sqrt(gamma * p * inv);
+    acc[7] = fmax(acc[7], fmax(fabs(W[0]), fmax(fabs(W[1]), fabs(W[2]))) + c);
+    return true;
+}
+template <int NW>
+__device__ __forceinline__ void block_reduce_diag(const double acc[CNS_NDIAG], double (*red)[CNS_NDIAG],
+                                                  gptr<double> dst, unsigned mask);
+
+// The staging box of a viscous tile has its origin at (x0 - 4, y0 - 4).  Its halo points,
+// where the tile's outer derivatives need viscous fluxes: rows y0-2, y0-1, y0+TY, y0+TY+1
+// of the tile's columns (kHaloY of them, whole waves), then columns x0-2, x0-1, x0+TX,
+// x0+TX+1 of its rows: the y and the x halo need different fluxes, and no wave has both.
+// Further points, whose primitives the gradients of the halo points need: the 2 x 2
+// corners between the halos, then columns x0-4, x0-3, x0+TX+2, x0+TX+3 of the tile's rows,
+// then rows y0-4, y0-3, y0+TY+2, y0+TY+3 of its columns.
+template <typename T>
+struct ViscTile {
+    static constexpr int TX = kViscTX, TY = kViscTY, kThreads = TX * TY;
+    static constexpr int kHaloY = 4 * TX, kHalo = kHaloY + 4 * TY, kExt = 16 + 4 * TY + 4 * TX;
+    static_assert(kHaloY % 64 == 0, "no wave holds points of both halos");
+    static_assert(kHalo <= kThreads && kExt <= kThreads, "one halo and one further point per thread");
+    static __device__ __forceinline__ void halo_pos(int h, int &bx, int &by) {
+        if (h < kHaloY) {
+            const int r = h / TX;
+            bx = 4 + h % TX;
+            by = r < 2 ? 2 + r : TY + 2 + r;
         } else {
-            acc[0] += ke;
-            acc[2] += r;
-            acc[3] += mx;
-            acc[4] += my;
-            acc[5] += mz;
-            acc[6] += e;
-            const double c = sqrt(gamma * p * inv);
-            acc[7] = fmax(acc[7], fmax(fabs(W[0]), fmax(fabs(W[1]), fabs(W[2]))) + c);
-            good = true;
+            const int q = h - kHaloY, c = q & 3;
+            bx = c < 2 ? 2 + c : TX + 2 + c;
+            by = 4 + (q >> 2);
         }
     }
-}
-__device__ __forceinline__ void block_reduce_diag(const double acc[CNS_NDIAG], double (*red)[CNS_NDIAG],
-                                                  gptr<double> dst, const double scale[CNS_NDIAG]);
+    static __device__ __forceinline__ void ext_pos(int e, int &bx, int &by) {
+        if (e < 16) {
+            const int cc = e >> 2;
+            bx = (cc & 1 ? TX + 4 : 2) + (e & 1);
+            by = (cc & 2 ? TY + 4 : 2) + ((e >> 1) & 1);
+        } else if (e < 16 + 4 * TY) {
+            const int q = e - 16, c = q & 3;
+            bx = c < 2 ? c : TX + 4 + c;
+            by = 4 + (q >> 2);
+        } else {
+            const int q = e - 16 - 4 * TY, r = q / TX;
+            bx = 4 + q % TX;
+            by = r < 2 ? r : TY + 4 + r;
+        }
+    }
+};
 
-// Viscous fluxes at points: the 12 first derivatives of (u, v, w, T) by the 5-point
-// central stencil, then tau, q and G.  A block owns a 32 x 8 (x, y) tile and marches
-// along z over visc_planes(nz) planes.  Each thread keeps its own column's primitives at planes
-// k-2 .. k+2 in registers (z derivatives); a thread that owns a point of the tile's halo
-// ring keeps that point's primitives at planes k .. k+2 in its own LDS slots.  Plane k
-// is staged in LDS from the two windows (x and y derivatives).  Each state value of a
-// plane is loaded once per tile, and the column and the ring point of plane k+2 are
-// loaded together, while the neighbouring tiles (same XCD, launched together) load the
-// same lines for their own columns, so the halo comes from L2.
+// Viscous and heat-flux terms: vd = sum_d D_d G_d, the viscous fluxes G formed and
+// differentiated in one pass (primitives -> 12 first derivatives -> tau, q -> G -> vd).
+// A block owns a 32 x 8 (x, y) tile and marches along z over vsz planes.  Each
+// thread keeps its own column's primitives at planes k-2 .. k+2 in registers; per plane
+// the block stages the primitives of the tile and of its +-4 halo in LDS, every thread
+// forms the gradients and G of its point, the owners of the halo points also those of
+// their halo point (z derivatives from their own LDS ring of five planes), G_x and G_y
+// meet in LDS, and G_z enters the pending sums of the planes k-2 .. k+2.  G is formed
+// at 1.6 points per point of the tile and at 4 extra planes per block, but never goes
+// through memory: 9 fields written and 12 read by the sweeps become 4 written and 4 read.
+// Every plane's sum takes its terms in the same order wherever a block starts.  Each load
+// is issued one plane ahead of its use, and five planes per pass rotate the windows by
+// renaming registers.
+// 512^3: 3.95 ms against 3.29 ms for the nine fluxes alone, whose 12 reads then cost each
+// sweep 0.9 ms more.  LDS half busy, VALU 0.4, 4.5 TB/s with the halos: the two barriers
+// per plane leave none saturated.  Tiles of 16 x 16 with a thread per halo column took 6.4 ms
+// (bank conflicts), of 32 x 16 the same time at 512^3 and 8 % more on ragged boxes.
 //
 // With DIAG (FP64 plans, the first stage of a step) the kernel also forms the partial
-// diagnostics of the state it reads, one partial per tile: the point quantities of a
-// plane as its column is loaded, the enstrophy from the velocity gradients it computes
-// anyway (the same central derivatives as the diagnostics kernel).  The state's
+// diagnostics of the state it reads, one partial per tile and group of diag_planes planes:
+// the point quantities of a plane as its column is loaded, the enstrophy from the velocity
+// gradients it computes anyway (the same central derivatives as the diagnostics kernel).  The state's
 // diagnostics then cost no read of their own.
 template <typename T, bool DIAG>
-__global__ __launch_bounds__(kPointThreads) void k_visc_flux(Launch L0) {
+__global__ __launch_bounds__(ViscTile<T>::kThreads, 2) void k_visc(Launch L0) {
 #pragma clang fp contract(off)
     static_assert(!DIAG || std::is_same<T, double>::value, "fused diagnostics in FP64 plans only");
+    using Tile = ViscTile<T>;
+    constexpr int TX = Tile::TX, TY = Tile::TY, kVThreads = Tile::kThreads, kVh = Tile::kHalo;
     const Launch L = with_params(L0);
-    __shared__ T pl[4][kViscTY + 4][kViscTX + 4];
-    __shared__ T rw[3][4][kViscRing];  // ring primitives, slot (plane - z0) mod 3
-    __shared__ double red[DIAG ? kPointThreads / 64 : 1][CNS_NDIAG];
-    const double one[CNS_NDIAG] = {1, 1, 1, 1, 1, 1, 1, 1, 1};
-    int rhx, rhy;
-    ring_pos(threadIdx.x, rhx, rhy);
-    const bool ring = threadIdx.x < kViscRing;
-    const int rt = ring ? threadIdx.x : 0;
+    __shared__ T sW[4][TY + 8][TX + 8];  // primitives of the plane, origin (x0-4, y0-4)
+    __shared__ T sFx[4][TY][TX + 4];     // G_x on the tile's rows and their x halo
+    __shared__ T sFy[4][TY + 4][TX];     // G_y on the tile's columns and their y halo
+    __shared__ T hW[5][4][kVh];          // primitives of the halo points, planes k-2 .. k+2
+    __shared__ double red[DIAG ? kVThreads / 64 : 1][CNS_NDIAG];
+    const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
     const VbRange R = vb_range(L.total);
     for (long long vb = R.vb; vb < R.end; vb += R.stride) {
         const int bi = find_box(L.off, L.nbox, vb);
         const BoxDesc &b = L.boxes[bi];
         const int nx = b.nx, ny = b.ny, nz = b.nz;
-        const size_t n3 = b.n3, sz = (size_t)nx * ny;
+        const size_t n3 = uni64(b.n3), sz = (size_t)nx * ny;
         const long long lb = vb - L.off[bi];
-        const int ntx = (nx + kViscTX - 1) / kViscTX, nty = (ny + kViscTY - 1) / kViscTY;
-        const int x0 = (int)(lb % ntx) * kViscTX, y0 = (int)((lb / ntx) % nty) * kViscTY;
-        const int vsz = visc_planes(nz);
+        // the halo points fall to the first waves of a block or, in every other set of 32 blocks
+        // (one per CU of an XCD), to the last: the two blocks of a CU load its SIMDs evenly
+        const int h = (threadIdx.x + (lb & 32 ? kVThreads / 2 : 0)) % kVThreads, e = kVThreads - 1 - h;
+        const bool own_h = h < kVh, yhalo = h < Tile::kHaloY, own_e = e < Tile::kExt;
+        int hbx = 0, hby = 0, ebx = 0, eby = 0;
+        if (own_h) Tile::halo_pos(h, hbx, hby);
+        if (own_e) Tile::ext_pos(e, ebx, eby);
+        const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY;
+        const int x0 = (int)(lb % ntx) * TX, y0 = (int)((lb / ntx) % nty) * TY;
+        const int vsz = b.vsz;
         const int z0 = (int)(lb / ((long long)ntx * nty)) * vsz, z1 = min(z0 + vsz, nz);
-        const int tx = threadIdx.x % kViscTX, ty = threadIdx.x / kViscTX;
         const bool act = x0 + tx < nx && y0 + ty < ny;
         // a column past a ragged edge wraps periodically: its primitives are halo values
         // of the active columns beside it
-        const size_t col = (size_t)wrapm(y0 + ty, ny) * nx + wrapm(x0 + tx, nx);
-        const size_t rcol = (size_t)wrapm(y0 - 2 + rhy, ny) * nx + wrapm(x0 - 2 + rhx, nx);
-        const gptr<const T> u = glob((const T *)state_ptr(b, L, L.in));
-        const gptr<T> G = glob((T *)b.G);
+        const uint32_t col = (uint32_t)(wrapm(y0 + ty, ny) * nx + wrapm(x0 + tx, nx));
+        const uint32_t hcol = (uint32_t)(wrapm(y0 - 4 + hby, ny) * nx + wrapm(x0 - 4 + hbx, nx));
+        const uint32_t ecol = (uint32_t)(wrapm(y0 - 4 + eby, ny) * nx + wrapm(x0 - 4 + ebx, nx));
+        const gptr<const T> u = uni(glob((const T *)state_ptr(b, L, L.in)));
+        const gptr<T> out = uni(glob(L.v_ov ? (T *)L.v_ov : (T *)b.G));
         const T gamma = T(b.gamma);
-        const T ihx = T(b.inv_h[0]), ihy = T(b.inv_h[1]), ihz = T(b.inv_h[2]);
+        // the 1/12 of the central differences is folded into the spacings
+        const T ihx = T(b.inv_h[0] / 12.0), ihy = T(b.inv_h[1] / 12.0), ihz = T(b.inv_h[2] / 12.0);
         const T mu = T(b.mu), kcond = T(b.mu / ((b.gamma - 1.0) * b.prandtl));
-        T Wz[5][4];  // this column's primitives at planes k-2 .. k+2
+        auto load = [&](uint32_t c, int plane, T s[5]) {
+            const uint32_t bo = (uint32_t)((c + (size_t)wrapi(plane, nz) * sz) * sizeof(T));
+#pragma unroll
+            for (int v = 0; v < 5; ++v) s[v] = *elem(u, n3, v, bo);
+        };
+        // windows over the planes k-2 .. k+2, plane k-2+m in slot (r+m) mod 5 at step r of a pass
+        T Wz[5][4];  // this column's primitives
+        T Tq[5][4];  // vd of this column as it accumulates
         double acc[CNS_NDIAG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
         unsigned good = 0;  // bit m: the column's point at plane k-2+m is valid (DIAG)
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const size_t ic = col + wrapi(z0 - 2 + m, nz) * sz;
+        const int k0 = z0 - 2;
+        // the sums of a group leave for the partials of its tile: the point quantities once its
+        // last plane has entered, the enstrophy once its last plane is formed
+        const int grp = diag_planes(nx, ny, nz);
+        auto flush = [&](int plane, bool enstrophy) {
             if constexpr (DIAG) {
-                const int zp = z0 - 2 + m;
-                bool gd;
-                prim_stats(u, n3, ic, gamma, Wz[m], act && zp >= z0 && zp < z1, acc, gd);
-                if (gd) good |= 1u << m;
-            } else {
-                prim_at(u, n3, ic, gamma, Wz[m]);
-            }
-        }
-        if (ring) {
-            for (int m = 0; m < 2; ++m) {
-                T w4[4];
-                prim_at(u, n3, rcol + wrapi(z0 + m, nz) * sz, gamma, w4);
+                const gptr<double> dst = glob(b.part) + (lb % ((long long)ntx * nty) +
+                                                         (long long)ntx * nty * (plane / grp)) * CNS_NDIAG;
+                block_reduce_diag<kVThreads / 64>(acc, red, dst, enstrophy ? 2u : ~2u);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) rw[m][c][rt] = w4[c];
+                for (int d = 0; d < CNS_NDIAG; ++d)
+                    if ((d == 1) == enstrophy) acc[d] = 0.0;
             }
-        }
-        int slot = 0;  // (k - z0) mod 3
-        for (int k = z0; k < z1; ++k) {
-            const int slot2 = slot == 0 ? 2 : slot - 1;  // (k + 2 - z0) mod 3
+        };
+        auto enter = [&](const T s[5], int plane, int slot, int m) {
+            prim_of(s, gamma, Wz[slot]);
             if constexpr (DIAG) {
-                bool gd;
-                prim_stats(u, n3, col + wrapi(k + 2, nz) * sz, gamma, Wz[4], act && k + 2 < z1, acc, gd);
-                if (gd) good |= 1u << 4;
-            } else {
-                prim_at(u, n3, col + wrapi(k + 2, nz) * sz, gamma, Wz[4]);
+                if (plane > z0 && plane <= z1 && (plane == z1 || plane % grp == 0)) flush(plane - 1, false);
+                if (act && plane >= z0 && plane < z1 && prim_stats(s, Wz[slot], gamma, acc)) good |= 1u << m;
             }
-            if (ring) {
-                T w4[4];
-                prim_at(u, n3, rcol + wrapi(k + 2, nz) * sz, gamma, w4);
+        };
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    rw[slot2][c][rt] = w4[c];
-                    pl[c][rhy][rhx] = rw[slot][c][rt];
+        for (int m = 0; m < 5; ++m) {
+            T s[5];
+            load(col, k0 - 2 + m, s);
+            enter(s, k0 - 2 + m, m, m);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) Tq[m][c] = T(0);
+        }
+        if (own_h)
+#pragma unroll
+            for (int m = 0; m < 5; ++m) {
+                T s[5], w4[4];
+                load(hcol, k0 - 2 + m, s);
+                prim_of(s, gamma, w4);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) hW[m][c][h] = w4[c];
+            }
+        T es[5] = {T(1), T(0), T(0), T(0), T(0)};  // state of the further point at the next full plane
+        auto step = [&](auto rc, const int k) {
+#pragma clang fp contract(off)
+            constexpr int r = decltype(rc)::value;
+            constexpr int i0 = r % 5, i1 = (r + 1) % 5, i2 = (r + 2) % 5, i3 = (r + 3) % 5, i4 = (r + 4) % 5;
+            // planes z0 .. z1-1 are formed in full; the two planes on either side only for G_z
+            const bool full = k >= z0 && k < z1;
+            T cs[5], hs[5];  // plane k+3 of the column and of the halo point
+            load(col, k + 3, cs);
+            if (own_h) {
+                load(hcol, k + 3, hs);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) sW[c][hby][hbx] = hW[i2][c][h];
+            }
+            if (own_e) {
+                if (full) {
+                    T w4[4];
+                    prim_of(es, gamma, w4);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) sW[c][eby][ebx] = w4[c];
                 }
+                if (k + 1 >= z0 && k + 1 < z1) load(ecol, k + 1, es);
             }
 #pragma unroll
-            for (int c = 0; c < 4; ++c) pl[c][ty + 2][tx + 2] = Wz[2][c];
+            for (int c = 0; c < 4; ++c) sW[c][ty + 4][tx + 4] = Wz[i2][c];
             __syncthreads();
-            if (act) {
-                T g[4][3];  // g[a][c] = d W_a / d x_c
+            // derivatives of field a at box position (X, Y)
+            auto ddx = [&](int a, int X, int Y) {
+                return dcen12(sW[a][Y][X - 2], sW[a][Y][X - 1], sW[a][Y][X + 1], sW[a][Y][X + 2]) * ihx;
+            };
+            auto ddy = [&](int a, int X, int Y) {
+                return dcen12(sW[a][Y - 2][X], sW[a][Y - 1][X], sW[a][Y + 1][X], sW[a][Y + 2][X]) * ihy;
+            };
+            {
+                T g[4][3];  // gradients of (u, v, w, T)
 #pragma unroll
                 for (int a = 0; a < 4; ++a) {
-                    g[a][0] = dcen_nc(pl[a][ty + 2][tx], pl[a][ty + 2][tx + 1], pl[a][ty + 2][tx + 3], pl[a][ty + 2][tx + 4]) * ihx;
-                    g[a][1] = dcen_nc(pl[a][ty][tx + 2], pl[a][ty + 1][tx + 2], pl[a][ty + 3][tx + 2], pl[a][ty + 4][tx + 2]) * ihy;
-                    g[a][2] = dcen_nc(Wz[0][a], Wz[1][a], Wz[3][a], Wz[4][a]) * ihz;
+                    g[a][0] = ddx(a, tx + 4, ty + 4);
+                    g[a][1] = ddy(a, tx + 4, ty + 4);
+                    g[a][2] = dcen12(Wz[i0][a], Wz[i1][a], Wz[i3][a], Wz[i4][a]) * ihz;
                 }
                 if constexpr (DIAG) {
-                    if (good & 4u) {
+                    if (full && (good & 4u)) {
                         // vorticity of the velocity, as the diagnostics kernel forms it
                         const double ox = g[2][1] - g[1][2], oy = g[0][2] - g[2][0], oz = g[1][0] - g[0][1];
                         if (isfinite(ox) && isfinite(oy) && isfinite(oz)) acc[1] += 0.5 * (ox * ox + oy * oy + oz * oz);
                     }
+                    if (full && (k + 1 == z1 || (k + 1) % grp == 0)) flush(k, true);
                 }
-                T div = g[0][0] + g[1][1] + g[2][2];
-                T tdiv = T(2) / T(3) * div;
-                T txx = mu * (T(2) * g[0][0] - tdiv);
-                T tyy = mu * (T(2) * g[1][1] - tdiv);
-                T tzz = mu * (T(2) * g[2][2] - tdiv);
-                T txy = mu * (g[0][1] + g[1][0]);
-                T txz = mu * (g[0][2] + g[2][0]);
-                T tyz = mu * (g[1][2] + g[2][1]);
-                const T vx = Wz[2][0], vy = Wz[2][1], vz = Wz[2][2];
-                const size_t idx = (size_t)k * sz + col;
-                // non-temporal stores: G is streamed to memory and read back by the sweeps
-                // (at 128^3: 1.3 % faster step, at 512^3: 1.9 %)
-                __builtin_nontemporal_store(txx, &G[idx]);
-                __builtin_nontemporal_store(tyy, &G[n3 + idx]);
-                __builtin_nontemporal_store(tzz, &G[2 * n3 + idx]);
-                __builtin_nontemporal_store(txy, &G[3 * n3 + idx]);
-                __builtin_nontemporal_store(txz, &G[4 * n3 + idx]);
-                __builtin_nontemporal_store(tyz, &G[5 * n3 + idx]);
-                __builtin_nontemporal_store(vx * txx + vy * txy + vz * txz + kcond * g[3][0], &G[6 * n3 + idx]);
-                __builtin_nontemporal_store(vx * txy + vy * tyy + vz * tyz + kcond * g[3][1], &G[7 * n3 + idx]);
-                __builtin_nontemporal_store(vx * txz + vy * tyz + vz * tzz + kcond * g[3][2], &G[8 * n3 + idx]);
+                const T vx = Wz[i2][0], vy = Wz[i2][1], vz = Wz[i2][2];
+                const T tdiv = (T(2) / T(3)) * ((g[0][0] + g[1][1]) + g[2][2]);
+                const T txz = mu * (g[0][2] + g[2][0]), tyz = mu * (g[1][2] + g[2][1]);
+                const T tzz = mu * vfma(T(2), g[2][2], -tdiv);
+                const T Gz[4] = {txz, tyz, tzz, vfma(vx, txz, vfma(vy, tyz, vfma(vz, tzz, kcond * g[3][2])))};
+                // D_z G_z: dcen = (8 (p1 - m1) - (p2 - m2)) / 12, so G_z of this plane enters the
+                // planes k-2, k-1, k+1, k+2 with -1, 8, -8, 1 times ihz
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const T w = ihz * Gz[a];
+                    Tq[i0][a] -= w;
+                    Tq[i1][a] = vfma(T(8), w, Tq[i1][a]);
+                    Tq[i3][a] = vfma(T(-8), w, Tq[i3][a]);
+                    Tq[i4][a] = w;
+                }
+                if (full) {
+                    const T txx = mu * vfma(T(2), g[0][0], -tdiv), tyy = mu * vfma(T(2), g[1][1], -tdiv);
+                    const T txy = mu * (g[0][1] + g[1][0]);
+                    sFx[0][ty][tx + 2] = txx;
+                    sFx[1][ty][tx + 2] = txy;
+                    sFx[2][ty][tx + 2] = txz;
+                    sFx[3][ty][tx + 2] = vfma(vx, txx, vfma(vy, txy, vfma(vz, txz, kcond * g[3][0])));
+                    sFy[0][ty + 2][tx] = txy;
+                    sFy[1][ty + 2][tx] = tyy;
+                    sFy[2][ty + 2][tx] = tyz;
+                    sFy[3][ty + 2][tx] = vfma(vx, txy, vfma(vy, tyy, vfma(vz, tyz, kcond * g[3][1])));
+                }
             }
-            __syncthreads();  // the next plane overwrites the LDS tile
+            if (own_h && full) {
+                // a halo point: the eight derivatives its G_y (y halo) or G_x (x halo) takes
+                auto hdz = [&](int a) { return dcen12(hW[i0][a][h], hW[i1][a][h], hW[i3][a][h], hW[i4][a][h]) * ihz; };
+                const T vx = sW[0][hby][hbx], vy = sW[1][hby][hbx], vz = sW[2][hby][hbx];
+                const T ux = ddx(0, hbx, hby), vyy = ddy(1, hbx, hby), wz = hdz(2);
+                const T tdiv = (T(2) / T(3)) * ((ux + vyy) + wz);
+                const T txy = mu * (ddy(0, hbx, hby) + ddx(1, hbx, hby));
+                if (yhalo) {
+                    const T tyy = mu * vfma(T(2), vyy, -tdiv), tyz = mu * (hdz(1) + ddy(2, hbx, hby));
+                    sFy[0][hby - 2][hbx - 4] = txy;
+                    sFy[1][hby - 2][hbx - 4] = tyy;
+                    sFy[2][hby - 2][hbx - 4] = tyz;
+                    sFy[3][hby - 2][hbx - 4] =
+                        vfma(vx, txy, vfma(vy, tyy, vfma(vz, tyz, kcond * ddy(3, hbx, hby))));
+                } else {
+                    const T txx = mu * vfma(T(2), ux, -tdiv), txz = mu * (hdz(0) + ddx(2, hbx, hby));
+                    sFx[0][hby - 4][hbx - 2] = txx;
+                    sFx[1][hby - 4][hbx - 2] = txy;
+                    sFx[2][hby - 4][hbx - 2] = txz;
+                    sFx[3][hby - 4][hbx - 2] =
+                        vfma(vx, txx, vfma(vy, txy, vfma(vz, txz, kcond * ddx(3, hbx, hby))));
+                }
+            }
+            __syncthreads();
+            if (full) {
 #pragma unroll
-            for (int m = 0; m < 4; ++m)
+                for (int a = 0; a < 4; ++a) {
+                    const T dx = dcen12(sFx[a][ty][tx], sFx[a][ty][tx + 1], sFx[a][ty][tx + 3], sFx[a][ty][tx + 4]);
+                    const T dy = dcen12(sFy[a][ty][tx], sFy[a][ty + 1][tx], sFy[a][ty + 3][tx], sFy[a][ty + 4][tx]);
+                    Tq[i2][a] = vfma(ihx, dx, vfma(ihy, dy, Tq[i2][a]));
+                }
+            }
+            if (k - 2 >= z0 && act) {
+                const uint32_t bo = (uint32_t)((col + (size_t)(k - 2) * sz) * sizeof(T));
 #pragma unroll
-                for (int c = 0; c < 4; ++c) Wz[m][c] = Wz[m + 1][c];
-            slot = slot == 2 ? 0 : slot + 1;
+                for (int a = 0; a < 4; ++a) __builtin_nontemporal_store(Tq[i0][a], elem(out, n3, a, bo));
+            }
+            // plane k+3 enters the windows in place of plane k-2
             good >>= 1;
-        }
-        if constexpr (DIAG) block_reduce_diag(acc, red, glob(b.part) + (size_t)lb * CNS_NDIAG, one);
-    }
-}
-
-// which G field holds component (momentum x, y, z, energy) of the viscous flux along DIR
-template <int DIR>
-__device__ __forceinline__ constexpr int gcomp(int c) {
-    return DIR == 0 ? (c == 0 ? 0 : c == 1 ? 3 : c == 2 ? 4 : 6)
-                    : (DIR == 1 ? (c == 0 ? 3 : c == 1 ? 1 : c == 2 ? 5 : 7) : (c == 0 ? 4 : c == 1 ? 5 : c == 2 ? 2 : 8));
-}
-
-// A stage's sweeps run x, y, z.  The G field of component c along DIR is read for the
-// last time in that stage by this sweep when no later sweep reads it (tau_xy: x then y;
-// tau_xz: x then z; tau_yz: y then z); such loads, and the z sweep's loads of rhs and
-// of the FP64 accumulator, are marked non-temporal so they do not displace lines that
-// are read again.
-template <int DIR, int C>
-__device__ __forceinline__ constexpr bool g_last_read() {
-    return DIR == 2 || (DIR == 1 && C != 2) || (DIR == 0 && (C == 0 || C == 3));
-}
-template <int DIR, int C, typename T>
-__device__ __forceinline__ T load_g(gptr<const T> G, size_t n3, size_t o) {
-    if constexpr (g_last_read<DIR, C>()) return __builtin_nontemporal_load(&G[gcomp<DIR>(C) * n3 + o]);
-    else return G[gcomp<DIR>(C) * n3 + o];
-}
-// the same with the point's byte offset
-template <int DIR, int C, typename T>
-__device__ __forceinline__ T load_gb(gptr<const T> G, size_t n3, uint32_t bo) {
-    if constexpr (g_last_read<DIR, C>()) return __builtin_nontemporal_load(elem(G, n3, gcomp<DIR>(C), bo));
-    else return *elem(G, n3, gcomp<DIR>(C), bo);
-}
-
-// viscous term alone: out = sum_d D_d G_d (the viscous-only entry point)
-template <typename T>
-__global__ __launch_bounds__(kPointThreads) void k_visc_div(Launch L0) {
-    const Launch L = with_params(L0);
-    const VbRange R = vb_range(L.total);
-    for (long long vb = R.vb; vb < R.end; vb += R.stride) {
-        const int bi = find_box(L.off, L.nbox, vb);
-        const BoxDesc &b = L.boxes[bi];
-        const int nx = b.nx, ny = b.ny, nz = b.nz;
-        const size_t n3 = b.n3;
-        const size_t idx = (size_t)(vb - L.off[bi]) * kPointThreads + threadIdx.x;
-        if (idx >= n3) continue;
-        const gptr<const T> G = glob((const T *)b.G);
-        const gptr<T> out = glob((T *)(L.out_ov ? L.out_ov : b.rhs));
-        const T ihx = T(b.inv_h[0]), ihy = T(b.inv_h[1]), ihz = T(b.inv_h[2]);
-        const int i = (int)(idx % nx);
-        const int j = (int)((idx / nx) % ny);
-        const int k = (int)(idx / ((size_t)nx * ny));
-        const size_t sy = nx, sz = (size_t)nx * ny;
-        const size_t row = idx - i, col = idx - j * sy, pil = idx - k * sz;
-        const size_t x[4] = {row + wrapi(i - 2, nx), row + wrapi(i - 1, nx), row + wrapi(i + 1, nx),
-                             row + wrapi(i + 2, nx)};
-        const size_t y[4] = {col + wrapi(j - 2, ny) * sy, col + wrapi(j - 1, ny) * sy, col + wrapi(j + 1, ny) * sy,
-                             col + wrapi(j + 2, ny) * sy};
-        const size_t z[4] = {pil + wrapi(k - 2, nz) * sz, pil + wrapi(k - 1, nz) * sz, pil + wrapi(k + 1, nz) * sz,
-                             pil + wrapi(k + 2, nz) * sz};
-        out[idx] = T(0);
+            enter(cs, k + 3, i0, 4);
+            if (own_h) {
+                T w4[4];
+                prim_of(hs, gamma, w4);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const gptr<const T> gx = G + gcomp<0>(c) * n3;
-            const gptr<const T> gy = G + gcomp<1>(c) * n3;
-            const gptr<const T> gz = G + gcomp<2>(c) * n3;
-            T s = dcen(gx[x[0]], gx[x[1]], gx[x[2]], gx[x[3]]) * ihx;
-            s += dcen(gy[y[0]], gy[y[1]], gy[y[2]], gy[y[3]]) * ihy;
-            s += dcen(gz[z[0]], gz[z[1]], gz[z[2]], gz[z[3]]) * ihz;
-            out[(1 + c) * n3 + idx] = s;
-        }
-    }
-}
-
-// ----------------------------------------------------------------------------
-// interface flux at j+1/2 from the states w and point fluxes f at j-2 .. j+3 and
-// (VISC) the viscous fluxes g at j-1 .. j+2:
-//   H = (f^L + f^R)/2 - |A| (u^R - u^L)/2 - (-g_{j-1} + 7 g_j + 7 g_{j+1} - g_{j+2})/12
-// ----------------------------------------------------------------------------
-template <typename T, typename B, int DIR, bool VISC, int WW>
-__device__ __forceinline__ void interface_flux(const T w[6][5], const T f[6][5], const T g[4][4], T gamma, T eps4,
-                                               T delta, T H[5]) {
-    // six-fold reconstructions (eps4 = 4 eps); D is linear in du, so H = (6 F - 6 D) / 12
-    T FL[5], FR[5], UL[5], UR[5], du[5], D[5];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-        weno5_lr6<T, B, WW>(f[0][v], f[1][v], f[2][v], f[3][v], f[4][v], f[5][v], eps4, FL[v], FR[v]);
-        weno5_lr6<T, B, WW>(w[0][v], w[1][v], w[2][v], w[3][v], w[4][v], w[5][v], eps4, UL[v], UR[v]);
-        du[v] = UR[v] - UL[v];
-    }
-    roe_dissipation<T, DIR>(w[2], w[3], du, gamma, delta, D);
-#pragma unroll
-    for (int v = 0; v < 5; ++v) H[v] = (FL[v] + FR[v] - D[v]) * (T(1) / T(12));
-    if constexpr (VISC) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            H[1 + c] -= (T(7) * (g[1][c] + g[2][c]) - (g[0][c] + g[3][c])) * (T(1) / T(12));
-    }
-}
-
-// The same interface flux with the point fluxes read from the per-thread LDS ring of the
-// marching sweep (slot sl[m] holds point j-2+m), one component at a time: the fence
-// between components keeps the scheduler from hoisting all thirty LDS reads, which
-// would hold them in registers across the whole reconstruction.  Same arithmetic, in
-// the same order, as interface_flux.
-template <typename T, typename B, int DIR, bool VISC, int WW>
-__device__ __forceinline__ void interface_flux_ring(const T w[6][5], const T *ring, const int sl[6], int bdim,
-                                                    const T g[4][4], T gamma, T eps4, T delta, T H[5]) {
-    T Fs[5], du[5], D[5];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-        T fm[6];
-#pragma unroll
-        for (int m = 0; m < 6; ++m) fm[m] = ring[(sl[m] * 5 + v) * bdim];
-        T FL, FR, UL, UR;
-        weno5_lr6<T, B, WW>(fm[0], fm[1], fm[2], fm[3], fm[4], fm[5], eps4, FL, FR);
-        weno5_lr6<T, B, WW>(w[0][v], w[1][v], w[2][v], w[3][v], w[4][v], w[5][v], eps4, UL, UR);
-        Fs[v] = FL + FR;
-        du[v] = UR - UL;
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    roe_dissipation<T, DIR>(w[2], w[3], du, gamma, delta, D);
-#pragma unroll
-    for (int v = 0; v < 5; ++v) H[v] = (Fs[v] - D[v]) * (T(1) / T(12));
-    if constexpr (VISC) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            H[1 + c] -= (T(7) * (g[1][c] + g[2][c]) - (g[0][c] + g[3][c])) * (T(1) / T(12));
-    }
-}
-
-// The same interface flux with every operand read from the rows kernel's LDS staging
-// (component-major arrays of `per` points; q[m] is the position of point i-2+m), one
-// component at a time behind a scheduling fence, so that the reconstruction holds
-// only the operands of the component in flight.
-template <typename T, typename B, int DIR, bool VISC, int WW>
-__device__ __forceinline__ void interface_flux_lds(const T *su, const T *sf, const T *sg, int per, const int q[6],
-                                                   T gamma, T eps4, T delta, T H[5]) {
-    T Fs[5], du[5], D[5];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-        const T *fv = sf + v * per, *uv = su + v * per;
-        T FL, FR, UL, UR;
-        weno5_lr6<T, B, WW>(fv[q[0]], fv[q[1]], fv[q[2]], fv[q[3]], fv[q[4]], fv[q[5]], eps4, FL, FR);
-        weno5_lr6<T, B, WW>(uv[q[0]], uv[q[1]], uv[q[2]], uv[q[3]], uv[q[4]], uv[q[5]], eps4, UL, UR);
-        Fs[v] = FL + FR;
-        du[v] = UR - UL;
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    T a[5], b[5];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-        a[v] = su[v * per + q[2]];
-        b[v] = su[v * per + q[3]];
-    }
-    roe_dissipation<T, DIR>(a, b, du, gamma, delta, D);
-#pragma unroll
-    for (int v = 0; v < 5; ++v) H[v] = (Fs[v] - D[v]) * (T(1) / T(12));
-    if constexpr (VISC) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const T *gc = sg + c * per;
-            H[1 + c] -= (T(7) * (gc[q[2]] + gc[q[3]]) - (gc[q[1]] + gc[q[4]])) * (T(1) / T(12));
+                for (int c = 0; c < 4; ++c) hW[i0][c][h] = w4[c];
+            }
+        };
+        for (int k = k0;;) {
+            step(std::integral_constant<int, 0>{}, k);
+            if (++k >= z1 + 2) break;
+            step(std::integral_constant<int, 1>{}, k);
+            if (++k >= z1 + 2) break;
+            step(std::integral_constant<int, 2>{}, k);
+            if (++k >= z1 + 2) break;
+            step(std::integral_constant<int, 3>{}, k);
+            if (++k >= z1 + 2) break;
+            step(std::integral_constant<int, 4>{}, k);
+            if (++k >= z1 + 2) break;
         }
     }
 }
@@ -542,40 +398,42 @@ __device__ __forceinline__ void interface_flux_lds(const T *su, const T *sf, con
 // ----------------------------------------------------------------------------
 // marching WENO5-Roe sweep along one direction
 // ----------------------------------------------------------------------------
-enum { MODE_WRITE = 0, MODE_ACCUM = 1, MODE_RK = 2 };
-
-// geometry of a sweep along DIR: lanes run over the plane normal to DIR (p fastest)
-struct SweepGeom {
-    int nline, np, npq;
-    size_t lstride, pstride, qstride;
-};
-template <int DIR>
-__host__ __device__ __forceinline__ SweepGeom sweep_geom(int nx, int ny, int nz) {
-    const size_t sy = (size_t)nx, sz = (size_t)nx * ny;
-    if (DIR == 0) return SweepGeom{nx, ny, ny * nz, 1, sy, sz};
-    if (DIR == 1) return SweepGeom{ny, nx, nx * nz, sy, 1, sz};
-    return SweepGeom{nz, nx, nx * ny, sz, 1, sy};
-}
+// MODE_RK1/2/3: the fused Runge-Kutta update, by what it reads besides rhs and the stage
+// state: nothing (first stages), u^n, or u^n and the accumulator (RK4 stage 4).  One kernel
+// with a run-time choice holds the operands of all three and spills 25 registers.
+enum { MODE_WRITE = 0, MODE_ACCUM = 1, MODE_RK1 = 2, MODE_RK2 = 3, MODE_RK3 = 4 };
+constexpr bool is_rk(int mode) { return mode >= MODE_RK1; }
 
 // Lanes run over consecutive lines of the plane (coalesced).  For y, a block of W
 // waves covers 64 lines times W consecutive segments, so neighbouring segments share
 // their six-point halos in the CU's cache; for x and z a block covers 64 W lines of one
 // segment (stacking z segments spreads a block over planes far apart in memory).
 //
-// The six point fluxes live in a per-thread ring in LDS (6 slots x 5 components,
-// component-major across the wave so lanes hit distinct banks), read one component
-// at a time; the registers this frees carry the loads of the next point and of the
-// point's rhs, issued before the interface-flux arithmetic so their latency overlaps
-// it (y sweep 12 % and fused-update sweep 6 % faster than a register window).  The
-// fused update's u^n and accumulator are loaded ahead in the same way.
-template <typename T, typename B, int DIR, int MODE, bool VISC, int WW>
+// A thread keeps the states of six consecutive points in registers and their fluxes 1-4
+// in a ring in LDS (6 slots x 4 components, component-major across the wave so lanes hit
+// distinct banks), read one component at a time; the sixth register slot receives the
+// next point's load, issued a whole step ahead of its use, as are the loads of the output
+// operands.  The step of cell k forms the cell's face values (weno5_cell6); those of its
+// right face, and what the Roe average takes from the cell, are carried to the next step,
+// those of its left face close the interface k-1/2, whose flux gives the difference at
+// point k-1.  Three steps per pass, so the window rotates by renaming registers and by
+// three slot copies a pass.
+//
+// Measured at 512^3 (interfaces formed from both biases, ten reconstructions and nine
+// stored viscous fluxes before): y 5.38 -> 3.85 ms, 987 -> 700 VALU instructions per point
+// and 20.9 -> 16.6 GB, now 0.81 of the issue slots at the 1.86 GHz the power limit leaves
+// and 0.92 of the copy rate; z with the update 6.16 -> 4.85 ms (mean of the stages), 0.9-1.0
+// of the copy rate: bound by memory.
+template <typename T, int DIR, int MODE, bool VISC, int WW>
 __global__ __launch_bounds__(256, 2) void k_sweep(Launch L0) {
+#pragma clang fp contract(off)
     const Launch L = with_params(L0);
     extern __shared__ unsigned char lds_raw[];
-    // each wave's ring: slot s, component v of lane l at (s * 5 + v) * 64 + l, so the
-    // component and slot strides are constants (immediate LDS offsets)
-    constexpr int bdim = 64;
-    T *ring = reinterpret_cast<T *>(lds_raw) + (threadIdx.x >> 6) * (30 * 64) + (threadIdx.x & 63);
+    // each wave's ring: slot s, component v of lane l at (s * 4 + v) * 64 + l, so the
+    // component and slot strides are constants (immediate LDS offsets); slots 0-2 and 3-5
+    // trade places after every pass
+    constexpr int kSlot = 4 * 64;
+    T *const ring0 = reinterpret_cast<T *>(lds_raw) + (threadIdx.x >> 6) * (6 * kSlot) + (threadIdx.x & 63);
     const VbRange R = vb_range(L.total);
     for (long long vb = R.vb; vb < R.end; vb += R.stride) {
         const int bi = find_box(L.off, L.nbox, vb);
@@ -601,361 +459,426 @@ __global__ __launch_bounds__(256, 2) void k_sweep(Launch L0) {
         const int p = pq % sg.np, q = pq / sg.np;
         const size_t base = p * sg.pstride + q * sg.qstride;
         const int j0 = sgi * seg;
-        const int j1 = min(j0 + seg, n);
+        const int len = min(seg, n - j0);  // points of the segment
         const size_t n3 = uni64(bx.n3);
         const gptr<const T> u = uni(glob((const T *)state_ptr(bx, L, L.in)));
-        const gptr<const T> G = uni(glob((const T *)bx.G));
-        const T gamma = T(bx.gamma), eps4 = T(4.0 * bx.eps), delta = T(bx.delta);
-        const T gm1 = gamma - T(1);
+        const gptr<const T> vd = uni(glob((const T *)bx.G));
+        const T eps4 = T(4.0 * bx.eps), delta = T(bx.delta);
+        const T gm1 = T(bx.gamma) - T(1);
         const T inv_dx = T(bx.inv_h[DIR]);
         const double dt = L.dt_ov > 0.0 ? L.dt_ov : bx.dt;
         // Every pointer the loop uses is read from the box table here, once: the loop
         // stores to global memory, which the compiler cannot tell apart from the table, so
         // a table read inside the loop would be repeated after every store, each time
         // behind a wait for all loads in flight (the ones issued ahead included).
-        const gptr<const T> rhs_in = uni(glob((const T *)(MODE == MODE_RK ? bx.rhs : (L.out_ov ? L.out_ov : bx.rhs))));
+        const gptr<const T> rhs_in = uni(glob((const T *)(is_rk(MODE) ? bx.rhs : (L.out_ov ? L.out_ov : bx.rhs))));
         const gptr<const T> un = uni(glob((const T *)state_ptr(bx, L, BUF_U)));
         const gptr<double> acc = uni(glob(bx.acc));
         const gptr<T> unext = uni(glob((T *)state_ptr(bx, L, L.out)));
         const gptr<T> rhs_out = uni(glob((T *)(L.out_ov ? L.out_ov : bx.rhs)));
 
-        T w[6][5], g[4][4], Hp[5], nw[5];
-        // One step body computes everything, so every point flux and every interface
-        // flux takes the same arithmetic in the same order wherever a segment starts:
-        // results are bitwise independent of the segment length.  Step j takes point
-        // j+3 (loaded one step ahead) and the viscous fluxes of point j+2; from j = j0-1
-        // on it forms the interface flux at j+1/2 and from j = j0 on the flux difference
-        // at point j.
-        {
-            const uint32_t bo = (uint32_t)((base + wrapi(j0 - 3, n) * sg.lstride) * sizeof(T));
+        T w[6][5];                // states: step r of a pass finds point k-2+m in w[r+m]
+        T Lf[kNS];                // face values of cell k-1 at k-1/2
+        RoeCell<T> ca;            // of cell k-1
+        T Hp[5];                  // interface flux at k-3/2
+        T *rlo = ring0, *rhi = ring0 + 3 * kSlot;
 #pragma unroll
-            for (int v = 0; v < 5; ++v) nw[v] = *elem(u, n3, v, bo);
-        }
-        int snew = 3;  // ring slot of point j+3; point j-2+m sits in slot (snew + 1 + m) mod 6
-        auto step = [&](const int j) {
+        for (int c = 0; c < kNS; ++c) Lf[c] = T(0);
+        ca = RoeCell<T>{T(1), {T(0), T(0), T(0)}, T(1)};
+        auto load = [&](int j, T (&d)[5]) {
+            const uint32_t bo = (uint32_t)((base + wrapi(j, n) * sg.lstride) * sizeof(T));
+#pragma unroll
+            for (int v = 0; v < 5; ++v) d[v] = *elem(u, n3, v, bo);
+        };
+        // the step's ring slot of point k-2+m: r+m, modulo 6
+        auto slot = [&](int s) -> T * { return s % 6 < 3 ? rlo + (s % 3) * kSlot : rhi + (s % 3) * kSlot; };
+        auto put_flux = [&](int s, const T (&d)[5]) {
+            T f[4];
+            euler_flux<T, DIR>(d, gm1, f);
+            T *o = slot(s);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) o[v * 64] = f[v];
+        };
+#pragma unroll
+        for (int m = 0; m < 5; ++m) load(j0 - 3 + m, w[m]);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) put_flux(m, w[m]);
+        // step i takes cell k = j0 - 1 + i, i = 0 .. len + 1
+        auto step = [&](auto rc, const int i) {
+#pragma clang fp contract(off)
+            constexpr int r = decltype(rc)::value;
+            const int k = j0 - 1 + i;
+            // The window enters each step through an empty asm: otherwise the optimiser
+            // shares the differences and indicator terms of a scalar between the cells of
+            // a pass and holds them for all scalars at once (hundreds of spilled registers).
 #pragma unroll
             for (int m = 0; m < 5; ++m)
 #pragma unroll
-                for (int v = 0; v < 5; ++v) w[m][v] = w[m + 1][v];
-#pragma unroll
-            for (int v = 0; v < 5; ++v) w[5][v] = nw[v];
-            // The window enters each step through an empty asm, so the two steps of a
-            // pass share no arithmetic (the optimiser would otherwise form a point's Roe
-            // terms once for both interfaces, outside the block where the other step
-            // fuses them into multiply-adds): every interface flux is computed by the
-            // same instructions in either step, bitwise as with one step per pass.
-#pragma unroll
-            for (int m = 0; m < 6; ++m)
-#pragma unroll
-                for (int v = 0; v < 5; ++v) asm volatile("" : "+v"(w[m][v]));
-            {
-                const uint32_t bo = (uint32_t)((base + wrapi(j + 4, n) * sg.lstride) * sizeof(T));
-#pragma unroll
-                for (int v = 0; v < 5; ++v) nw[v] = *elem(u, n3, v, bo);
-            }
-            if constexpr (VISC) {
-#pragma unroll
-                for (int m = 0; m < 3; ++m)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) g[m][c] = g[m + 1][c];
-                const uint32_t bog = (uint32_t)((base + wrapi(j + 2, n) * sg.lstride) * sizeof(T));
-                g[3][0] = load_gb<DIR, 0>(G, n3, bog);
-                g[3][1] = load_gb<DIR, 1>(G, n3, bog);
-                g[3][2] = load_gb<DIR, 2>(G, n3, bog);
-                g[3][3] = load_gb<DIR, 3>(G, n3, bog);
-#pragma unroll
-                for (int m = 0; m < 3; ++m)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(g[m][c]));
-            }
-            const int sold = snew;
-            {
-                T fn[5];
-                euler_flux<T, DIR>(w[5], gm1, fn);
-#pragma unroll
-                for (int v = 0; v < 5; ++v) ring[(snew * 5 + v) * bdim] = fn[v];
-                snew = snew == 5 ? 0 : snew + 1;
-            }
-            if (j < j0 - 1) return;
-
-            // output operands of point j, loaded before the interface-flux arithmetic
-            const size_t o = base + (size_t)(j >= j0 ? j : j0) * sg.lstride;
+                for (int v = 0; v < 5; ++v) pin(w[(r + m) % 6][v]);
+            load(k + 3, w[(r + 5) % 6]);
+            // output operands of point k-1, loaded before the arithmetic
+            const size_t o = base + (size_t)(i >= 2 ? k - 1 : j0) * sg.lstride;
             const uint32_t bo = (uint32_t)(o * sizeof(T)), boa = (uint32_t)(o * sizeof(double));
             T pr[5], pu[5];
             double pa[5];
-            if (MODE != MODE_WRITE && j >= j0) {
+            if (i >= 2) {
+                if constexpr (VISC) {  // the viscous term of the point joins the writing sweep
+                    static_assert(DIR == 0 && MODE == MODE_WRITE, "the x sweep takes the viscous term");
 #pragma unroll
-                for (int v = 0; v < 5; ++v) {
-                    if constexpr (MODE == MODE_RK) pr[v] = __builtin_nontemporal_load(elem(rhs_in, n3, v, bo));
-                    else pr[v] = *elem(rhs_in, n3, v, bo);
+                    for (int c = 0; c < 4; ++c) pr[1 + c] = __builtin_nontemporal_load(elem(vd, n3, c, bo));
                 }
-                if (MODE == MODE_RK && L.stage >= 2) {
-                    // u^n: every later stage but the mixed form's RK4 stage 4, which
-                    // needs only the accumulator
-                    if (L.scheme == CNS_TVDRK3 || kFp64Stages<T> || L.stage != 4) {
-#pragma unroll
-                        for (int v = 0; v < 5; ++v) pu[v] = *elem(un, n3, v, bo);
-                    }
-                    // the FP64 form reads the accumulator in the last stage only
-                    if (L.scheme != CNS_TVDRK3 && (!kFp64Stages<T> || L.stage == 4)) {
-#pragma unroll
-                        for (int v = 0; v < 5; ++v) pa[v] = __builtin_nontemporal_load(elem(acc, n3, v, boa));
-                    }
-                }
-            }
-
-            T H[5];
-            {
-                int sl[6];
-#pragma unroll
-                for (int m = 0; m < 6; ++m) {
-                    const int sm = sold + 1 + m;  // slot of point j-2+m (point j+3 is in sold)
-                    sl[m] = sm >= 6 ? sm - 6 : sm;
-                }
-                interface_flux_ring<T, B, DIR, VISC, WW>(w, ring, sl, bdim, g, gamma, eps4, delta, H);
-            }
-            if (j >= j0) {
-                if constexpr (MODE == MODE_RK) {
+                if constexpr (MODE != MODE_WRITE) {
 #pragma unroll
                     for (int v = 0; v < 5; ++v) {
-                        const T r = -(H[v] - Hp[v]) * inv_dx;
-                        const gptr<T> ue = elem(unext, n3, v, bo);
-                        const gptr<double> ae = elem(acc, n3, v, boa);
-                        const double k = double(pr[v] + r);
-                        // w[2] holds the stage state at j: u^n itself in the first stage
-                        const double us = double(w[2][v]);
-                        if (L.scheme == CNS_TVDRK3) {
-                            // Shu-Osher: U1 = u + dt k; U2 = 3/4 u + 1/4 (U1 + dt k);
-                            // u^{n+1} = 1/3 u + 2/3 (U2 + dt k)
-                            if (L.stage == 1) {
-                                *ue = T(us + dt * k);
-                            } else {
+                        if constexpr (is_rk(MODE)) pr[v] = __builtin_nontemporal_load(elem(rhs_in, n3, v, bo));
+                        else pr[v] = *elem(rhs_in, n3, v, bo);
+                    }
+                }
+                if constexpr (MODE == MODE_RK2 || MODE == MODE_RK3) {
+#pragma unroll
+                    for (int v = 0; v < 5; ++v) pu[v] = *elem(un, n3, v, bo);
+                }
+                if constexpr (MODE == MODE_RK3) {
+#pragma unroll
+                    for (int v = 0; v < 5; ++v) pa[v] = __builtin_nontemporal_load(elem(acc, n3, v, boa));
+                }
+            }
+            put_flux(r + 4, w[(r + 4) % 6]);
+            const RoeCell<T> cb = roe_cell(w[(r + 2) % 6], gm1);
+            // the fence between scalars keeps the scheduler from hoisting all the LDS
+            // reads, which would hold them in registers across the reconstructions
+            T du[5], Fs[5];
+#pragma unroll
+            for (int c = 0; c < kNS; ++c) {
+                T s[5], lf, rf;
+#pragma unroll
+                for (int m = 0; m < 5; ++m) s[m] = c < 5 ? w[(r + m) % 6][c] : slot(r + m)[(c - 5) * 64];
+                weno5_cell6<WW>(s[0], s[1], s[2], s[3], s[4], eps4, lf, rf);
+                face_pair<T, DIR>(c, Lf[c], rf, du, Fs);
+                Lf[c] = lf;
+                pin(Lf[c]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            {
+                T H[5];
+                interface_flux<T, DIR>(du, Fs, ca, cb, gm1, delta, H);  // (unused at i = 0)
+                if (i >= 2) {
+#pragma unroll
+                    for (int v = 0; v < 5; ++v) {
+                        const T dH = Hp[v] - H[v];
+                        if constexpr (is_rk(MODE)) {
+                            const gptr<T> ue = elem(unext, n3, v, bo);
+                            const gptr<double> ae = elem(acc, n3, v, boa);
+                            const double kk = double(fmadd(dH, inv_dx, pr[v]));
+                            // the stage state at the point: u^n itself in the first stage
+                            const double us = double(w[(r + 1) % 6][v]);
+                            // RK4: the FP64 stage states give back dt k1 / 6 =
+                            // (U2 - u) / 3 and dt k3 / 3 = (U4 - u) / 3, so the accumulator is
+                            // written in stage 2 and read in stage 4 only.  TVD-RK3 in
+                            // Shu-Osher form: U1 = u + dt k; U2 = 3/4 u + 1/4 (U1 + dt k);
+                            // u^{n+1} = 1/3 u + 2/3 (U2 + dt k).
+                            if constexpr (MODE == MODE_RK1) {
+                                if (L.scheme == CNS_TVDRK3) {
+                                    *ue = T(fma(dt, kk, us));
+                                } else {
+                                    *ue = T(fma(0.5 * dt, kk, us));
+                                }
+                            } else if constexpr (MODE == MODE_RK2) {
                                 const double uo = double(pu[v]);
-                                if (L.stage == 2) *ue = T(0.75 * uo + 0.25 * (us + dt * k));
-                                else *ue = T((1.0 / 3.0) * uo + (2.0 / 3.0) * (us + dt * k));
-                            }
-                        } else if constexpr (kFp64Stages<T>) {
-                            // FP64 stage states give back dt k1 / 6 = (U2 - u) / 3 and
-                            // dt k3 / 3 = (U4 - u) / 3, so the accumulator is written in
-                            // stage 2 and read in stage 4 only
-                            if (L.stage == 1) {
-                                *ue = us + (0.5 * dt) * k;
-                            } else if (L.stage == 2) {
-                                const double uo = pu[v];
-                                __builtin_nontemporal_store((uo + (1.0 / 3.0) * (us - uo)) + (dt / 3.0) * k, ae);
-                                *ue = uo + (0.5 * dt) * k;
-                            } else if (L.stage == 3) {
-                                *ue = pu[v] + dt * k;
+                                if (L.scheme == CNS_TVDRK3) {
+                                    const double e = fma(dt, kk, us);
+                                    if (L.stage == 2) *ue = T(fma(0.75, uo, 0.25 * e));
+                                    else *ue = T(fma(1.0 / 3.0, uo, (2.0 / 3.0) * e));
+                                } else if (L.stage == 2) {
+                                    __builtin_nontemporal_store(fma(dt / 3.0, kk, fma(1.0 / 3.0, us - uo, uo)), ae);
+                                    *ue = T(fma(0.5 * dt, kk, uo));
+                                } else {
+                                    *ue = T(fma(dt, kk, uo));
+                                }
                             } else {
-                                *ue = (pa[v] + (1.0 / 3.0) * (us - pu[v])) + (dt / 6.0) * k;
+                                *ue = fma(dt / 6.0, kk, fma(1.0 / 3.0, us - pu[v], pa[v]));
                             }
-                        } else if (L.stage == 1) {
-                            *ae = us + (dt / 6.0) * k;
-                            *ue = T(us + (0.5 * dt) * k);
-                        } else if (L.stage == 2) {
-                            const double uo = double(pu[v]);
-                            *ae = pa[v] + (dt / 3.0) * k;
-                            *ue = T(uo + (0.5 * dt) * k);
-                        } else if (L.stage == 3) {
-                            const double uo = double(pu[v]);
-                            *ae = pa[v] + (dt / 3.0) * k;
-                            *ue = T(uo + dt * k);
+                        } else if constexpr (MODE == MODE_ACCUM) {
+                            *elem(rhs_out, n3, v, bo) = fmadd(dH, inv_dx, pr[v]);
                         } else {
-                            *ue = T(pa[v] + (dt / 6.0) * k);
+                            *elem(rhs_out, n3, v, bo) = VISC && v > 0 ? fmadd(dH, inv_dx, pr[v]) : dH * inv_dx;
                         }
                     }
-                } else {
-#pragma unroll
-                    for (int v = 0; v < 5; ++v) {
-                        const T r = -(H[v] - Hp[v]) * inv_dx;
-                        if constexpr (MODE == MODE_WRITE) *elem(rhs_out, n3, v, bo) = r;
-                        else *elem(rhs_out, n3, v, bo) = pr[v] + r;
-                    }
                 }
-            }
 #pragma unroll
-            for (int v = 0; v < 5; ++v) Hp[v] = H[v];
+                for (int v = 0; v < 5; ++v) Hp[v] = H[v];
+            }
+            ca = cb;
         };
-        // Two steps per pass: the window shifts of the first step become register
-        // renamings instead of copies (y sweep 64 -> 26, z sweep 66 -> 30 64-bit moves
-        // per point).
-        int j = j0 - 6;
-#pragma nounroll
-        for (; j + 1 < j1; j += 2) {
-            step(j);
-            step(j + 1);
+        for (int i = 0;;) {
+            step(std::integral_constant<int, 0>{}, i);
+            if (++i > len + 1) break;
+            step(std::integral_constant<int, 1>{}, i);
+            if (++i > len + 1) break;
+            step(std::integral_constant<int, 2>{}, i);
+            if (++i > len + 1) break;
+#pragma unroll
+            for (int m = 0; m < 3; ++m)
+#pragma unroll
+                for (int v = 0; v < 5; ++v) {
+                    const T tmp = w[m][v];
+                    w[m][v] = w[m + 3][v];
+                    w[m + 3][v] = tmp;
+                }
+            T *const tmp = rlo;
+            rlo = rhi;
+            rhi = tmp;
         }
-        if (j < j1) step(j);
     }
 }
 
 // ----------------------------------------------------------------------------
-// x sweep with whole periodic rows staged in LDS: one thread per point and per
-// interface, lanes along x (coalesced loads and stores), `rows` rows per block of
-// 256 threads, each thread handling up to P points.  Every interface of a row is
-// computed once; the periodic wrap happens in LDS.
+// x sweep: rows staged in LDS, lanes along x, two neighbouring cells per thread.
+//
+// A thread forms the face values of its cells A = 2s and B = 2s+1 from six staged points
+// (the indicator terms of the stencils the cells share are formed once, and each staged
+// value is read 3 times instead of 5), the flux at the face between them, then, with B's
+// right-face values of its left neighbour, the flux at A's left face; the flux at B's
+// right face comes from the right neighbour.  Against one cell per thread that halves the
+// exchanges through LDS and the barriers per cell.  512^3: 5.43 -> 4.06 ms, 1044 -> 742 VALU
+// instructions per point, 0.77 of the issue slots at the clock of the run (one cell per
+// thread 6.4 ms, 834 instructions, waiting on LDS and barriers); 128^3: 0.106 -> 0.081 ms.
+//
+// Staged per point: the state, the velocity along x and the pressure (7 fields), from
+// which the fluxes are formed as they are read; two ghost points on the left of a row and
+// two or three on its right carry the periodic wrap.
 // ----------------------------------------------------------------------------
-template <typename T, typename B, bool VISC, int P, int WW>
+template <typename T>
+using vec2 = T __attribute__((ext_vector_type(2)));
+constexpr int kXF = 7;                      // staged fields
+constexpr int kXMax = 2 * kRowThreads;      // cells per block
+// staged points of a row: its cells (rounded up to even), two ghosts on either side
+__host__ __device__ __forceinline__ int xrow_points(int nx) { return (nx + 1) / 2 * 2 + 4; }
+constexpr int kXPer = kXMax + 4;            // staged points of a chunk of a long row
+
+template <typename T>
+__device__ __forceinline__ void stage_point(T *st, int per, int pos, const T w[5], T vn, T p) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v) st[v * per + pos] = w[v];
+    st[5 * per + pos] = vn;
+    st[6 * per + pos] = p;
+}
+template <typename T>
+__device__ __forceinline__ void x_vel_pressure(const T w[5], T gm1, T &vn, T &p) {
+#pragma clang fp contract(off)
+    const T inv = rcp(w[0]);
+    vn = w[1] * inv;
+    p = gm1 * fmadd(T(-0.5), fmadd(w[1], vn, fmadd(w[2], w[2] * inv, w[3] * (w[3] * inv))), w[4]);
+}
+
+// Face values of the two cells whose six stencil points are staged from position `at`
+// (even), one scalar at a time behind a scheduling fence, so that a reconstruction holds
+// only the operands of the scalar in flight.  ar: A at its left face; du, Fs: the jumps
+// and flux sums of the face between A and B; the right-face values of B (of A when there
+// is no B) go to ex for the right neighbour.
+template <typename T, int WW>
+__device__ __forceinline__ void pair_faces(const T *st, int per, int at, T eps4, bool has_b, T *ex, T ar[kNS], T du[5],
+                                           T Fs[5]) {
+#pragma clang fp contract(off)
+    auto get = [&](int f, T q[6]) {
+        const vec2<T> *p = reinterpret_cast<const vec2<T> *>(st + f * per + at);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            const vec2<T> x = p[m];
+            q[2 * m] = x.x;
+            q[2 * m + 1] = x.y;
+        }
+    };
+    T vn[6];
+#pragma unroll
+    for (int c = 0; c < kNS; ++c) {
+        T q[6];
+        get(c < 5 ? c : c - 4, q);
+        if (c == 5) get(5, vn);
+        if (c == 5 || c == 8) {
+            T p[6];
+            get(6, p);
+#pragma unroll
+            for (int m = 0; m < 6; ++m) q[m] = c == 5 ? fmadd(q[m], vn[m], p[m]) : (q[m] + p[m]) * vn[m];
+        } else if (c > 5) {
+#pragma unroll
+            for (int m = 0; m < 6; ++m) q[m] = q[m] * vn[m];
+        }
+        T al, bl, br;
+        weno5_cell6<WW>(q[0], q[1], q[2], q[3], q[4], eps4, al, ar[c]);
+        weno5_cell6<WW>(q[1], q[2], q[3], q[4], q[5], eps4, bl, br);
+        face_pair<T, 0>(c, al, br, du, Fs);
+        ex[c * kRowThreads] = has_b ? bl : al;
+        pin(ar[c]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+template <typename T>
+__device__ __forceinline__ RoeCell<T> staged_cell(const T *st, int per, int pos, T gm1) {
+    T w[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) w[v] = st[v * per + pos];
+    return roe_cell(w, gm1);
+}
+
+// outputs at the two cells of a pair, o = offset of A: fluxes at A's left face, between
+// the cells and at B's right face
+template <typename T, bool VISC>
+__device__ __forceinline__ void write_pair(gptr<T> out, gptr<const T> vd, size_t n3, size_t o, bool vec, bool has_b,
+                                           const T Hl[5], const T Hi[5], const T Hn[5], T inv_dx) {
+#pragma clang fp contract(off)
+    T a[5], b[5], pa[4], pb[4];
+    if constexpr (VISC) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (vec) {
+                const vec2<T> x = __builtin_nontemporal_load((gptr<const vec2<T>>)(vd + c * n3 + o));
+                pa[c] = x.x;
+                pb[c] = x.y;
+            } else {
+                pa[c] = __builtin_nontemporal_load(vd + c * n3 + o);
+                pb[c] = has_b ? __builtin_nontemporal_load(vd + c * n3 + o + 1) : T(0);
+            }
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+        const T da = Hl[v] - Hi[v], db = Hi[v] - Hn[v];
+        a[v] = VISC && v > 0 ? fmadd(da, inv_dx, pa[v - 1]) : da * inv_dx;
+        b[v] = VISC && v > 0 ? fmadd(db, inv_dx, pb[v - 1]) : db * inv_dx;
+        if (vec) {
+            *(gptr<vec2<T>>)(out + v * n3 + o) = vec2<T>{a[v], b[v]};
+        } else {
+            out[v * n3 + o] = a[v];
+            if (has_b) out[v * n3 + o + 1] = b[v];
+        }
+    }
+}
+
+// whole rows of at most kXMax points, `rows` of them per block
+template <typename T, bool VISC, int WW>
 __global__ __launch_bounds__(kRowThreads, 2) void k_sweep_x_rows(Launch L0) {
+#pragma clang fp contract(off)
     const Launch L = with_params(L0);
     extern __shared__ unsigned char lds_raw[];
-    T *lds = reinterpret_cast<T *>(lds_raw);
-    // A block walks over several row groups (grid stride).  With one point per thread
-    // the global loads of the next group are issued into registers before the
-    // interface arithmetic of the current one, so their latency overlaps it; with more
-    // points per thread the extra registers would halve the occupancy, so the loads
-    // stay at the top of each group.
-    constexpr bool kPrefetch = P == 1;
-    T pw[P][5], pg[P][4];
+    T *const ex = reinterpret_cast<T *>(lds_raw);  // [9][256] face values handed to the right neighbour
+    T *const st = ex + kNS * kRowThreads;          // [7][per] staged points; later [5][256] left-face fluxes
+    // A block walks over several row groups (grid stride); the global loads of the next
+    // group are issued into registers before the arithmetic of the current one, so their
+    // latency overlaps it.
+    T pw[2][5];
     auto fetch = [&](long long vb) {
         const int bi = find_box(L.off, L.nbox, vb);
         const BoxDesc &bx = L.boxes[bi];
-        const int nx = bx.nx;
-        const long long nrows = (long long)bx.ny * bx.nz;
         const long long row0 = (vb - L.off[bi]) * bx.rows;
-        const int nact = (int)min((long long)bx.rows, nrows - row0) * nx;
-        const size_t obase = (size_t)row0 * nx, n3 = bx.n3;
-        const gptr<const T> u = glob((const T *)state_ptr(bx, L, L.in));
-        const gptr<const T> G = glob((const T *)bx.G);
+        const int nact = (int)min((long long)bx.rows, (long long)bx.ny * bx.nz - row0) * bx.nx;
+        const size_t n3 = uni64(bx.n3);
+        const gptr<const T> u = uni(glob((const T *)state_ptr(bx, L, L.in)));
 #pragma unroll
-        for (int k = 0; k < P; ++k) {
-            const int t = threadIdx.x + k * kRowThreads;
-            if (t < nact) {
-                const size_t o = obase + t;
+        for (int k = 0; k < 2; ++k) {
+            const int m = threadIdx.x + k * kRowThreads;
+            if (m < nact) {
+                const uint32_t bo = (uint32_t)(((size_t)row0 * bx.nx + m) * sizeof(T));
 #pragma unroll
-                for (int v = 0; v < 5; ++v) pw[k][v] = u[v * n3 + o];
-                if constexpr (VISC) {
-                    pg[k][0] = load_g<0, 0>(G, n3, o);
-                    pg[k][1] = load_g<0, 1>(G, n3, o);
-                    pg[k][2] = load_g<0, 2>(G, n3, o);
-                    pg[k][3] = load_g<0, 3>(G, n3, o);
-                }
+                for (int v = 0; v < 5; ++v) pw[k][v] = *elem(u, n3, v, bo);
             }
         }
     };
+    const int t = threadIdx.x;
     const VbRange R = vb_range(L.total);
-    if (kPrefetch && R.vb < R.end) fetch(R.vb);
+    if (R.vb < R.end) fetch(R.vb);
     for (long long vb = R.vb; vb < R.end; vb += R.stride) {
         const int bi = find_box(L.off, L.nbox, vb);
         const BoxDesc &bx = L.boxes[bi];
-        const int nx = bx.nx;
-        // LDS stride of a field: the block's points, or with one point per thread (every
-        // block of rows fits 256 points) the constant 256, which turns the component
-        // offsets of the stencil reads into immediates
-        const int per = P == 1 ? kRowThreads : bx.rows * nx;
-        T *su = lds;           // [5][per] states, later the interface fluxes
-        T *sf = su + 5 * per;  // [5][per] point fluxes
-        T *sg = sf + 5 * per;  // [4][per] viscous fluxes (VISC)
-        const size_t n3 = bx.n3;
-        const T gamma = T(bx.gamma), eps4 = T(4.0 * bx.eps), delta = T(bx.delta);
-        const T gm1 = gamma - T(1);
+        const int nx = bx.nx, hp = (nx + 1) / 2, rs = xrow_points(nx), per = bx.rows * rs;
+        const size_t n3 = uni64(bx.n3);
+        const T eps4 = T(4.0 * bx.eps), delta = T(bx.delta);
+        const T gm1 = T(bx.gamma) - T(1);
         const T inv_dx = T(bx.inv_h[0]);
-        const long long nrows = (long long)bx.ny * bx.nz;
         const long long row0 = (vb - L.off[bi]) * bx.rows;
-        const int nact = (int)min((long long)bx.rows, nrows - row0) * nx;  // active points
-        const size_t obase = (size_t)row0 * nx;
-        const gptr<T> out = glob((T *)(L.out_ov ? L.out_ov : bx.rhs));
-
+        const int nrow = (int)min((long long)bx.rows, (long long)bx.ny * bx.nz - row0);
+        const gptr<T> out = uni(glob((T *)(L.out_ov ? L.out_ov : bx.rhs)));
+        const gptr<const T> vd = uni(glob((const T *)bx.G));
+        // quotients of numbers below 2^16 by nx and hp: the rounding of the reciprocal moves
+        // (m + 1/2) / n by less than its distance to the next integer
+        const float inx = 1.0f / (float)nx, ihp = 1.0f / (float)hp;
 #pragma unroll
-        for (int k = 0; k < P; ++k) {
-            const int t = threadIdx.x + k * kRowThreads;
-            if (t < nact) {
-                T wk[5], gk[4], f[5];
-                if constexpr (kPrefetch) {
-#pragma unroll
-                    for (int v = 0; v < 5; ++v) wk[v] = pw[k][v];
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) gk[c] = pg[k][c];
-                } else {
-                    const gptr<const T> u = glob((const T *)state_ptr(bx, L, L.in));
-                    const gptr<const T> G = glob((const T *)bx.G);
-                    const size_t o = obase + t;
-#pragma unroll
-                    for (int v = 0; v < 5; ++v) wk[v] = u[v * n3 + o];
-                    if constexpr (VISC) {
-                        gk[0] = load_g<0, 0>(G, n3, o);
-                        gk[1] = load_g<0, 1>(G, n3, o);
-                        gk[2] = load_g<0, 2>(G, n3, o);
-                        gk[3] = load_g<0, 3>(G, n3, o);
-                    }
-                }
-                euler_flux<T, 0>(wk, gm1, f);
-#pragma unroll
-                for (int v = 0; v < 5; ++v) {
-                    su[v * per + t] = wk[v];
-                    sf[v * per + t] = f[v];
-                }
-                if constexpr (VISC) {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) sg[c * per + t] = gk[c];
-                }
+        for (int k = 0; k < 2; ++k) {
+            const int m = t + k * kRowThreads;
+            if (m < nrow * nx) {
+                const int r = (int)(((float)m + 0.5f) * inx), c = m - r * nx, pos = r * rs + 2 + c;
+                T vn, p;
+                x_vel_pressure(pw[k], gm1, vn, p);
+                stage_point(st, per, pos, pw[k], vn, p);
+                if (c <= 2 * hp + 1 - nx) stage_point(st, per, pos + nx, pw[k], vn, p);
+                if (c >= nx - 2) stage_point(st, per, pos - nx, pw[k], vn, p);
             }
         }
         __syncthreads();
-        if (kPrefetch && vb + R.stride < R.end) fetch(vb + R.stride);
-        T H[P][5];
+        if (vb + R.stride < R.end) fetch(vb + R.stride);
+        const int r = (int)(((float)t + 0.5f) * ihp), s = t - r * hp;
+        const bool act = r < nrow, has_b = 2 * s + 1 < nx;
+        T ar[kNS], Hl[5], Hi[5];
+        RoeCell<T> ca, cb;
+        if (act) {
+            const int at = r * rs + 2 * s;
+            T du[5], Fs[5];
+            pair_faces<T, WW>(st, per, at, eps4, has_b, ex + t, ar, du, Fs);
+            cb = staged_cell(st, per, at + 2, gm1);
+            interface_flux<T, 0>(du, Fs, cb, staged_cell(st, per, at + 3, gm1), gm1, delta, Hi);
 #pragma unroll
-        for (int k = 0; k < P; ++k) {
-            const int t = threadIdx.x + k * kRowThreads;
-            if (t < nact) {
-                const int r = t / nx, i = t - r * nx, rb = r * nx;
-                int q[6];
-#pragma unroll
-                for (int m = 0; m < 6; ++m) q[m] = rb + wrapi(i - 2 + m, nx);
-                interface_flux_lds<T, B, 0, VISC, WW>(su, sf, sg, per, q, gamma, eps4, delta, H[k]);  // at i+1/2
-            }
+            for (int v = 0; v < 5; ++v) pin(Hi[v]);
+            ca = staged_cell(st, per, at + 1, gm1);
         }
-        __syncthreads();  // every thread has read the staged states
+        __syncthreads();  // the exchanged values are in place, every thread has read the staging
+        if (act) {
+            T du[5], Fs[5];
+            const T *const el = ex + (s > 0 ? t - 1 : t + hp - 1);
 #pragma unroll
-        for (int k = 0; k < P; ++k) {
-            const int t = threadIdx.x + k * kRowThreads;
-            if (t < nact)
+            for (int c = 0; c < kNS; ++c) face_pair<T, 0>(c, el[c * kRowThreads], ar[c], du, Fs);
+            interface_flux<T, 0>(du, Fs, ca, cb, gm1, delta, Hl);
 #pragma unroll
-                for (int v = 0; v < 5; ++v) su[v * per + t] = H[k][v];
+            for (int v = 0; v < 5; ++v) st[v * kRowThreads + t] = Hl[v];
         }
         __syncthreads();
+        if (act) {
+            T Hn[5];
+            const T *const hn = st + (s < hp - 1 ? t + 1 : t - (hp - 1));
 #pragma unroll
-        for (int k = 0; k < P; ++k) {
-            const int t = threadIdx.x + k * kRowThreads;
-            if (t < nact) {
-                const int r = t / nx, i = t - r * nx;
-                const int qm = r * nx + wrapi(i - 1, nx);
-                const size_t o = obase + t;
-#pragma unroll
-                for (int v = 0; v < 5; ++v) out[v * n3 + o] = -(H[k][v] - su[v * per + qm]) * inv_dx;
-            }
+            for (int v = 0; v < 5; ++v) Hn[v] = hn[v * kRowThreads];
+            write_pair<T, VISC>(out, vd, n3, (size_t)(row0 + r) * nx + 2 * s, !(nx & 1), has_b, Hl, Hi, Hn, inv_dx);
         }
         __syncthreads();  // LDS is reused by the next virtual block
     }
 }
 
-// ----------------------------------------------------------------------------
-// x sweep for rows longer than a block: one block walks one periodic row in chunks of
-// kRowThreads interfaces.  Chunk c stages the points c*256-2 .. c*256+258 (the six-point
-// stencils of its interfaces, wrapped) in LDS and one thread forms one interface flux.
-// The flux difference of point i takes the interface fluxes at i-1/2 and i+1/2; the first
-// point of a chunk takes i-1/2 from the previous chunk (carried in LDS), and the row's
-// first point waits for the last chunk.  Compared with staging the whole row, the LDS of
-// a block no longer grows with the row (29 KB in FP64), so the CU holds twice the blocks
-// at 512 points per row; each chunk re-reads five stencil points of its neighbour.
-// ----------------------------------------------------------------------------
-constexpr int kChunkPts = kRowThreads + 5;  // points staged per chunk
-__host__ __device__ __forceinline__ size_t chunk_lds_bytes(size_t esz) { return (14 * kChunkPts + 5) * esz; }
+// Rows longer than kXMax: one block walks one periodic row in chunks of kXMax cells, each
+// staged with its ghost points.  A chunk's last cell waits for the next chunk, whose first
+// thread finishes it (the cell's right-face values and left-face flux are carried in
+// LDS); the row's first face waits for the last chunk.
+constexpr int kCarry = kNS + 5;           // of a chunk's last cell: right-face values, left-face flux
+constexpr int kFirst = kNS + 5 + 5 + 5;   // of the row's first cell: left-face values, right-face flux, Roe quantities of
+                                          // the cells on either side of its left face
+__host__ __device__ __forceinline__ size_t chunk_lds_bytes(size_t esz) {
+    return (kNS * kRowThreads + kXF * kXPer + 2 * kCarry + kFirst) * esz;
+}
+__host__ __device__ __forceinline__ size_t rows_lds_bytes(int nx, int rows, size_t esz) {
+    // the left-face fluxes reuse the staging
+    return (kNS * kRowThreads + std::max(kXF * rows * xrow_points(nx), 5 * kRowThreads)) * esz;
+}
 
-// FP64 Jiang-Shu and WENO-Z: at least five waves per SIMD (96 VGPRs, two of them
-// spilled around the chunk loop) hide the chunk barriers better than four: 512^3 x
-// sweep -3 %.  The mapped weights would spill more; FP32 states need fewer registers
-// (more waves by themselves, which the bound would cap).
-template <typename T, typename B, bool VISC, int WW>
-__global__ __launch_bounds__(kRowThreads)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && WW != CNS_WENO_M ? 5 : 2))) void k_sweep_x_chunks(Launch L0) {
+template <typename T, bool VISC, int WW>
+__global__ __launch_bounds__(kRowThreads, 2) void k_sweep_x_chunks(Launch L0) {
+#pragma clang fp contract(off)
     const Launch L = with_params(L0);
     extern __shared__ unsigned char lds_raw[];
-    T *su = reinterpret_cast<T *>(lds_raw);  // [5][kChunkPts] states, later the interface fluxes
-    T *sf = su + 5 * kChunkPts;              // [5][kChunkPts] point fluxes
-    T *sg = sf + 5 * kChunkPts;              // [4][kChunkPts] viscous fluxes (VISC)
-    T *carry = sg + 4 * kChunkPts;           // [5] interface flux carried to the next chunk
+    T *const ex = reinterpret_cast<T *>(lds_raw);
+    T *const st = ex + kNS * kRowThreads;
+    T *const carry = st + kXF * kXPer;      // [2][kCarry], by chunk parity
+    T *const first = carry + 2 * kCarry;    // [kFirst]
     const int t = threadIdx.x;
+    auto put_cell = [&](T *d, const RoeCell<T> &c) { d[0] = c.s, d[1] = c.v[0], d[2] = c.v[1], d[3] = c.v[2], d[4] = c.H; };
+    auto get_cell = [&](const T *d) { return RoeCell<T>{d[0], {d[1], d[2], d[3]}, d[4]}; };
     const VbRange R = vb_range(L.total);
     for (long long vb = R.vb; vb < R.end; vb += R.stride) {
         const int bi = find_box(L.off, L.nbox, vb);
@@ -963,69 +886,93 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && WW != CNS_WENO_M ? 5 : 2)))
         const int nx = bx.nx;
         const size_t n3 = uni64(bx.n3), obase = (size_t)(vb - L.off[bi]) * nx;
         const gptr<const T> u = uni(glob((const T *)state_ptr(bx, L, L.in)));
-        const gptr<const T> G = uni(glob((const T *)bx.G));
+        const gptr<const T> vd = uni(glob((const T *)bx.G));
         const gptr<T> out = uni(glob((T *)(L.out_ov ? L.out_ov : bx.rhs)));
-        const T gamma = T(bx.gamma), eps4 = T(4.0 * bx.eps), delta = T(bx.delta);
-        const T gm1 = gamma - T(1);
+        const T eps4 = T(4.0 * bx.eps), delta = T(bx.delta);
+        const T gm1 = T(bx.gamma) - T(1);
         const T inv_dx = T(bx.inv_h[0]);
-        const int nch = (nx + kRowThreads - 1) / kRowThreads;
-        T Hfirst[5];  // interface 1/2 of the row (thread 0)
+        const int nch = (nx + kXMax - 1) / kXMax;
+        // the point of one cell from the fluxes of its faces
+        auto write_cell = [&](int i, const T *Ha, const T Hb[5]) {
+            const size_t o = obase + i;
+#pragma unroll
+            for (int v = 0; v < 5; ++v) {
+                const T dH = Ha[v] - Hb[v];
+                out[v * n3 + o] = VISC && v > 0 ? fmadd(dH, inv_dx, vd[(v - 1) * n3 + o]) : dH * inv_dx;
+            }
+        };
         for (int c = 0; c < nch; ++c) {
-            const int i0 = c * kRowThreads;
-            for (int sp = t; sp < kChunkPts; sp += kRowThreads) {
+            const int i0 = c * kXMax, cells = min(kXMax, nx - i0);
+            for (int sp = t; sp < cells + 4 + (cells & 1); sp += kRowThreads) {
                 const size_t o = obase + wrapm(i0 - 2 + sp, nx);
-                T wk[5], f[5];
+                T w[5], vn, p;
 #pragma unroll
-                for (int v = 0; v < 5; ++v) wk[v] = u[v * n3 + o];
-                euler_flux<T, 0>(wk, gm1, f);
-#pragma unroll
-                for (int v = 0; v < 5; ++v) {
-                    su[v * kChunkPts + sp] = wk[v];
-                    sf[v * kChunkPts + sp] = f[v];
-                }
-                if constexpr (VISC) {
-                    sg[0 * kChunkPts + sp] = load_g<0, 0>(G, n3, o);
-                    sg[1 * kChunkPts + sp] = load_g<0, 1>(G, n3, o);
-                    sg[2 * kChunkPts + sp] = load_g<0, 2>(G, n3, o);
-                    sg[3 * kChunkPts + sp] = load_g<0, 3>(G, n3, o);
-                }
+                for (int v = 0; v < 5; ++v) w[v] = u[v * n3 + o];
+                x_vel_pressure(w, gm1, vn, p);
+                stage_point(st, kXPer, sp, w, vn, p);
             }
             __syncthreads();
-            const int i = i0 + t;
-            const bool act = i < nx;
-            T H[5];
+            const int i = i0 + 2 * t;  // cell A
+            const bool act = 2 * t < cells, has_b = 2 * t + 1 < cells, last = 2 * t + 2 >= cells;
+            T *const cn = carry + (c & 1) * kCarry, *const cp = carry + (~c & 1) * kCarry;
+            T ar[kNS], Hl[5], Hi[5];
+            RoeCell<T> ca, cb;
             if (act) {
-                int q[6];
+                T du[5], Fs[5];
+                pair_faces<T, WW>(st, kXPer, 2 * t, eps4, has_b, ex + t, ar, du, Fs);
+                cb = staged_cell(st, kXPer, 2 * t + 2, gm1);
+                interface_flux<T, 0>(du, Fs, cb, staged_cell(st, kXPer, 2 * t + 3, gm1), gm1, delta, Hi);
 #pragma unroll
-                for (int m = 0; m < 6; ++m) q[m] = t + m;  // point i-2+m
-                interface_flux_lds<T, B, 0, VISC, WW>(su, sf, sg, kChunkPts, q, gamma, eps4, delta, H);  // at i+1/2
-            }
-            __syncthreads();  // every thread has read the staged chunk
-            if (act)
+                for (int v = 0; v < 5; ++v) pin(Hi[v]);
+                ca = staged_cell(st, kXPer, 2 * t + 1, gm1);
+                if (i == 0) {
 #pragma unroll
-                for (int v = 0; v < 5; ++v) su[v * kChunkPts + t] = H[v];
-            if (c == 0 && t == 0)
+                    for (int s = 0; s < kNS; ++s) first[s] = ar[s];
 #pragma unroll
-                for (int v = 0; v < 5; ++v) Hfirst[v] = H[v];
-            __syncthreads();
-            // point i from the interfaces at i-1/2 and i+1/2; the row's first point waits
-            if (act && (c > 0 || t > 0)) {
-                const size_t o = obase + i;
-#pragma unroll
-                for (int v = 0; v < 5; ++v) {
-                    const T hm = t > 0 ? su[v * kChunkPts + t - 1] : carry[v];
-                    out[v * n3 + o] = -(H[v] - hm) * inv_dx;
+                    for (int v = 0; v < 5; ++v) first[kNS + v] = Hi[v];
+                    put_cell(first + kNS + 5, ca);
+                    put_cell(first + kNS + 10, cb);
                 }
             }
-            __syncthreads();  // carry read; the next chunk overwrites the staging
-            if (i == min(i0 + kRowThreads, nx) - 1)
+            __syncthreads();  // the exchanged values are in place, every thread has read the staging
+            if (t < kNS) cn[t] = ex[t * kRowThreads + (cells + 1) / 2 - 1];
+            if (act && i > 0) {
+                T du[5], Fs[5];
 #pragma unroll
-                for (int v = 0; v < 5; ++v) carry[v] = H[v];
+                for (int s = 0; s < kNS; ++s)
+                    face_pair<T, 0>(s, t > 0 ? ex[s * kRowThreads + t - 1] : cp[s], ar[s], du, Fs);
+                interface_flux<T, 0>(du, Fs, ca, cb, gm1, delta, Hl);
+#pragma unroll
+                for (int v = 0; v < 5; ++v) st[v * kRowThreads + t] = Hl[v];
+            }
+            if (act && last)
+#pragma unroll
+                for (int v = 0; v < 5; ++v) cn[kNS + v] = has_b ? Hi[v] : Hl[v];
+            __syncthreads();
+            // the chunk's last cell waits for the next chunk, whose first thread finishes it
+            if (act && !last) {
+                T Hn[5];
+#pragma unroll
+                for (int v = 0; v < 5; ++v) Hn[v] = st[v * kRowThreads + t + 1];
+                if (i > 0) write_pair<T, VISC>(out, vd, n3, obase + i, !(nx & 1), true, Hl, Hi, Hn, inv_dx);
+                else write_cell(1, Hi, Hn);
+            } else if (act && has_b && i > 0) {
+                write_cell(i, Hl, Hi);
+            }
+            if (t == 0 && c > 0) write_cell(i0 - 1, cp + kNS, Hl);
+            __syncthreads();  // the next chunk overwrites the staging
         }
-        __syncthreads();  // carry now holds the interface at nx-1/2
         if (t == 0) {
+            // the face at the row's wrap, its first and its last point
+            const T *const cl = carry + ((nch - 1) & 1) * kCarry;
+            T du[5], Fs[5], H[5], Hr[5];
 #pragma unroll
-            for (int v = 0; v < 5; ++v) out[v * n3 + obase] = -(Hfirst[v] - carry[v]) * inv_dx;
+            for (int s = 0; s < kNS; ++s) face_pair<T, 0>(s, cl[s], first[s], du, Fs);
+            interface_flux<T, 0>(du, Fs, get_cell(first + kNS + 5), get_cell(first + kNS + 10), gm1, delta, H);
+#pragma unroll
+            for (int v = 0; v < 5; ++v) Hr[v] = first[kNS + v];
+            write_cell(nx - 1, cl + kNS, H);
+            write_cell(0, H, Hr);
         }
         __syncthreads();  // LDS is reused by the next row
     }
@@ -1045,38 +992,36 @@ __device__ __forceinline__ double wave_max(double v) {
     return v;
 }
 // the diagnostics walk the box in the tiles of the viscous-flux kernel (32 x 8 columns,
-// visc_planes(nz) planes); one partial-sum block per tile, at most kDiagBlocksMax (then a
+// diag_planes planes); one partial-sum block per tile, at most kDiagBlocksMax (then a
 // block takes every kDiagBlocksMax-th tile)
-__host__ __device__ __forceinline__ long long diag_tiles(int nx, int ny, int nz) {
-    return (long long)((nx + kViscTX - 1) / kViscTX) * ((ny + kViscTY - 1) / kViscTY) *
-           ((nz + visc_planes(nz) - 1) / visc_planes(nz));
-}
 __host__ __device__ __forceinline__ int diag_blocks(int nx, int ny, int nz) {
     const long long t = diag_tiles(nx, ny, nz);
     return (int)(t < kDiagBlocksMax ? t : kDiagBlocksMax);
 }
 
-// block reduction of CNS_NDIAG values (slot 7 a max, the others sums) in a fixed order
-__device__ __forceinline__ void block_reduce_diag(const double acc[CNS_NDIAG], double (*red)[CNS_NDIAG], gptr<double> dst,
-                                                  const double scale[CNS_NDIAG]) {
+// block reduction over NW waves of CNS_NDIAG values (slot 7 a max, the others sums) in a
+// fixed order: those of `mask` are reduced and written to dst
+template <int NW>
+__device__ __forceinline__ void block_reduce_diag(const double acc[CNS_NDIAG], double (*red)[CNS_NDIAG],
+                                                  gptr<double> dst, unsigned mask) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
     for (int d = 0; d < CNS_NDIAG; ++d) {
+        if (!(mask >> d & 1)) continue;
         double v = (d == 7) ? wave_max(acc[d]) : wave_sum(acc[d]);
         if (lane == 0) red[wid][d] = v;
     }
     __syncthreads();
-    if (threadIdx.x < CNS_NDIAG) {
+    if (threadIdx.x < CNS_NDIAG && (mask >> threadIdx.x & 1)) {
         const int d = threadIdx.x;
         double v = red[0][d];
-        for (int w2 = 1; w2 < kDiagThreads / 64; ++w2) v = (d == 7) ? fmax(v, red[w2][d]) : v + red[w2][d];
-        if (dst) dst[d] = v * scale[d];
+        for (int w2 = 1; w2 < NW; ++w2) v = (d == 7) ? fmax(v, red[w2][d]) : v + red[w2][d];
+        if (dst) dst[d] = v;
     }
     __syncthreads();
 }
 
-static_assert(kDiagThreads == kViscTX * kViscTY && kPointThreads == kViscTX * kViscTY,
-              "the tiled kernels map one thread to each column of a kViscTX x kViscTY tile");
+static_assert(kDiagThreads == kViscTX * kViscTY, "one thread to each column of a kViscTX x kViscTY tile");
 
 // velocity m/rho of the state at linear index i (FP64, for the diagnostics)
 template <typename T>
@@ -1134,7 +1079,6 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_partial(Launch L0) {
     __shared__ double red[kDiagThreads / 64][CNS_NDIAG];
     __shared__ double pv[3][kViscTY + 4][kViscTX + 4];
     __shared__ double rv[3][3][kViscRing];  // ring velocities, slot (plane - z0) mod 3
-    const double one[CNS_NDIAG] = {1, 1, 1, 1, 1, 1, 1, 1, 1};
     int rhx, rhy;
     ring_pos(threadIdx.x, rhx, rhy);
     const bool ring = threadIdx.x < kViscRing;
@@ -1147,6 +1091,7 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_partial(Launch L0) {
         const size_t n3 = bx.n3, sz = (size_t)nx * ny;
         const int nblk = diag_blocks(nx, ny, nz);
         const long long ntile = diag_tiles(nx, ny, nz);
+        const int grp = diag_planes(nx, ny, nz);
         const int lb = (int)(vb - L.off[bi]);
         const gptr<const T> u = glob((const T *)state_ptr(bx, L, BUF_U));
         const double gamma = bx.gamma, ihx = bx.inv_h[0], ihy = bx.inv_h[1], ihz = bx.inv_h[2];
@@ -1155,7 +1100,7 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_partial(Launch L0) {
         double acc[CNS_NDIAG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
         for (long long tile = lb; tile < ntile; tile += nblk) {
             const int x0 = (int)(tile % ntx) * kViscTX, y0 = (int)((tile / ntx) % nty) * kViscTY;
-            const int z0 = (int)(tile / ((long long)ntx * nty)) * visc_planes(nz), z1 = min(z0 + visc_planes(nz), nz);
+            const int z0 = (int)(tile / ((long long)ntx * nty)) * grp, z1 = min(z0 + grp, nz);
             const bool act = x0 + tx < nx && y0 + ty < ny;
             // a column past a ragged edge wraps periodically (halo of the columns beside it)
             const size_t col = (size_t)wrapm(y0 + ty, ny) * nx + wrapm(x0 + tx, nx);
@@ -1228,7 +1173,7 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_partial(Launch L0) {
                 slot = slot == 2 ? 0 : slot + 1;
             }
         }
-        block_reduce_diag(acc, red, glob(bx.part) + (size_t)lb * CNS_NDIAG, one);
+        block_reduce_diag<kDiagThreads / 64>(acc, red, glob(bx.part) + (size_t)lb * CNS_NDIAG, ~0u);
     }
 }
 
@@ -1247,9 +1192,10 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_final(Launch L0) {
                 acc[d] = (d == 7) ? fmax(acc[d], v) : acc[d] + v;
             }
         const double inv = 1.0 / (double)bx.n3;
-        const double scale[CNS_NDIAG] = {inv, inv, inv, inv, inv, inv, inv, 1.0, 1.0};
         const gptr<double> dst = L.diag ? glob(L.diag) + ((size_t)bi * L.diag_box_stride + L.step) * CNS_NDIAG : nullptr;
-        block_reduce_diag(acc, red, dst, scale);
+        block_reduce_diag<kDiagThreads / 64>(acc, red, dst, ~0u);
+        // the thread that wrote a mean's sum divides it by the number of points
+        if (dst && threadIdx.x < 7) dst[threadIdx.x] *= inv;
     }
 }
 
@@ -1356,20 +1302,18 @@ __global__ void k_set_params(GraphParams *gp, const void *u, double *diag, doubl
 // ----------------------------------------------------------------------------
 // host side: shapes, block counts, launchers
 // ----------------------------------------------------------------------------
-int rows_for(int nx) {
-    int g = 1;
-    while (nx * g * 2 <= kRowThreads) g *= 2;
-    return g;
+// as many rows as the pairs of a block's threads hold, the staging (7 fields) at most
+// 34 KiB in FP64, which keeps three blocks on a CU
+int rows_max(int nx) {
+    return std::max(1, std::min(kRowThreads / ((nx + 1) / 2), 608 / xrow_points(nx)));
 }
 
-bool rows_fit(int nx, int rows, size_t esz, int *P) {
+size_t xrows_lds(int nx, int rows, size_t esz) { return rows_lds_bytes(nx, rows, esz); }
+
+bool rows_fit(int nx, int rows, size_t esz) {
     const long long per = (long long)rows * nx;
-    const long long p = (per + kRowThreads - 1) / kRowThreads;
-    if (P) *P = (int)p;
-    return rows >= 1 && p <= 4 && (size_t)14 * per * esz <= (size_t)kRowLdsMax;
+    return rows >= 1 && per <= 4 * kRowThreads && (size_t)14 * per * esz <= (size_t)kRowLdsMax;
 }
-
-static long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
 
 long long family_blocks(const BoxDesc &b, int fam, int block) {
     switch (fam) {
@@ -1389,38 +1333,10 @@ long long family_blocks(const BoxDesc &b, int fam, int block) {
         }
         case F_DIAG: return diag_blocks(b.nx, b.ny, b.nz);
         case F_VISC:
-            return cdiv(b.nx, kViscTX) * cdiv(b.ny, kViscTY) * cdiv(b.nz, visc_planes(b.nz));
+            return cdiv(b.nx, kViscTX) * cdiv(b.ny, kViscTY) * cdiv(b.nz, b.vsz);
         case F_BOX: return 1;
     }
     return 0;
-}
-
-static Launch make_launch(const Batch &bt, int fam) {
-    Launch L{};
-    L.gp = bt.gp;
-    L.boxes = bt.d_boxes;
-    L.off = bt.d_off[fam];
-    L.nbox = bt.nbox;
-    L.total = bt.total[fam];
-    return L;
-}
-
-static Launch with_family(const Batch &bt, Launch L, int fam) {
-    L.off = bt.d_off[fam];
-    L.total = bt.total[fam];
-    return L;
-}
-
-static inline unsigned grid_for(long long total) {
-    const long long cap = 1ll << 30;
-    return (unsigned)(total < cap ? total : cap);
-}
-
-// launched blocks of family fam: bt.grid[fam] when set (a persistent launch), else one
-// per virtual block
-static inline unsigned grid_of(const Batch &bt, int fam, long long total) {
-    const long long g = bt.grid[fam];
-    return grid_for(g > 0 && g < total ? g : total);
 }
 
 void launch_init_state(int prec, size_t n3, double gamma, const double *rho, const double *vel, const double *p,
@@ -1438,55 +1354,76 @@ void launch_fill(int prec, size_t n, void *out, hipStream_t s) {
     else hipLaunchKernelGGL(k_fill<float>, dim3(g), dim3(256), 0, s, n, (float *)out);
 }
 
+// The launchers are templated on the state type: float hands over to the mixed form's own.
+template <typename T>
+constexpr bool kMixed = std::is_same<T, float>::value;
+
 template <typename T, bool DIAG = false>
 static void visc_fields(const Batch &bt, Launch L) {
-    L = with_family(bt, L, F_VISC);
-    if (!L.total) return;
-    ProfScope ps(bt.prof, K_VISC_FLUX, bt.stream);
-    hipLaunchKernelGGL((k_visc_flux<T, DIAG>), dim3(grid_of(bt, F_VISC, L.total)), dim3(kPointThreads), 0, bt.stream,
-                       L);
+    if constexpr (kMixed<T>) {
+        mixed::visc_fields(bt, L);
+    } else {
+        L = with_family(bt, L, F_VISC);
+        if (!L.total) return;
+        ProfScope ps(bt.prof, K_VISC_FLUX, bt.stream);
+        hipLaunchKernelGGL((k_visc<T, DIAG>), dim3(grid_of(bt, F_VISC, L.total)),
+                           dim3(ViscTile<T>::kThreads), 0, bt.stream,
+                           L);
+    }
 }
+
+// flux ring of the marching sweeps: 6 slots x 4 per thread
+static size_t sweep_lds_bytes(int block) { return 24 * (size_t)block * sizeof(double); }
 
 template <typename T, int DIR, int MODE, bool VISC>
 static void sweep_t(const Batch &bt, const Launch &L) {
     const dim3 g(grid_of(bt, F_SWEEP_X + DIR, L.total)), b(bt.block);
-    const size_t ring = 30 * (size_t)bt.block * sizeof(T);  // point-flux ring, 6 slots x 5 per thread
+    const size_t ring = sweep_lds_bytes(bt.block);
     if (bt.weights == CNS_WENO_Z)
-        hipLaunchKernelGGL((k_sweep<T, double, DIR, MODE, VISC, CNS_WENO_Z>), g, b, ring, bt.stream, L);
+        hipLaunchKernelGGL((k_sweep<T, DIR, MODE, VISC, CNS_WENO_Z>), g, b, ring, bt.stream, L);
     else if (bt.weights == CNS_WENO_M)
-        hipLaunchKernelGGL((k_sweep<T, double, DIR, MODE, VISC, CNS_WENO_M>), g, b, ring, bt.stream, L);
+        hipLaunchKernelGGL((k_sweep<T, DIR, MODE, VISC, CNS_WENO_M>), g, b, ring, bt.stream, L);
     else
-        hipLaunchKernelGGL((k_sweep<T, double, DIR, MODE, VISC, CNS_WENO_JS>), g, b, ring, bt.stream, L);
+        hipLaunchKernelGGL((k_sweep<T, DIR, MODE, VISC, CNS_WENO_JS>), g, b, ring, bt.stream, L);
 }
 
 template <typename T, int MODE>
 static void sweep(const Batch &bt, Launch L, int dir, bool visc) {
-    L = with_family(bt, L, F_SWEEP_X + dir);
-    if (!L.total) return;
-    if (visc) {
-        if (dir == 0) sweep_t<T, 0, MODE, true>(bt, L);
-        else if (dir == 1) sweep_t<T, 1, MODE, true>(bt, L);
-        else sweep_t<T, 2, MODE, true>(bt, L);
+    if constexpr (kMixed<T>) {
+        if constexpr (MODE == MODE_WRITE) mixed::sweep_write(bt, L, dir, visc);
+        else mixed::sweep_accum(bt, L, dir, visc);
     } else {
-        if (dir == 0) sweep_t<T, 0, MODE, false>(bt, L);
-        else if (dir == 1) sweep_t<T, 1, MODE, false>(bt, L);
-        else sweep_t<T, 2, MODE, false>(bt, L);
+        L = with_family(bt, L, F_SWEEP_X + dir);
+        if (!L.total) return;
+        if (dir == 0) {  // the writing sweep, which takes the viscous term
+            if constexpr (MODE == MODE_WRITE) {
+                if (visc) sweep_t<T, 0, MODE, true>(bt, L);
+                else sweep_t<T, 0, MODE, false>(bt, L);
+            }
+        } else if (dir == 1) {
+            if constexpr (!is_rk(MODE)) sweep_t<T, 1, MODE, false>(bt, L);
+        } else {
+            sweep_t<T, 2, MODE, false>(bt, L);
+        }
     }
+}
+
+// the z sweep with the fused update of stage L.stage of L.scheme
+template <typename T>
+static void sweep_rk(const Batch &bt, const Launch &L) {
+    if constexpr (kMixed<T>) mixed::sweep_rk(bt, L, bt.any_visc);
+    else if (L.stage == 1) sweep<T, MODE_RK1>(bt, L, 2, false);
+    else if (L.scheme == CNS_RK4 && L.stage == 4) sweep<T, MODE_RK3>(bt, L, 2, false);
+    else sweep<T, MODE_RK2>(bt, L, 2, false);
 }
 
 template <typename T, bool VISC, int WW>
 static void xrows_tw(const Batch &bt, const Launch &L) {
-    // about four row groups per block when the loads of the next one are prefetched
+    // about four row groups per block, so that the loads of the next one are prefetched
     const long long nb = bt.grid[F_XROWS] > 0 ? std::min<long long>(bt.grid[F_XROWS], L.total)
-                         : (bt.rowP == 1 ? std::max<long long>(std::min<long long>(L.total, 2048), L.total / 4)
-                                         : L.total);
-    const dim3 g(grid_for(nb)), b(kRowThreads);
-    switch (bt.rowP) {
-        case 1: hipLaunchKernelGGL((k_sweep_x_rows<T, double, VISC, 1, WW>), g, b, bt.rowLds, bt.stream, L); break;
-        case 2: hipLaunchKernelGGL((k_sweep_x_rows<T, double, VISC, 2, WW>), g, b, bt.rowLds, bt.stream, L); break;
-        case 3: hipLaunchKernelGGL((k_sweep_x_rows<T, double, VISC, 3, WW>), g, b, bt.rowLds, bt.stream, L); break;
-        default: hipLaunchKernelGGL((k_sweep_x_rows<T, double, VISC, 4, WW>), g, b, bt.rowLds, bt.stream, L); break;
-    }
+                                              : std::max<long long>(std::min<long long>(L.total, 2048), L.total / 4);
+    hipLaunchKernelGGL((k_sweep_x_rows<T, VISC, WW>), dim3(grid_for(nb)), dim3(kRowThreads), bt.rowLds, bt.stream,
+                       L);
 }
 
 template <typename T, bool VISC>
@@ -1501,29 +1438,33 @@ static void xchunks_t(const Batch &bt, const Launch &L) {
     const dim3 g(grid_of(bt, F_XCHUNK, L.total)), b(kRowThreads);
     const size_t lds = chunk_lds_bytes(sizeof(T));
     if (bt.weights == CNS_WENO_Z)
-        hipLaunchKernelGGL((k_sweep_x_chunks<T, double, VISC, CNS_WENO_Z>), g, b, lds, bt.stream, L);
+        hipLaunchKernelGGL((k_sweep_x_chunks<T, VISC, CNS_WENO_Z>), g, b, lds, bt.stream, L);
     else if (bt.weights == CNS_WENO_M)
-        hipLaunchKernelGGL((k_sweep_x_chunks<T, double, VISC, CNS_WENO_M>), g, b, lds, bt.stream, L);
+        hipLaunchKernelGGL((k_sweep_x_chunks<T, VISC, CNS_WENO_M>), g, b, lds, bt.stream, L);
     else
-        hipLaunchKernelGGL((k_sweep_x_chunks<T, double, VISC, CNS_WENO_JS>), g, b, lds, bt.stream, L);
+        hipLaunchKernelGGL((k_sweep_x_chunks<T, VISC, CNS_WENO_JS>), g, b, lds, bt.stream, L);
 }
 
 // x sweep (always the first, writing sweep): the rows kernel for boxes whose rows fill at
 // most one block, the chunked rows kernel for longer rows, the marching kernel when chosen
 template <typename T>
 static void sweep_x(const Batch &bt, const Launch &L, bool visc) {
-    ProfScope ps(bt.prof, K_SWEEP_X, bt.stream);
-    const Launch R = with_family(bt, L, F_XROWS);
-    if (R.total) {
-        if (visc) xrows_t<T, true>(bt, R);
-        else xrows_t<T, false>(bt, R);
+    if constexpr (kMixed<T>) {
+        mixed::sweep_x(bt, L, visc);
+    } else {
+        ProfScope ps(bt.prof, K_SWEEP_X, bt.stream);
+        const Launch R = with_family(bt, L, F_XROWS);
+        if (R.total) {
+            if (visc) xrows_t<T, true>(bt, R);
+            else xrows_t<T, false>(bt, R);
+        }
+        const Launch C = with_family(bt, L, F_XCHUNK);
+        if (C.total) {
+            if (visc) xchunks_t<T, true>(bt, C);
+            else xchunks_t<T, false>(bt, C);
+        }
+        sweep<T, MODE_WRITE>(bt, L, 0, visc);
     }
-    const Launch C = with_family(bt, L, F_XCHUNK);
-    if (C.total) {
-        if (visc) xchunks_t<T, true>(bt, C);
-        else xchunks_t<T, false>(bt, C);
-    }
-    sweep<T, MODE_WRITE>(bt, L, 0, visc);
 }
 
 template <typename T>
@@ -1567,9 +1508,16 @@ static void viscous_t(const Batch &bt, const void *u_ov, void *out_ov) {
     Launch L = make_launch(bt, F_POINT);
     L.in = BUF_U;
     L.u_ov = u_ov;
-    L.out_ov = out_ov;
-    visc_fields<T>(bt, L);
-    hipLaunchKernelGGL(k_visc_div<T>, dim3(grid_for(L.total)), dim3(kPointThreads), 0, bt.stream, L);
+    if constexpr (kMixed<T>) {
+        L.out_ov = out_ov;
+        mixed::viscous(bt, L);
+    } else {
+        // rows 1-4 of the output; the density row has no viscous term
+        const size_t n3 = bt.n3_0;
+        L.v_ov = (T *)out_ov + n3;
+        launch_fill(bt.prec, n3, out_ov, bt.stream);
+        visc_fields<T>(bt, L);
+    }
 }
 
 void launch_viscous(const Batch &bt, const void *u_ov, void *out_ov) {
@@ -1696,7 +1644,7 @@ static void rk4_step_t(const Batch &bt, const void *u_ov, double dt_ov, double *
             sweep<T, MODE_ACCUM>(bt, L, 1, bt.any_visc);
         }
         ProfScope ps(bt.prof, K_SWEEP_Z, bt.stream);
-        sweep<T, MODE_RK>(bt, L, 2, bt.any_visc);
+        sweep_rk<T>(bt, L);
     }
     if (diag && diag_own) diag_t<T>(bt, u_ov, diag, stride, step);
 }
@@ -1736,7 +1684,7 @@ static void tvdrk3_step_t(const Batch &bt, const void *u_ov, double dt_ov, doubl
             sweep<T, MODE_ACCUM>(bt, L, 1, bt.any_visc);
         }
         ProfScope ps(bt.prof, K_SWEEP_Z, bt.stream);
-        sweep<T, MODE_RK>(bt, L, 2, bt.any_visc);
+        sweep_rk<T>(bt, L);
     }
     if (diag && diag_own) diag_t<T>(bt, u_ov, diag, stride, step);
 }
@@ -1800,21 +1748,20 @@ static long long cu_count() {
 
 long long resident_sweep_blocks(const Batch &bt) {
     int n = 0;
-    const size_t ring = 30 * (size_t)bt.block * (bt.prec == CNS_FP64 ? sizeof(double) : sizeof(float));
-    hipError_t e = bt.prec == CNS_FP64
-                       ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                             &n, k_sweep<double, double, 2, MODE_RK, true, CNS_WENO_JS>, bt.block, ring)
-                       : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                             &n, k_sweep<float, double, 2, MODE_RK, true, CNS_WENO_JS>, bt.block, ring);
-    return (e == hipSuccess && n > 0 ? n : 1) * cu_count();
+    if (bt.prec != CNS_FP64) n = mixed::resident_sweep_blocks(bt.block);
+    else if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_sweep<double, 2, MODE_RK2, false, CNS_WENO_JS>, bt.block,
+                                                          sweep_lds_bytes(bt.block)) != hipSuccess)
+        n = 0;
+    return (n > 0 ? n : 1) * cu_count();
 }
 
 long long resident_tile_blocks(const Batch &bt) {
     int n = 0;
-    hipError_t e = bt.prec == CNS_FP64
-                       ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_visc_flux<double, false>, kPointThreads, 0)
-                       : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_visc_flux<float, false>, kPointThreads, 0);
-    return (e == hipSuccess && n > 0 ? n : 1) * cu_count();
+    if (bt.prec != CNS_FP64) n = mixed::resident_tile_blocks();
+    else if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_visc<double, false>, ViscTile<double>::kThreads, 0) !=
+             hipSuccess)
+        n = 0;
+    return (n > 0 ? n : 1) * cu_count();
 }
 
 void prof_flush(Prof *p) {
