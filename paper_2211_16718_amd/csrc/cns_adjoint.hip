@@ -4,10 +4,11 @@
 // (dR/du)^T rbar of the semi-discrete operator R(u) = -sum_d (H_{j+1/2} - H_{j-1/2})/dx_d
 // + sum_d D_d G^v_d is assembled as
 //   convective part, per direction d:  Hbar_{j+1/2} = (rbar_{j+1} - rbar_j)/dx_d;
-//     k_adj_conv<d>: one thread per interface forms the local product of the
+//     k_adj_conv<x>: one thread per interface forms the local product of the
 //     interface flux (the point-flux and state adjoints of the six cells it reads)
 //     and adds them, in a fixed order, into LDS accumulators of the cells, which are
 //     then finished and written;
+//     k_adj_march<y, z>: a thread marches along a segment of a line, one cell a step;
 //   viscous part: the adjoint of a central difference is minus the same central
 //     difference, so Gbar_d = -D_d rbar; k_adj_visc maps it through the viscous
 //     fluxes to the adjoints of the velocity/temperature gradients and of the
@@ -17,6 +18,7 @@
 #include <hip/hip_runtime.h>
 
 #include "cns_adjoint.h"
+#include "cns_batch.h"
 #include "cns_device_adj.h"
 #include "cns_internal.h"
 
@@ -239,6 +241,238 @@ __global__ __launch_bounds__(256, 2) void k_adj_conv(AdjGeom g, const double *__
             if (accumulate) ubar[v * n3 + q] += s;
             else ubar[v * n3 + q] = s;
         }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Convective adjoint along DIR = y or z by cells: ubar += the terms of every cell's
+// reconstructions and of every face's dissipation.
+//
+// A thread marches over a segment s0 .. s1-1 of one periodic line.  In step j it transposes
+// the nine reconstructions of cell j (the state and the fluxes 1-4; the mass flux is the
+// momentum along the line, so its adjoint joins that component's), for which it has formed
+// dub = M^T Db of the right face from the states j, j+1, and the left face's a step before;
+// the values then give the jump at the left face, whose dissipation is transposed for the
+// states j-1, j.  A reconstruction's terms go to cells j-2 .. j+2: the sums of the four
+// cells not yet complete stay in registers and move up one place as they are added to;
+// cell j-2 is complete, and leaves as J^T F + U (J the flux Jacobian: once per cell).
+// Nothing is shared between threads, so the march has no barrier: LDS holds each thread's
+// own window of five cells (state, normal velocity, pressure) and dub.
+//
+// Segments meet without redundant cells.  A thread adds to ubar cells s0-2 .. s1-3 during
+// its march, and after a barrier (the segments of a line are in one block) the sums of
+// cells s1-2 .. s1+1 that it still holds; a segment is at least four cells long, so in
+// either phase no two threads touch the same cell.  The face between two segments is the
+// left one's: it forms the right-biased values of cell s1 again.
+//
+// Bound by FP64 issue: 1440 instructions a step at 78 % of the issue rate, two waves per SIMD
+// (the sums and face values take all 256 registers).  128^3: 167 us, 215 with a thread per
+// interface, six-point stencils and the sums in LDS; 130 x 90 x 66: 86 against 117.
+// ---------------------------------------------------------------------------
+constexpr int kAmThreads = 256;
+constexpr int kAmCells = 5, kAmComp = 7;  // cells of the window, scalars of a cell
+
+template <int DIR, int WW>
+__global__ __launch_bounds__(kAmThreads, 2) void k_adj_march(AdjGeom g, const double *u_,
+                                                             const double *rbar_, double *ubar_, int Lb,
+                                                             int nseg) {
+    __shared__ double win[(kAmCells * kAmComp + 5) * kAmThreads];  // 80 KiB: two blocks on a CU
+    constexpr int NT = kAmThreads;
+    const auto u = (gptr<const double>)u_, rbar = (gptr<const double>)rbar_;
+    const auto ubar = (gptr<double>)ubar_;
+    const int t = threadIdx.x, seg = t / Lb;
+    const size_t n3 = g.n3, nlines = DIR == 1 ? (size_t)g.nx * g.nz : (size_t)g.nx * g.ny;
+    const size_t line = (size_t)blockIdx.x * Lb + (t - seg * Lb);
+    const int n = DIR == 1 ? g.ny : g.nz;
+    // byte offsets within a component
+    const uint32_t stride = (uint32_t)(8 * (DIR == 1 ? (size_t)g.nx : (size_t)g.nx * g.ny));
+    const uint32_t base = (uint32_t)(8 * (DIR == 1 ? line / g.nx * ((size_t)g.nx * g.ny) + line % g.nx : line));
+    const bool ok = seg < nseg && line < nlines;
+    const int s0 = (int)((long long)seg * n / nseg), s1 = (int)((long long)(seg + 1) * n / nseg);
+    const int len = ok ? s1 - s0 : 0, kmax = (n + nseg - 1) / nseg;
+    const double ih12 = g.ih[DIR] * (1.0 / 12.0), gm1 = g.gamma - 1.0, eps4 = 4.0 * g.eps;
+    double *const dubL = win + kAmCells * kAmComp * NT + t;  // dub of the left face
+    auto at = [&](int slot, int v) -> double & { return win[(slot * kAmComp + v) * NT + t]; };
+    auto cell = [&](int j) { return base + (uint32_t)wrapj(j, n) * stride; };
+    auto load5 = [&](gptr<const double> p, uint32_t c, double w[5]) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) w[v] = *elem(p, n3, v, c);
+    };
+    auto keep = [&](int slot, const double w[5]) {
+        const double inv = rcp(w[0]), vx = w[1] * inv, vy = w[2] * inv, vz = w[3] * inv;
+#pragma unroll
+        for (int v = 0; v < 5; ++v) at(slot, v) = w[v];
+        at(slot, 5) = DIR == 1 ? vy : vz;
+        at(slot, 6) = gm1 * (w[4] - 0.5 * (w[1] * vx + w[2] * vy + w[3] * vz));
+    };
+    auto states = [&](int sa, int sb, double a[5], double b[5]) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) a[v] = at(sa, v), b[v] = at(sb, v);
+    };
+    // Everything per face is held for six times the reconstructed values: H = Hbar / 12, dub =
+    // M^T Db / 6 = -M^T H, the jumps 6 du with H in place of Hbar / 2.
+    // -M^T H of the face between the cells at sa and sb
+    auto jump_adjoint = [&](int sa, int sb, const double H[5], double dub[5]) {
+        double a[5], b[5], Db[5];
+        states(sa, sb, a, b);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Db[v] = -H[v], dub[v] = 0.0;
+        const RoeFace R = roe_face<DIR>(a, at(sa, 6), b, at(sb, 6), gm1, g.delta);
+        roe_jump_vjp<DIR>(R, gm1, Db, dub);
+    };
+    double AU[4][5], AF[4][4];  // sums of cells j-2 .. j+1 before step j
+    double UL[5], Hl[5];        // six times the left-biased values, and H, of the left face
+    auto state_adjoint = [&](int sa, int sb, double h, const double du6[5], double ab[5], double bb[5]) {
+        double a[5], b[5], Db[5];
+        states(sa, sb, a, b);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Db[v] = h * Hl[v];
+        const RoeFace R = roe_face<DIR>(a, at(sa, 6), b, at(sb, 6), gm1, g.delta);
+        double vbar[3], Hbar;
+        roe_mean_vjp<DIR>(R, gm1, g.delta, du6, Db, vbar, Hbar);
+        pin(vbar[0]), pin(vbar[1]), pin(vbar[2]), pin(Hbar);
+        adj_stage_fence();
+        states(sa, sb, a, b);
+        roe_cells_vjp(R, a, at(sa, 6), b, at(sb, 6), gm1, vbar, Hbar, ab, bb);
+    };
+    // ubar at q += J^T f + us, J of the cell at slot
+    auto finish = [&](int slot, const double us[5], const double f[4], const double old[5], uint32_t q) {
+        double w[5], fb[5] = {0.0, f[0], f[1], f[2], f[3]}, out[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) w[v] = at(slot, v), out[v] = us[v];
+        euler_flux_vjp<DIR>(w, gm1, fb, out);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) *elem(ubar, n3, v, q) = old[v] + out[v];
+    };
+    double rb[5], rn[5];  // rbar of cells j and j+1
+    if (ok) {
+        double w[kAmCells][5], rm[5];
+#pragma unroll
+        for (int m = 0; m < kAmCells; ++m) load5(u, cell(s0 - 2 + m), w[m]);
+        load5(rbar, cell(s0 - 1), rm);
+        load5(rbar, cell(s0), rb);
+        load5(rbar, cell(s0 + 1), rn);
+#pragma unroll
+        for (int m = 0; m < kAmCells; ++m) keep(m, w[m]);
+        double dub[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Hl[v] = (rb[v] - rm[v]) * ih12, UL[v] = 0.0;
+        jump_adjoint(1, 2, Hl, dub);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) dubL[v * NT] = dub[v];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+#pragma unroll
+            for (int v = 0; v < 5; ++v) AU[m][v] = 0.0;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) AF[m][v] = 0.0;
+        }
+    }
+    int o0 = 0, o1 = 1, o2 = 2, o3 = 3, o4 = 4;  // slots of cells j-2 .. j+2
+    for (int k = 0; k < kmax; ++k) {
+        if (k < len) {
+            const int j = s0 + k;
+            double Hr[5], dub[5], du[5], dU[5], dF[4], old[5], un[5];  // un: state of cell j+3
+#pragma unroll
+            for (int v = 0; v < 5; ++v) Hr[v] = (rn[v] - rb[v]) * ih12, rb[v] = rn[v], pin(Hr[v]);
+            const int o[5] = {o0, o1, o2, o3, o4};
+            double x[5], xn[5], xb[5], L6, R6;
+            // the fluxes; each component's loads from LDS are issued one component ahead
+            {
+                double vn[5], p[5];
+#pragma unroll
+                for (int m = 0; m < 5; ++m) vn[m] = at(o[m], 5), xn[m] = at(o[m], 1);
+#pragma unroll
+                for (int v = 1; v < 5; ++v) {
+#pragma unroll
+                    for (int m = 0; m < 5; ++m) {
+                        x[m] = xn[m] * vn[m];
+                        if (v == 1 + DIR) x[m] += at(o[m], 6);
+                        if (v == 4) x[m] += p[m] * vn[m];
+                        if (v < 4) xn[m] = at(o[m], v + 1);
+                        if (v == 3) p[m] = at(o[m], 6);
+                    }
+                    adj_stage_fence();
+                    weno5_cell_vjp<WW>(x, eps4, Hr[v], Hl[v], xb, L6, R6);
+                    dF[v - 1] = AF[0][v - 1] + xb[0];
+#pragma unroll
+                    for (int m = 0; m < 3; ++m) AF[m][v - 1] = AF[m + 1][v - 1] + xb[m + 1];
+                    AF[3][v - 1] = xb[4];
+                    pin(dF[v - 1]);
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) pin(AF[m][v - 1]);
+                    adj_stage_fence();
+                }
+            }
+            jump_adjoint(o2, o3, Hr, dub);
+#pragma unroll
+            for (int v = 0; v < 5; ++v) pin(dub[v]);
+            adj_stage_fence();
+            // the states, with the mass flux's terms in the momentum along the line
+            double dl = dubL[0];
+#pragma unroll
+            for (int m = 0; m < 5; ++m) xn[m] = at(o[m], 0);
+#pragma unroll
+            for (int v = 0; v < 5; ++v) {
+#pragma unroll
+                for (int m = 0; m < 5; ++m) x[m] = xn[m];
+                double Lb = -dub[v], Rb = dl;
+                dubL[v * NT] = dub[v];
+                if (v == 1 + DIR) Lb += Hr[0], Rb += Hl[0];
+                if (v < 4) {
+#pragma unroll
+                    for (int m = 0; m < 5; ++m) xn[m] = at(o[m], v + 1);
+                    dl = dubL[(v + 1) * NT];
+                }
+                if (v == 1) load5(u, cell(j + 3), un);
+                if (v == 2) load5(ubar, cell(j - 2), old);
+                if (v == 4) load5(rbar, cell(j + 2), rn);
+                adj_stage_fence();
+                weno5_cell_vjp<WW>(x, eps4, Lb, Rb, xb, L6, R6);
+                du[v] = R6 - UL[v];
+                UL[v] = L6;
+                dU[v] = AU[0][v] + xb[0];
+#pragma unroll
+                for (int m = 0; m < 3; ++m) AU[m][v] = AU[m + 1][v] + xb[m + 1];
+                AU[3][v] = xb[4];
+                pin(du[v]), pin(UL[v]), pin(dU[v]);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) pin(AU[m][v]);
+                adj_stage_fence();
+            }
+            finish(o0, dU, dF, old, cell(j - 2));
+            keep(o0, un);
+            adj_stage_fence();
+            state_adjoint(o1, o2, k > 0 ? -1.0 : 0.0, du, AU[0], AU[1]);
+#pragma unroll
+            for (int v = 0; v < 5; ++v) pin(AU[0][v]), pin(AU[1][v]);
+#pragma unroll
+            for (int v = 0; v < 5; ++v) Hl[v] = Hr[v];
+        }
+        const int f = o0;
+        o0 = o1, o1 = o2, o2 = o3, o3 = o4, o4 = f;
+    }
+    int e0 = len % kAmCells;  // slot of cell s1-2
+    auto slot_of = [&](int m) { return e0 + m >= kAmCells ? e0 + m - kAmCells : e0 + m; };
+    if (ok) {
+        double du[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+            double L6, R6;
+            weno5_cell6<WW>(at(slot_of(0), v), at(slot_of(1), v), at(slot_of(2), v), at(slot_of(3), v), at(slot_of(4), v),
+                            eps4, L6, R6);
+            du[v] = R6 - UL[v];
+        }
+        state_adjoint(slot_of(1), slot_of(2), -1.0, du, AU[1], AU[2]);
+    }
+    __syncthreads();
+    if (!ok) return;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const uint32_t q = cell(s1 - 2 + m);
+        double old[5];
+        load5(ubar, q, old);
+        finish(slot_of(m), AU[m], AF[m], old, q);
     }
 }
 
@@ -640,17 +874,37 @@ __global__ void k_ic_vjp(size_t n3, const double *__restrict__ rho, const double
 // ----------------------------------------------------------------------------
 static inline dim3 grid1(size_t n) { return dim3((unsigned)((n + 255) / 256)); }
 
+// Lines and segments per block of k_adj_march (their product is at most the block).  The
+// busiest CU decides: of its blocks two run side by side, one alone takes about 0.7 of the
+// two's time, and a segment adds 0.4 steps of its own to its cells.  So small boxes get
+// short segments on every CU, and ragged ones a split that leaves no nearly empty round.
+struct MarchSplit {
+    int Lb, nseg;
+};
+static MarchSplit march_split(size_t nlines, int n) {
+    MarchSplit best{64, 1};
+    double cost = 0.0;
+    for (int Lb = 64; Lb >= 8; --Lb) {
+        const int nseg = std::min(kAmThreads / Lb, n / 4);
+        const size_t k = ((nlines + Lb - 1) / Lb + 255) / 256;
+        const double c = (double)((n + nseg - 1) / nseg + 0.4) * ((double)(k / 2) * 2.0 + (k % 2 ? 1.4 : 0.0));
+        if (Lb == 64 || c < cost) best = MarchSplit{Lb, nseg}, cost = c;
+    }
+    return best;
+}
+
 template <int WW>
 static void adj_conv(const BoxDesc &b, hipStream_t s, const AdjGeom &g, const double *u, const double *rbar,
                      double *ubar) {
-    // blocks: x, 4 rows each; y, z: one x tile of the lines at one z (y) each
+    // blocks of the x kernel: 4 rows each
     const unsigned bx = (unsigned)(((size_t)b.ny * b.nz + 3) / 4);
-    constexpr int TB = 4 * AdjConvShape<1>::LW;
-    static_assert(AdjConvShape<2>::LW == AdjConvShape<1>::LW, "y and z blocks alike");
-    const unsigned ntx = (unsigned)((b.nx + TB - 1) / TB);
     hipLaunchKernelGGL((k_adj_conv<0, WW>), dim3(bx), dim3(256), 0, s, g, u, rbar, ubar, 0);
-    hipLaunchKernelGGL((k_adj_conv<1, WW>), dim3(ntx * (unsigned)b.nz), dim3(256), 0, s, g, u, rbar, ubar, 1);
-    hipLaunchKernelGGL((k_adj_conv<2, WW>), dim3(ntx * (unsigned)b.ny), dim3(256), 0, s, g, u, rbar, ubar, 1);
+    const size_t ly = (size_t)b.nx * b.nz, lz = (size_t)b.nx * b.ny;
+    const MarchSplit my = march_split(ly, b.ny), mz = march_split(lz, b.nz);
+    hipLaunchKernelGGL((k_adj_march<1, WW>), dim3((unsigned)((ly + my.Lb - 1) / my.Lb)), dim3(kAmThreads), 0, s, g, u, rbar,
+                       ubar, my.Lb, my.nseg);
+    hipLaunchKernelGGL((k_adj_march<2, WW>), dim3((unsigned)((lz + mz.Lb - 1) / mz.Lb)), dim3(kAmThreads), 0, s, g, u, rbar,
+                       ubar, mz.Lb, mz.nseg);
 }
 
 // the stage-combination epilogue by separate launches (boxes without viscous terms)

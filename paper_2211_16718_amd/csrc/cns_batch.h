@@ -98,14 +98,6 @@ __device__ __forceinline__ gptr<T> elem(gptr<T> a, size_t n3, int c, uint32_t bo
     return (gptr<T>)((gptr<Byte>)(a + (size_t)c * n3) + boff);
 }
 
-// Holds a value at this point of the program: pure arithmetic whose result is only used in
-// a later block would otherwise be sunk into that block, past the scheduling fences that
-// bound what is live.
-template <typename T>
-__device__ __forceinline__ void pin(T &v) {
-    asm volatile("" : "+v"(v));
-}
-
 __device__ __forceinline__ const void *state_ptr(const BoxDesc &b, const Launch &L, int which) {
     if (which == BUF_U) return L.u_ov ? L.u_ov : b.u;
     if (which == BUF_A) return L.a_ov ? L.a_ov : b.A;

@@ -74,6 +74,14 @@ __device__ __forceinline__ T harten_abs(T lam, T delta, T h) {
     return (a >= delta) ? a : (lam * lam + delta * delta) * h;
 }
 
+// Holds a value at this point of the program: pure arithmetic whose result is only used in
+// a later block would otherwise be sunk into that block, past the scheduling fences that
+// bound what is live.
+template <typename T>
+__device__ __forceinline__ void pin(T &v) {
+    asm volatile("" : "+v"(v));
+}
+
 __device__ __forceinline__ double fmadd(double a, double b, double c) { return fma(a, b, c); }
 __device__ __forceinline__ float fmadd(float a, float b, float c) { return fmaf(a, b, c); }
 

@@ -203,6 +203,77 @@ __device__ __forceinline__ void weno5_lr_vjp(const double q[6], double eps, doub
     Rv = R;
 }
 
+// ---------------------------------------------------------------------------
+// The reconstructions of one cell transposed (weno5_cell6 with the weights WW): given the
+// adjoints Lb6, Rb6 of L6 and R6, six times the left-biased value at the cell's right face and
+// the right-biased value at its left face, SET qb[0..4] to dL6/dq^T Lb6 + dR6/dq^T Rb6 (q = j-2
+// .. j+2); the values themselves are returned in L6, R6.
+//
+// As in the forward, the two values share the indicator sums S_k = 4 (eps + beta_k), and
+// both are q_j plus a combination of differences.  With the candidates l_k (L) and -r_k (R)
+// less 6 q_j, A_k = t_k^2, t_k the product of the other two S, and P = S1 S2 S3, the
+// Jiang-Shu weights are (A1, 6 A2, 3 A3) / D_L and (3 A1, 6 A2, A3) / D_R, and an indicator
+// sum receives from both sides at once: d(value)/dS_k = -2 w_k (candidate_k - value) / S_k
+// with 1 / S_k = t_k / P.  About 120 FP64 operations for the two values of a cell (166 for
+// the two values at an interface, whose sides have indicators of their own).
+// ---------------------------------------------------------------------------
+template <int WW>
+__device__ __forceinline__ void weno5_cell_vjp(const double q[5], double eps4, double Lb6, double Rb6, double qb[5],
+                                               double &L6, double &R6) {
+    const double c0 = q[2];
+    const double g0 = q[1] - q[0], g1 = c0 - q[1], g2 = q[3] - c0, g3 = q[4] - q[3];
+    const double D1 = g1 - g0, D2 = g2 - g1, D3 = g3 - g2;
+    const double e1 = 3.0 * g1 - g0, e2 = g1 + g2, e3 = 3.0 * g2 - g3;
+    const double k = 13.0 / 3.0;
+    const double k1 = k * D1, k2 = k * D2, k3 = k * D3;
+    const double S1 = (k1 * D1 + eps4) + e1 * e1, S2 = (k2 * D2 + eps4) + e2 * e2, S3 = (k3 * D3 + eps4) + e3 * e3;
+    const double l1 = 2.0 * e1 - g1, l2 = 2.0 * g2 + g1, l3 = e3 + g2;
+    const double r1 = e1 + g1, r2 = 2.0 * g1 + g2, r3 = 2.0 * e3 - g2;
+    double xL, xR;        // six times the values less 6 q_j (R: with the opposite sign)
+    double lb[3], rb[3];  // adjoints of l_k, r_k
+    double s1, s2, s3;    // twice the adjoints of S_k
+    if constexpr (WW == CNS_WENO_JS) {
+        const double t1 = S2 * S3, t2 = S1 * S3, t3 = S1 * S2;
+        const double A1 = t1 * t1, A2 = t2 * t2, A3 = t3 * t3;
+        const double B1 = 3.0 * A1, B2 = 6.0 * A2, B3 = 3.0 * A3;
+        const double s = (A1 + A3) + B2;
+        const double dL = 2.0 * A3 + s, dR = 2.0 * A1 + s;
+        const double rr = rcp(dL * dR), iL = dR * rr, iR = dL * rr;
+        const double iP4 = -4.0 * rcp(t1 * S1);
+        xL = (A1 * l1 + (B2 * l2 + B3 * l3)) * iL;
+        xR = (A3 * r3 + (B2 * r2 + B1 * r1)) * iR;
+        const double hL = Lb6 * iL, hR = -Rb6 * iR;
+        lb[0] = hL * A1, lb[1] = hL * B2, lb[2] = hL * B3;
+        rb[0] = hR * B1, rb[1] = hR * B2, rb[2] = hR * A3;
+        s1 = (iP4 * t1) * (lb[0] * (l1 - xL) + rb[0] * (r1 - xR));
+        s2 = (iP4 * t2) * (lb[1] * (l2 - xL) + rb[1] * (r2 - xR));
+        s3 = (iP4 * t3) * (lb[2] * (l3 - xL) + rb[2] * (r3 - xR));
+    } else {
+        double w[3], v[3], dl[3], dr[3];
+        weno_side_vjp<WW>(S1, S2, S3, l1, l2, l3, xL, w, dl);
+        weno_side_vjp<WW>(S3, S2, S1, r3, r2, r1, xR, v, dr);  // mirrored stencils
+        lb[0] = Lb6 * w[0], lb[1] = Lb6 * w[1], lb[2] = Lb6 * w[2];
+        rb[0] = -Rb6 * v[2], rb[1] = -Rb6 * v[1], rb[2] = -Rb6 * v[0];
+        s1 = 2.0 * (Lb6 * dl[0] - Rb6 * dr[2]);
+        s2 = 2.0 * (Lb6 * dl[1] - Rb6 * dr[1]);
+        s3 = 2.0 * (Lb6 * dl[2] - Rb6 * dr[0]);
+    }
+    L6 = 6.0 * c0 + xL;
+    R6 = 6.0 * c0 - xR;
+    // S = 4 eps + (13/3) D^2 + e^2; candidates; differences
+    const double d1 = k1 * s1, d2 = k2 * s2, d3 = k3 * s3;
+    const double f1 = e1 * s1 + (2.0 * lb[0] + rb[0]), f2 = e2 * s2, f3 = e3 * s3 + (2.0 * rb[2] + lb[2]);
+    const double h0 = -f1 - d1;
+    const double h1 = (3.0 * f1 + f2) + (d1 - d2) + ((lb[1] - lb[0]) + (2.0 * rb[1] + rb[0]));
+    const double h2 = (3.0 * f3 + f2) + (d2 - d3) + ((rb[1] - rb[2]) + (2.0 * lb[1] + lb[2]));
+    const double h3 = d3 - f3;
+    qb[0] = -h0;
+    qb[1] = h0 - h1;
+    qb[2] = 6.0 * (Lb6 + Rb6) + (h1 - h2);
+    qb[3] = h2 - h3;
+    qb[4] = h3;
+}
+
 // component v of the convective flux along DIR
 template <int DIR>
 __device__ __forceinline__ double euler_flux_comp(const double w[5], double gm1, int v) {
@@ -237,38 +308,34 @@ __device__ __forceinline__ void euler_flux_vjp(const double w[5], double gm1, co
 }
 
 // ---------------------------------------------------------------------------
-// Roe dissipation (roe_dissipation, wave-strength form) D = M(a, b) du: linear in the
-// jump du, with M from the Roe average of the cell states a, b alone (Harten's fix
-// acts on the eigenvalues).  Given Db, the two parts of its transpose product:
-//   STATES = false: dub += M^T Db (needs no du);
-//   STATES = true:  ab, bb += the adjoints of a and b through M (needs du).
+// Roe dissipation (wave-strength form) D = M(a, b) du: linear in the jump du, with M from
+// the Roe average of the cell states a, b alone (Harten's fix acts on the eigenvalues).
+// Given Db, the transpose product in three parts, so that little is held at a time:
+//   roe_jump_vjp:  dub += M^T Db (needs no du);
+//   roe_mean_vjp:  the adjoints of the Roe-averaged velocity and enthalpy (needs du);
+//   roe_cells_vjp: from these ab, bb += the adjoints of the states; what it needs of the
+//     cells is formed from the states and pressures again.
 // ---------------------------------------------------------------------------
-// The Roe average of the cell states a, b and the fixed eigenvalues: formed once per
-// interface for both parts of the transpose product.
-struct RoeAvg {
-    double ra, rb, ia, ib, va[3], vb[3], pa, pb, Ha, Hb, sa, sb, iw, wa, wb, v[3], H, q2, c, ic, ic2, l1, l2, l5;
+// The Roe average of the states a, b (pressures pa, pb) and the fixed eigenvalues; ra, rb =
+// 1/sqrt(rho), wa, wb the weights and iw = 1 / (sqrt(rho_a) + sqrt(rho_b)).
+struct RoeFace {
+    double ra, rb, iw, wa, wb, v[3], H, q2, c, ic, ic2, l1, l2, l5;
 };
+__device__ __forceinline__ double pressure(const double w[5], double gm1) {
+    return gm1 * (w[4] - 0.5 * rcp(w[0]) * (w[1] * w[1] + w[2] * w[2] + w[3] * w[3]));
+}
 template <int DIR>
-__device__ __forceinline__ RoeAvg roe_avg(const double a[5], const double b[5], double gamma, double delta) {
-    const double gm1 = gamma - 1.0;
-    RoeAvg R;
+__device__ __forceinline__ RoeFace roe_face(const double a[5], double pa, const double b[5], double pb, double gm1,
+                                            double delta) {
+    RoeFace R;
     R.ra = rsq(a[0]), R.rb = rsq(b[0]);
-    R.ia = R.ra * R.ra, R.ib = R.rb * R.rb;
+    R.iw = rcp(a[0] * R.ra + b[0] * R.rb);
+    // wa va = (a_k / sqrt(rho_a)) iw
+    const double xa = R.ra * R.iw, xb = R.rb * R.iw;
+    R.wa = a[0] * xa, R.wb = b[0] * xb;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        R.va[k] = a[1 + k] * R.ia;
-        R.vb[k] = b[1 + k] * R.ib;
-    }
-    const double qa = a[1] * R.va[0] + a[2] * R.va[1] + a[3] * R.va[2];
-    const double qb = b[1] * R.vb[0] + b[2] * R.vb[1] + b[3] * R.vb[2];
-    R.pa = gm1 * (a[4] - 0.5 * qa), R.pb = gm1 * (b[4] - 0.5 * qb);
-    R.Ha = (a[4] + R.pa) * R.ia, R.Hb = (b[4] + R.pb) * R.ib;
-    R.sa = a[0] * R.ra, R.sb = b[0] * R.rb;
-    R.iw = rcp(R.sa + R.sb);
-    R.wa = R.sa * R.iw, R.wb = R.sb * R.iw;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) R.v[k] = R.wa * R.va[k] + R.wb * R.vb[k];
-    R.H = R.wa * R.Ha + R.wb * R.Hb;
+    for (int k = 0; k < 3; ++k) R.v[k] = xa * a[1 + k] + xb * b[1 + k];
+    R.H = xa * (a[4] + pa) + xb * (b[4] + pb);
     R.q2 = R.v[0] * R.v[0] + R.v[1] * R.v[1] + R.v[2] * R.v[2];
     const double c2 = gm1 * (R.H - 0.5 * R.q2);
     R.ic = rsq(c2);
@@ -278,163 +345,106 @@ __device__ __forceinline__ RoeAvg roe_avg(const double a[5], const double b[5], 
     return R;
 }
 
-template <int DIR, bool STATES>
-__device__ __forceinline__ void roe_dissipation_vjp(const RoeAvg &R, const double a[5], const double b[5],
-                                                    const double du[5], double gamma, double delta,
-                                                    const double Db[5], double ab[5], double bb[5], double dub[5]) {
+// The reverse of the wave strengths common to both products: the adjoints of alpha and
+// lambda alpha, down to X's.
+struct RoeStrengths {
+    double a1b, a2b, a5b, at1b, at2b, numb, Xb;
+    double s1b, s2b, s5b, st1b, st2b;
+};
+template <int DIR>
+__device__ __forceinline__ RoeStrengths roe_strengths_vjp(const RoeFace &R, double gm1, const double Db[5]) {
     constexpr int N = DIR, T1 = (DIR + 1) % 3, T2 = (DIR + 2) % 3;
-    const double gm1 = gamma - 1.0;
-    const double ra = R.ra, rb = R.rb, ia = R.ia, ib = R.ib, pa = R.pa, pb = R.pb, Ha = R.Ha, Hb = R.Hb;
-    const double sa = R.sa, sb = R.sb, iw = R.iw, wa = R.wa, wb = R.wb, H = R.H, q2 = R.q2;
-    const double c = R.c, ic = R.ic, ic2 = R.ic2, l1 = R.l1, l2 = R.l2, l5 = R.l5;
-    const double *va = R.va, *vb = R.vb, *v = R.v;
-    const double vn = v[N];
-    const double idelta = 1.0 / delta;
-    // ---- forward recompute: the wave strengths of du (only the state adjoints need them)
-    double at1 = 0, at2 = 0, a1 = 0, a2 = 0, a5 = 0, s1 = 0, s2 = 0, s5 = 0, st1 = 0, st2 = 0, ssum = 0;
-    if constexpr (STATES) {
-        at1 = du[1 + T1] - v[T1] * du[0];
-        at2 = du[1 + T2] - v[T2] * du[0];
-        const double dEb = du[4] - at1 * v[T1] - at2 * v[T2];
-        const double X = du[0] * (H - vn * vn) + vn * du[1 + N] - dEb;
-        a2 = gm1 * ic2 * X;
-        const double num = du[0] * (vn + c) - du[1 + N] - c * a2;
-        a1 = num * (0.5 * ic);
-        a5 = du[0] - (a1 + a2);
-        s1 = l1 * a1, s2 = l2 * a2, s5 = l5 * a5, st1 = l2 * at1, st2 = l2 * at2;
-        ssum = s1 + s2 + s5;
-    }
-
-    // ---- reverse
-    double s1b = 0, s2b = 0, s5b = 0, st1b = 0, st2b = 0, ssumb = 0, Hbar = 0, vnb = 0, cb = 0, q2b = 0;
-    double vbar[3] = {0, 0, 0};
-    // D4 = s1 (H - vn c) + s2 q2/2 + s5 (H + vn c) + st1 v_t1 + st2 v_t2
-    s1b += Db[4] * (H - vn * c);
-    s5b += Db[4] * (H + vn * c);
-    s2b += Db[4] * 0.5 * q2;
-    st1b += Db[4] * v[T1];
-    st2b += Db[4] * v[T2];
-    if constexpr (STATES) {
-        Hbar += Db[4] * (s1 + s5);
-        vnb += Db[4] * (s5 - s1) * c;
-        cb += Db[4] * (s5 - s1) * vn;
-        q2b += Db[4] * 0.5 * s2;
-        vbar[T1] += Db[4] * st1;
-        vbar[T2] += Db[4] * st2;
-    }
-    // D[1+T1] += st1, D[1+T2] += st2, D[1+N] += c (s5 - s1)
-    st1b += Db[1 + T1];
-    st2b += Db[1 + T2];
-    s5b += Db[1 + N] * c;
-    s1b -= Db[1 + N] * c;
-    if constexpr (STATES) cb += Db[1 + N] * (s5 - s1);
-    // D0 = ssum, D[1+k] = ssum v_k (before the additions above)
-    ssumb += Db[0];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        ssumb += Db[1 + k] * v[k];
-        if constexpr (STATES) vbar[k] += Db[1 + k] * ssum;
-    }
-    s1b += ssumb;
-    s2b += ssumb;
-    s5b += ssumb;
-    // s = |lam| alpha
-    double a1b = s1b * l1, a2b = s2b * l2, a5b = s5b * l5, at1b = st1b * l2, at2b = st2b * l2;
-    if constexpr (STATES) {
-        const double l1b = s1b * a1, l2b = s2b * a2 + st1b * at1 + st2b * at2, l5b = s5b * a5;
-        const double x1 = l1b * harten_dabs(vn - c, delta, idelta);
-        const double x5 = l5b * harten_dabs(vn + c, delta, idelta);
-        vnb += x1 + l2b * harten_dabs(vn, delta, idelta) + x5;
-        cb += x5 - x1;
-    }
-    // a5 = du0 - (a1 + a2)
-    if constexpr (!STATES) dub[0] += a5b;
-    a1b -= a5b;
-    a2b -= a5b;
-    // a1 = num / (2c)
-    const double numb = a1b * (0.5 * ic);
-    if constexpr (STATES) {
-        cb -= a1b * a1 * ic;
-        vnb += numb * du[0];
-        cb += numb * du[0];
-        cb -= numb * a2;
-    } else {
-        dub[0] += numb * (vn + c);
-        dub[1 + N] -= numb;
-    }
-    a2b -= numb * c;
-    // a2 = gm1/c2 X
-    const double Xb = a2b * gm1 * ic2;
-    // X = du0 (H - vn^2) + vn du_n - dEb;  dEb = du4 - at1 v_t1 - at2 v_t2;  at = du_t - v_t du0
-    const double dEbb = -Xb;
-    at1b -= dEbb * v[T1];
-    at2b -= dEbb * v[T2];
-    if constexpr (!STATES) {
-        dub[0] += Xb * (H - vn * vn);
-        dub[1 + N] += Xb * vn;
-        dub[4] += dEbb;
-        dub[1 + T1] += at1b;
-        dub[0] -= at1b * v[T1];
-        dub[1 + T2] += at2b;
-        dub[0] -= at2b * v[T2];
-        return;
-    }
-    double c2b = -a2b * a2 * ic2;
-    Hbar += Xb * du[0];
-    vnb += Xb * (du[1 + N] - 2.0 * vn * du[0]);
-    vbar[T1] -= dEbb * at1;
-    vbar[T2] -= dEbb * at2;
-    vbar[T1] -= at1b * du[0];
-    vbar[T2] -= at2b * du[0];
+    const double vnc = R.v[N] * R.c;
+    RoeStrengths r;
+    // D0 = ssum, D[1+k] = ssum v_k + ..., D4 = s1 (H - vn c) + s2 q2/2 + s5 (H + vn c) + st1 v_t1
+    // + st2 v_t2; D[1+T] += st, D[1+N] += c (s5 - s1)
+    const double ssumb = Db[0] + Db[1] * R.v[0] + Db[2] * R.v[1] + Db[3] * R.v[2];
+    r.s1b = Db[4] * (R.H - vnc) - Db[1 + N] * R.c + ssumb;
+    r.s5b = Db[4] * (R.H + vnc) + Db[1 + N] * R.c + ssumb;
+    r.s2b = Db[4] * 0.5 * R.q2 + ssumb;
+    r.st1b = Db[4] * R.v[T1] + Db[1 + T1];
+    r.st2b = Db[4] * R.v[T2] + Db[1 + T2];
+    // s = |lam| alpha; a5 = du0 - (a1 + a2); a1 = num / (2c); num = du0 (vn + c) - du_n - c a2
+    r.a5b = r.s5b * R.l5;
+    r.a1b = r.s1b * R.l1 - r.a5b;
+    r.numb = r.a1b * (0.5 * R.ic);
+    r.a2b = r.s2b * R.l2 - r.a5b - r.numb * R.c;
+    // a2 = gm1/c2 X;  X = du0 (H - vn^2) + vn du_n - dEb;  dEb = du4 - at1 v_t1 - at2 v_t2; at = du_t - v_t du0
+    r.Xb = r.a2b * gm1 * R.ic2;
+    r.at1b = r.st1b * R.l2 + r.Xb * R.v[T1];
+    r.at2b = r.st2b * R.l2 + r.Xb * R.v[T2];
+    return r;
+}
+template <int DIR>
+__device__ __forceinline__ void roe_jump_vjp(const RoeFace &R, double gm1, const double Db[5], double dub[5]) {
+    constexpr int N = DIR, T1 = (DIR + 1) % 3, T2 = (DIR + 2) % 3;
+    const double vn = R.v[N];
+    const RoeStrengths r = roe_strengths_vjp<DIR>(R, gm1, Db);
+    dub[0] += r.a5b + r.numb * (vn + R.c) + r.Xb * (R.H - vn * vn) - r.at1b * R.v[T1] - r.at2b * R.v[T2];
+    dub[1 + N] += r.Xb * vn - r.numb;
+    dub[1 + T1] += r.at1b;
+    dub[1 + T2] += r.at2b;
+    dub[4] -= r.Xb;
+}
+template <int DIR>
+__device__ __forceinline__ void roe_mean_vjp(const RoeFace &R, double gm1, double delta, const double du[5],
+                                             const double Db[5], double vbar[3], double &Hbar) {
+    constexpr int N = DIR, T1 = (DIR + 1) % 3, T2 = (DIR + 2) % 3;
+    const double vn = R.v[N], c = R.c, idelta = 1.0 / delta;
+    const RoeStrengths r = roe_strengths_vjp<DIR>(R, gm1, Db);
+    // the wave strengths of du
+    const double at1 = du[1 + T1] - R.v[T1] * du[0], at2 = du[1 + T2] - R.v[T2] * du[0];
+    const double dEb = du[4] - at1 * R.v[T1] - at2 * R.v[T2];
+    const double a2 = gm1 * R.ic2 * (du[0] * (R.H - vn * vn) + vn * du[1 + N] - dEb);
+    const double a1 = (du[0] * (vn + c) - du[1 + N] - c * a2) * (0.5 * R.ic), a5 = du[0] - (a1 + a2);
+    const double s1 = R.l1 * a1, s2 = R.l2 * a2, s5 = R.l5 * a5, ssum = s1 + s2 + s5, sd = s5 - s1;
+    Hbar = Db[4] * (s1 + s5) + r.Xb * du[0];
+    double vnb = Db[4] * sd * c, cb = Db[4] * sd * vn + Db[1 + N] * sd, q2b = Db[4] * 0.5 * s2;
+    vbar[N] = Db[1 + N] * ssum;
+    vbar[T1] = Db[4] * R.l2 * at1 + Db[1 + T1] * ssum + r.Xb * at1 - r.at1b * du[0];
+    vbar[T2] = Db[4] * R.l2 * at2 + Db[1 + T2] * ssum + r.Xb * at2 - r.at2b * du[0];
+    const double x1 = r.s1b * a1 * harten_dabs(vn - c, delta, idelta), x5 = r.s5b * a5 * harten_dabs(vn + c, delta, idelta);
+    vnb += x1 + (r.s2b * a2 + r.st1b * at1 + r.st2b * at2) * harten_dabs(vn, delta, idelta) + x5;
+    cb += x5 - x1;
+    cb -= r.a1b * a1 * R.ic;
+    vnb += r.numb * du[0];
+    cb += r.numb * (du[0] - a2);
+    vnb += r.Xb * (du[1 + N] - 2.0 * vn * du[0]);
     vbar[N] += vnb;
     // c = sqrt(c2); c2 = gm1 (H - q2/2); q2 = |v|^2
-    c2b += cb * (0.5 * ic);
+    const double c2b = cb * (0.5 * R.ic) - r.a2b * a2 * R.ic2;
     Hbar += c2b * gm1;
     q2b -= 0.5 * gm1 * c2b;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) vbar[k] += 2.0 * v[k] * q2b;
-    // H = wa Ha + wb Hb;  v = wa va + wb vb
-    double wab = Hbar * Ha, wbb = Hbar * Hb;
-    const double Hab = Hbar * wa, Hbb = Hbar * wb;
-    double vab[3], vbb[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        wab += vbar[k] * va[k];
-        wbb += vbar[k] * vb[k];
-        vab[k] = vbar[k] * wa;
-        vbb[k] = vbar[k] * wb;
-    }
-    // wa = sa iw, wb = sb iw, iw = 1/(sa + sb)
-    const double iwb = wab * sa + wbb * sb;
-    const double sab = wab * iw - iwb * iw * iw;
-    const double sbb = wbb * iw - iwb * iw * iw;
-    // Ha = (a4 + pa) ia; pa = gm1 (a4 - qa/2); qa = sum a_k va_k; va = a_k ia; ia = 1/a0
-    {
-        const double pab = Hab * ia;
-        double iab = Hab * (a[4] + pa);
-        ab[4] += Hab * ia + pab * gm1;
-        const double qab = -0.5 * gm1 * pab;
+    for (int k = 0; k < 3; ++k) vbar[k] += 2.0 * R.v[k] * q2b;
+}
+// H = wa Ha + wb Hb, v = wa va + wb vb; wa = sa iw, wb = sb iw, iw = 1/(sa + sb), s = sqrt(rho);
+// Ha = (a4 + pa) / a0, va = a_k / a0
+__device__ __forceinline__ void roe_cells_vjp(const RoeFace &R, const double a[5], double pa, const double b[5],
+                                              double pb, double gm1, const double vbar[3], double Hbar, double ab[5],
+                                              double bb[5]) {
+    const double ia = R.ra * R.ra, ib = R.rb * R.rb;
+    const double Ha = (a[4] + pa) * ia, Hb = (b[4] + pb) * ib;
+    const double wab = Hbar * Ha + (vbar[0] * a[1] + vbar[1] * a[2] + vbar[2] * a[3]) * ia;
+    const double wbb = Hbar * Hb + (vbar[0] * b[1] + vbar[1] * b[2] + vbar[2] * b[3]) * ib;
+    // sa' = wab iw - iw (wab wa + wbb wb), and d sqrt(rho)/d rho = 1/(2 sqrt(rho))
+    const double t = wab * R.wa + wbb * R.wb;
+    const double sab = (wab - t) * R.iw, sbb = (wbb - t) * R.iw;
+    auto cell = [&](const double w[5], double H, double i, double wt, double s0, double out[5]) {
+        const double Hw = Hbar * wt, p = Hw * i;  // adjoints of H of the cell, and of e + p
+        const double q = -0.5 * gm1 * p;          // of m.v
+        double is = Hw * H;                       // of 1/rho, times rho
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const double vk = vab[k] + qab * a[1 + k];
-            ab[1 + k] += qab * va[k] + vk * ia;
-            iab += vk * a[1 + k];
+            const double vk = vbar[k] * wt + q * w[1 + k], v = w[1 + k] * i;
+            out[1 + k] += q * v + vk * i;
+            is += vk * v;
         }
-        ab[0] += -iab * ia * ia + sab * (0.5 * ra);  // d sqrt(rho)/d rho = 1/(2 sqrt(rho))
-    }
-    {
-        const double pbb = Hbb * ib;
-        double ibb = Hbb * (b[4] + pb);
-        bb[4] += Hbb * ib + pbb * gm1;
-        const double qbb = -0.5 * gm1 * pbb;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const double vk = vbb[k] + qbb * b[1 + k];
-            bb[1 + k] += qbb * vb[k] + vk * ib;
-            ibb += vk * b[1 + k];
-        }
-        bb[0] += -ibb * ib * ib + sbb * (0.5 * rb);
-    }
+        out[4] += p + gm1 * p;
+        out[0] += s0 - is * i;
+    };
+    cell(a, Ha, ia, R.wa, sab * (0.5 * R.ra), ab);
+    cell(b, Hb, ib, R.wb, sbb * (0.5 * R.rb), bb);
 }
 
 // ---------------------------------------------------------------------------
@@ -480,6 +490,7 @@ __device__ __forceinline__ void interface_flux_vjp(const double *st, int cs, con
     // dissipation D = M(a, b) du at cells a = j, b = j+1: first dub = M^T Db, which needs
     // no du; the reverse of the reconstructed states then yields du itself (UR - UL);
     // last the adjoints of a and b through M
+    const double gm1 = gamma - 1.0;
     double a[5], b[5], Db[5], du[5], dub[5] = {0, 0, 0, 0, 0};
     double ab[5] = {0, 0, 0, 0, 0}, bb[5] = {0, 0, 0, 0, 0};
 #pragma unroll
@@ -487,10 +498,9 @@ __device__ __forceinline__ void interface_flux_vjp(const double *st, int cs, con
         a[v] = st[v * cs + c[2]];
         b[v] = st[v * cs + c[3]];
         Db[v] = -0.5 * Hb[v];
-        du[v] = 0.0;
     }
-    const RoeAvg R = roe_avg<DIR>(a, b, gamma, delta);
-    roe_dissipation_vjp<DIR, false>(R, a, b, du, gamma, delta, Db, ab, bb, dub);
+    const RoeFace R = roe_face<DIR>(a, pressure(a, gm1), b, pressure(b, gm1), gm1, delta);
+    roe_jump_vjp<DIR>(R, gm1, Db, dub);
     adj_stage_fence();
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
@@ -509,7 +519,9 @@ __device__ __forceinline__ void interface_flux_vjp(const double *st, int cs, con
         a[v] = st[v * cs + c[2]];
         b[v] = st[v * cs + c[3]];
     }
-    roe_dissipation_vjp<DIR, true>(R, a, b, du, gamma, delta, Db, ab, bb, dub);
+    double vbar[3], Hbar;
+    roe_mean_vjp<DIR>(R, gm1, delta, du, Db, vbar, Hbar);
+    roe_cells_vjp(R, a, pressure(a, gm1), b, pressure(b, gm1), gm1, vbar, Hbar, ab, bb);
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
         addU(2, v, ab[v]);
