@@ -4,16 +4,14 @@
 // (dR/du)^T rbar of the semi-discrete operator R(u) = -sum_d (H_{j+1/2} - H_{j-1/2})/dx_d
 // + sum_d D_d G^v_d is assembled as
 //   convective part, per direction d:  Hbar_{j+1/2} = (rbar_{j+1} - rbar_j)/dx_d;
-//     k_adj_conv<x>: one thread per interface forms the local product of the
-//     interface flux (the point-flux and state adjoints of the six cells it reads)
-//     and adds them, in a fixed order, into LDS accumulators of the cells, which are
-//     then finished and written;
-//     k_adj_march<y, z>: a thread marches along a segment of a line, one cell a step;
+//     k_adj_cells, k_adj_march: a lane per cell, or a thread marching from cell to cell,
+//     transposes the cell's reconstructions and a face's dissipation and adds the
+//     point-flux and state adjoints of the cells, which are then finished and written;
 //   viscous part: the adjoint of a central difference is minus the same central
 //     difference, so Gbar_d = -D_d rbar; k_adj_visc maps it through the viscous
 //     fluxes to the adjoints of the velocity/temperature gradients and of the
 //     point velocities, applies -D once more and the primitive map, in one pass.
-// Every sum is formed in a fixed order (deterministic: the LDS atomic adds into a cell
+// Every sum is formed in a fixed order (deterministic: the LDS additions into a cell
 // come from one wave, whose LDS operations take effect in program order).
 #include <hip/hip_runtime.h>
 
@@ -51,197 +49,6 @@ static AdjGeom adj_geom(const BoxDesc &b) {
     g.eps = b.eps;
     g.delta = b.delta;
     return g;
-}
-
-// linear index of (i,j,k) displaced by off along d
-__device__ __forceinline__ size_t shift_idx(const AdjGeom &g, int i, int j, int k, int d, int off) {
-    if (d == 0) i = wrapj(i + off, g.nx);
-    else if (d == 1) j = wrapj(j + off, g.ny);
-    else k = wrapj(k + off, g.nz);
-    return ((size_t)k * g.ny + j) * g.nx + i;
-}
-
-// ---------------------------------------------------------------------------
-// Convective adjoint along DIR, fused with the gather: ubar(=|+=) sum over the six
-// interfaces that read each cell of their contributions.
-//
-// A block of 256 threads owns TB whole periodic lines along DIR and marches along
-// them in chunks of TA interfaces; each wave owns LW of the lines and all TA
-// interfaces of a chunk on them (x: one row, 64 interfaces; y, z: 4 lines consecutive
-// in x, 16 interfaces each).  Each thread forms the product of one interface (j+1/2,
-// cells j-2 .. j+3) and adds its terms, as they are formed, to two LDS rings of cell
-// accumulators: the adjoints of the cells' point fluxes (ringF) and those of their
-// states through the dissipation (ringU).  Every cell of a wave's lines is touched by
-// that wave alone, and a wave's LDS operations take effect in program order, so no
-// barrier orders the additions; they are LDS atomic adds, and the six terms of one
-// instruction (cells j-2+m of the interfaces j of the wave) go to six different
-// cells, so the order of the additions into every cell is fixed (deterministic).  A
-// complete cell leaves as J(u)^T ringF + ringU, J the Jacobian of the point flux: the
-// transpose is applied once per cell instead of once per interface and cell.
-//
-// Cells are indexed along the line without wrapping, e = -2 .. n+2; e and e+n are
-// the same grid cell.  After the chunk with interfaces I .. I+TA-1 the cells up to
-// I+TA-3 are complete: cells 3 .. n-3 are written out, and the finished parts of
-// cells -2 .. 2 are set aside ("head") until the last chunk adds the rest of those
-// five grid cells (e = n-2 .. n+2); the transpose is linear, so the two parts are
-// transposed separately.  The rings hold RS >= TA + 5 cells, the cells one chunk
-// touches.  Before each chunk the block stages the states of the cells I-2 .. I+TA+2
-// of its lines and their point fluxes along DIR in LDS (coalesced along x in every
-// direction; each flux formed once instead of by each of the six interfaces that
-// read it), so the stages of the interface product, which re-read the states rather
-// than hold them, and the transposes at write-out read LDS instead of the caches.
-// ---------------------------------------------------------------------------
-template <int DIR> struct AdjConvShape;
-template <> struct AdjConvShape<0> { static constexpr int TA = 64, LW = 1, RS = 128, PAD = 0; };
-template <> struct AdjConvShape<1> { static constexpr int TA = 16, LW = 4, RS = 32, PAD = 4; };
-template <> struct AdjConvShape<2> { static constexpr int TA = 16, LW = 4, RS = 32, PAD = 4; };
-
-template <int DIR, int WW>
-__global__ __launch_bounds__(256, 2) void k_adj_conv(AdjGeom g, const double *__restrict__ u,
-                                                     const double *__restrict__ rbar, double *__restrict__ ubar,
-                                                     int accumulate) {
-    using S = AdjConvShape<DIR>;
-    constexpr int TA = S::TA, LW = S::LW, RS = S::RS, TB = 4 * LW;
-    constexpr int NC = TA + 5;  // staged cells per line
-    static_assert(TA * LW == 64 && RS >= TA + 5 && (RS & (RS - 1)) == 0, "chunk shape");
-    // staged component v of line l, cell k (v = 0-4 the state, 5-9 its point flux along
-    // DIR): x: (l * 10 + v) * NC + k; y, z: k * KS + v * TB + l, the cell stride padded
-    // so that the sixteen cells a wave reads in one instruction spread over all LDS
-    // banks.  Both rings, the head and the staged cells of a block fit twice in the
-    // 160 KiB of LDS of a compute unit.
-    constexpr int KS = 10 * TB + S::PAD;
-    constexpr int cs = DIR == 0 ? NC : TB;  // component stride of stg
-    __shared__ double ringF[4 * 5 * RS * LW];
-    __shared__ double ringU[4 * 5 * RS * LW];
-    __shared__ double head[TB * 25];
-    __shared__ double stg[DIR == 0 ? TB * 10 * NC : NC * KS];
-    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
-    const int ta = lane / LW;  // interface within the chunk
-    const int tl = lane % LW;  // line within the wave
-    const int tb = w * LW + tl;  // line within the block
-    // ring slot of cell e for component v: the wave's own region, consecutive lanes
-    // on consecutive doubles
-    auto slot = [&](int e, int v) -> int { return ((w * 5 + v) * RS + ((e + 2) & (RS - 1))) * LW + tl; };
-    // offset in stg of this lane's line at staged cell k
-    auto cell = [&](int k) -> int { return DIR == 0 ? tb * 10 * NC + k : k * KS + tb; };
-    const size_t n3 = g.n3;
-    const int n = DIR == 0 ? g.nx : (DIR == 1 ? g.ny : g.nz);
-    const size_t stride = DIR == 0 ? 1 : (DIR == 1 ? (size_t)g.nx : (size_t)g.nx * g.ny);
-    const int ntx = (g.nx + TB - 1) / TB;
-    const double gm1 = g.gamma - 1.0;
-    // the line of lane column t: whether it exists, and the offset of its cell 0
-    auto line = [&](int t, size_t &lb) -> bool {
-        if (DIR == 0) {
-            const size_t row = (size_t)blockIdx.x * TB + t;
-            lb = row * g.nx;
-            return row < (size_t)g.ny * g.nz;
-        }
-        const int x = (int)(blockIdx.x % ntx) * TB + t, o = (int)(blockIdx.x / ntx);
-        lb = (DIR == 1 ? (size_t)o * g.nx * g.ny : (size_t)o * g.nx) + (size_t)x;
-        return x < g.nx;
-    };
-    // the finished adjoint of cell e, staged at k: J^T ringF + ringU
-    auto finish = [&](int e, int k, double out[5]) {
-        double wc[5], fb[5];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) {
-            wc[v] = stg[v * cs + cell(k)];
-            fb[v] = ringF[slot(e, v)];
-            out[v] = ringU[slot(e, v)];
-        }
-        euler_flux_vjp<DIR>(wc, gm1, fb, out);
-    };
-    size_t base;
-    const bool lane_ok = line(tb, base);
-    const double ih = g.ih[DIR];
-    for (int t = threadIdx.x; t < 4 * 5 * RS * LW; t += 256) {
-        ringF[t] = 0.0;
-        ringU[t] = 0.0;
-    }
-    int I = 0;
-    for (;; I += TA) {
-        // the previous chunk's write-out has read stg
-        __syncthreads();
-        // stage cells I-2 .. I+TA+2 (any number of periods: short lines wrap more than
-        // once) and their point fluxes
-        for (int t = threadIdx.x; t < TB * NC; t += 256) {
-            const int k = DIR == 0 ? t % NC : t / TB, l = DIR == 0 ? t / NC : t % TB;
-            const int at = DIR == 0 ? l * 10 * NC + k : k * KS + l;
-            size_t lb;
-            if (line(l, lb)) {
-                int c = (I - 2 + k) % n;
-                if (c < 0) c += n;
-                double wc[5];
-#pragma unroll
-                for (int v = 0; v < 5; ++v) wc[v] = u[v * n3 + lb + (size_t)c * stride];
-#pragma unroll
-                for (int v = 0; v < 5; ++v) {
-                    stg[at + v * cs] = wc[v];
-                    stg[at + (5 + v) * cs] = euler_flux_comp<DIR>(wc, gm1, v);
-                }
-            }
-        }
-        __syncthreads();
-        const int j = I + ta;
-        if (lane_ok && j < n) {
-            // cell j-2+m is staged cell ta+m
-            int c[6];
-#pragma unroll
-            for (int m = 0; m < 6; ++m) c[m] = cell(ta + m);
-            const size_t p = base + (size_t)j * stride, pn = base + (size_t)wrapj(j + 1, n) * stride;
-            double Hb[5];
-#pragma unroll
-            for (int v = 0; v < 5; ++v) Hb[v] = (rbar[v * n3 + pn] - rbar[v * n3 + p]) * ih;
-            interface_flux_vjp<DIR, WW>(
-                stg, cs, c, Hb, g.gamma, g.eps, g.delta,
-                [&](int m, int v, double x) { atomicAdd(&ringF[slot(j + m - 2, v)], x); },
-                [&](int m, int v, double x) { atomicAdd(&ringU[slot(j + m - 2, v)], x); });
-        }
-        // every addition of this wave precedes the reads of the write-out
-        adj_stage_fence();
-        const bool last = I + TA >= n;
-        const int e = I - 2 + ta;  // completed by this chunk (all of them unless last)
-        if (lane_ok && e <= 2) {
-            double out[5];
-            finish(e, ta, out);
-#pragma unroll
-            for (int v = 0; v < 5; ++v) head[tb * 25 + (e + 2) * 5 + v] = out[v];
-        } else if (lane_ok && !last && e <= n - 3) {
-            double out[5];
-            finish(e, ta, out);
-            const size_t q = base + (size_t)e * stride;
-#pragma unroll
-            for (int v = 0; v < 5; ++v) {
-                if (accumulate) ubar[v * n3 + q] += out[v];
-                else ubar[v * n3 + q] = out[v];
-            }
-        }
-        if (last) break;
-        adj_stage_fence();
-#pragma unroll
-        for (int v = 0; v < 5; ++v) {
-            ringF[slot(e, v)] = 0.0;
-            ringU[slot(e, v)] = 0.0;
-        }
-        adj_stage_fence();
-    }
-    // the rest of the line: cells max(I-2, 3) .. n+2 (staged at e - (I-2)), folding
-    // e >= n-2 with the head; the wave reads only what it wrote itself
-    adj_stage_fence();
-    for (int e = I - 2 + ta; e <= n + 2; e += TA) {
-        if (!lane_ok || e < 3) continue;
-        const int r = e >= n ? e - n : e;
-        const size_t q = base + (size_t)r * stride;
-        double out[5];
-        finish(e, e - (I - 2), out);
-#pragma unroll
-        for (int v = 0; v < 5; ++v) {
-            double s = out[v];
-            if (e >= n - 2) s += head[tb * 25 + (e - n + 2) * 5 + v];
-            if (accumulate) ubar[v * n3 + q] += s;
-            else ubar[v * n3 + q] = s;
-        }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -477,6 +284,263 @@ __global__ __launch_bounds__(kAmThreads, 2) void k_adj_march(AdjGeom g, const do
 }
 
 // ---------------------------------------------------------------------------
+// Convective adjoint with a lane per cell, along x and in small boxes along y and z: ubar = (x)
+// or += the same terms.  A wave takes chunks of 16 cells of four segments of lines (x: loads of
+// whole 128-byte pieces), with the segments, their two phases and their faces as in the march.  What a thread of the march
+// keeps in registers is in LDS, private to the wave, so that no barrier orders it: the sums of
+// the chunk's cells and two on either side (LDS additions: one instruction adds to sixteen
+// different cells of a segment, so their order is fixed), dub and the left-biased values at a
+// slot per face, and the states, pressures and rbar of the chunk, whose next cells are
+// loaded a chunk ahead.
+//
+// Bound by FP64 issue (75 % of the rate) and LDS (47 % busy), two waves per SIMD.  128^3 along
+// x: 181 us against 215 with a lane per interface; 130 x 90 x 66: 92 against 117.
+// ---------------------------------------------------------------------------
+constexpr int kAcTA = 16, kAcLW = 4;            // cells of a chunk, segments of a wave
+constexpr int kAcNC = kAcTA + 5;                // staged cells I-2 .. I+TA+2
+constexpr int kAcKA = kAcTA + 4;                // summed cells I-2 .. I+TA+1
+constexpr int kAcSeg = 4 * kAcLW;               // segments of a block
+constexpr int kAcWave = (12 * kAcNC + 9 * kAcKA + 10 * (kAcTA + 1)) * kAcLW;
+
+template <int DIR, int WW>
+__global__ __launch_bounds__(256, 2) void k_adj_cells(AdjGeom g, const double *u_, const double *rbar_, double *ubar_,
+                                                      int nseg) {
+    constexpr int TA = kAcTA, LW = kAcLW, NC = kAcNC, KA = kAcKA;
+    __shared__ double lds[4 * kAcWave];
+    const auto u = (gptr<const double>)u_, rbar = (gptr<const double>)rbar_;
+    const auto ubar = (gptr<double>)ubar_;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, ta = lane / LW, tl = lane % LW;
+    const int lb = kAcSeg / nseg, vs = wv * LW + tl, seg = vs / lb;
+    const size_t n3 = g.n3, line = (size_t)blockIdx.x * lb + vs % lb;
+    const size_t nlines = DIR == 0 ? (size_t)g.ny * g.nz : (DIR == 1 ? (size_t)g.nx * g.nz : (size_t)g.nx * g.ny);
+    const int n = DIR == 0 ? g.nx : (DIR == 1 ? g.ny : g.nz);
+    const bool ok = line < nlines;
+    // byte offsets within a component
+    const uint32_t stride = (uint32_t)(8 * (DIR == 0 ? (size_t)1 : (DIR == 1 ? (size_t)g.nx : (size_t)g.nx * g.ny)));
+    const uint32_t base = (uint32_t)(8 * (DIR == 0 ? line * n
+                                                   : (DIR == 1 ? line / g.nx * ((size_t)g.nx * g.ny) + line % g.nx : line)));
+    const int s0 = (int)((long long)seg * n / nseg), s1 = ok ? (int)((long long)(seg + 1) * n / nseg) : s0;
+    const double ih12 = g.ih[DIR] * (1.0 / 12.0), gm1 = g.gamma - 1.0, eps4 = 4.0 * g.eps;
+    double *const sw = lds + wv * kAcWave + tl;
+    // staged scalar v of staged cell c (0-4 the state, 5 normal velocity, 6 pressure, 7-11 rbar),
+    // sum v of summed cell c (0-4 state, 5-8 fluxes 1-4), dub and left-biased value v of face slot c
+    auto S = [&](int v, int c) -> double & { return sw[(v * NC + c) * LW]; };
+    auto A = [&](int v, int c) -> double & { return sw[(12 * NC + v * KA + c) * LW]; };
+    auto D = [&](int v, int c) -> double & { return sw[(12 * NC + 9 * KA + v * (TA + 1) + c) * LW]; };
+    auto UL = [&](int v, int c) -> double & { return sw[(12 * NC + 9 * KA + (5 + v) * (TA + 1) + c) * LW]; };
+    auto cell = [&](int j) { return base + (uint32_t)wrapn(j, n) * stride; };
+    auto load5 = [&](gptr<const double> p, uint32_t c, double w[5]) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) w[v] = *elem(p, n3, v, c);
+    };
+    auto keep = [&](int c, const double w[5], const double r[5]) {
+        const double inv = rcp(w[0]), vx = w[1] * inv, vy = w[2] * inv, vz = w[3] * inv;
+#pragma unroll
+        for (int v = 0; v < 5; ++v) S(v, c) = w[v], S(7 + v, c) = r[v];
+        S(5, c) = DIR == 0 ? vx : (DIR == 1 ? vy : vz);
+        S(6, c) = gm1 * (w[4] - 0.5 * (w[1] * vx + w[2] * vy + w[3] * vz));
+    };
+    auto states = [&](int c, double a[5], double b[5]) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) a[v] = S(v, c), b[v] = S(v, c + 1);
+    };
+    auto jump_adjoint = [&](int c, const double H[5], double dub[5]) {  // as in the march; the face of cells c, c + 1
+        double a[5], b[5], Db[5];
+        states(c, a, b);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Db[v] = -H[v], dub[v] = 0.0;
+        const RoeFace R = roe_face<DIR>(a, S(6, c), b, S(6, c + 1), gm1, g.delta);
+        roe_jump_vjp<DIR>(R, gm1, Db, dub);
+    };
+    auto state_adjoint = [&](int c, const double Db[5], const double du6[5], double ab[5], double bb[5]) {
+        double a[5], b[5], vbar[3], Hbar;
+        states(c, a, b);
+        const RoeFace R = roe_face<DIR>(a, S(6, c), b, S(6, c + 1), gm1, g.delta);
+        roe_mean_vjp<DIR>(R, gm1, g.delta, du6, Db, vbar, Hbar);
+        pin(vbar[0]), pin(vbar[1]), pin(vbar[2]), pin(Hbar);
+        adj_stage_fence();
+        states(c, a, b);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) ab[v] = bb[v] = 0.0;
+        roe_cells_vjp(R, a, S(6, c), b, S(6, c + 1), gm1, vbar, Hbar, ab, bb);
+    };
+    // J^T f + us of cell c
+    auto finish = [&](int c, double out[5]) {
+        double w[5], fb[5];
+        fb[0] = 0.0;
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+            w[v] = S(v, c), out[v] = A(v, c);
+            if (v > 0) fb[v] = A(4 + v, c);
+        }
+        euler_flux_vjp<DIR>(w, gm1, fb, out);
+    };
+    int I = s0;
+    if (ok) {
+        double w[5], r[5];
+        load5(u, cell(s0 - 2 + ta), w);
+        load5(rbar, cell(s0 - 2 + ta), r);
+        keep(ta, w, r);
+        if (ta < NC - TA) {
+            load5(u, cell(s0 - 2 + TA + ta), w);
+            load5(rbar, cell(s0 - 2 + TA + ta), r);
+            keep(TA + ta, w, r);
+        }
+#pragma unroll
+        for (int v = 0; v < 9; ++v) {
+            A(v, ta) = 0.0;
+            if (ta < KA - TA) A(v, TA + ta) = 0.0;
+        }
+    }
+    adj_stage_fence();
+    if (ok && ta == 0) {  // dub of the left face of cell s0
+        double H[5], dub[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) H[v] = (S(7 + v, 2) - S(7 + v, 1)) * ih12;
+        jump_adjoint(1, H, dub);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) D(v, 0) = dub[v], UL(v, 0) = 0.0;
+    }
+    // the segments of a wave may differ by one cell, and so by one chunk
+    for (bool live = ok; __any(live);) {
+        adj_stage_fence();
+        const bool act = live && I + ta < s1, more = live && I + TA < s1;
+        double un[5], rn[5];
+        if (more) {
+            load5(u, cell(I + TA + 3 + ta), un);
+            load5(rbar, cell(I + TA + 3 + ta), rn);
+        }
+        if (act) {
+            // cell j = I + ta is staged cell ta + 2; its stencil starts at ta
+            double Hl[5], Hr[5], x[5], xn[5], xb[5], L6, R6, dub[5], du[5];
+#pragma unroll
+            for (int v = 0; v < 5; ++v) {
+                const double r0 = S(7 + v, ta + 2);
+                Hl[v] = (r0 - S(7 + v, ta + 1)) * ih12;
+                Hr[v] = (S(7 + v, ta + 3) - r0) * ih12;
+                pin(Hl[v]), pin(Hr[v]);
+            }
+            {
+                double vn[5], p[5];
+#pragma unroll
+                for (int m = 0; m < 5; ++m) vn[m] = S(5, ta + m), p[m] = S(6, ta + m), xn[m] = S(1, ta + m);
+#pragma unroll
+                for (int v = 1; v < 5; ++v) {
+#pragma unroll
+                    for (int m = 0; m < 5; ++m) {
+                        x[m] = xn[m] * vn[m];
+                        if (v == 1 + DIR) x[m] += p[m];
+                        if (v == 4) x[m] += p[m] * vn[m];
+                        if (v < 4) xn[m] = S(v + 1, ta + m);
+                    }
+                    adj_stage_fence();
+                    weno5_cell_vjp<WW>(x, eps4, Hr[v], Hl[v], xb, L6, R6);
+#pragma unroll
+                    for (int m = 0; m < 5; ++m) atomicAdd(&A(4 + v, ta + m), xb[m]);
+                    adj_stage_fence();
+                }
+            }
+            jump_adjoint(ta + 2, Hr, dub);
+#pragma unroll
+            for (int v = 0; v < 5; ++v) D(v, ta + 1) = dub[v], pin(dub[v]);
+            adj_stage_fence();
+            double dl = D(0, ta);
+#pragma unroll
+            for (int m = 0; m < 5; ++m) xn[m] = S(0, ta + m);
+#pragma unroll
+            for (int v = 0; v < 5; ++v) {
+#pragma unroll
+                for (int m = 0; m < 5; ++m) x[m] = xn[m];
+                double Lb = -dub[v], Rb = dl;
+                if (v == 1 + DIR) Lb += Hr[0], Rb += Hl[0];
+                if (v < 4) {
+#pragma unroll
+                    for (int m = 0; m < 5; ++m) xn[m] = S(v + 1, ta + m);
+                    dl = D(v + 1, ta);
+                }
+                adj_stage_fence();
+                weno5_cell_vjp<WW>(x, eps4, Lb, Rb, xb, L6, R6);
+                UL(v, ta + 1) = L6;
+                du[v] = R6;
+                pin(du[v]);
+#pragma unroll
+                for (int m = 0; m < 5; ++m) atomicAdd(&A(v, ta + m), xb[m]);
+                adj_stage_fence();
+            }
+            // the left face; the first one of a segment is the neighbour's
+            const double h = I + ta > s0 ? -1.0 : 0.0;
+            double Db[5], ab[5], bb[5];
+#pragma unroll
+            for (int v = 0; v < 5; ++v) du[v] -= UL(v, ta), Db[v] = h * Hl[v];
+            state_adjoint(ta + 1, Db, du, ab, bb);
+#pragma unroll
+            for (int v = 0; v < 5; ++v) {
+                atomicAdd(&A(v, ta + 1), ab[v]);
+                atomicAdd(&A(v, ta + 2), bb[v]);
+            }
+        }
+        adj_stage_fence();
+        if (live && I - 2 + ta <= s1 - 3) {
+            const uint32_t q = cell(I - 2 + ta);
+            double out[5], old[5];
+            if (DIR != 0) load5(ubar, q, old);
+            finish(ta, out);
+#pragma unroll
+            for (int v = 0; v < 5; ++v) *elem(ubar, n3, v, q) = DIR != 0 ? old[v] + out[v] : out[v];
+        }
+        adj_stage_fence();
+        if (more) {
+            // the last four sums, the last five staged cells and the last face go first
+#pragma unroll
+            for (int v = 0; v < 9; ++v) {
+                const double a = ta < KA - TA ? A(v, TA + ta) : 0.0;
+                A(v, ta) = a;
+                if (ta < KA - TA) A(v, TA + ta) = 0.0;
+            }
+            if (ta < NC - TA) {
+#pragma unroll
+                for (int v = 0; v < 12; ++v) S(v, ta) = S(v, TA + ta);
+            }
+            if (ta == 0) {
+#pragma unroll
+                for (int v = 0; v < 5; ++v) D(v, 0) = D(v, TA), UL(v, 0) = UL(v, TA);
+            }
+            adj_stage_fence();
+            keep(NC - TA + ta, un, rn);
+            I += TA;
+        }
+        live = more;
+    }
+    adj_stage_fence();
+    const int c1 = s1 - I;  // staged and summed cell of cell s1-2
+    if (ok && ta == 0) {
+        double du[5], Db[5], ab[5], bb[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+            double L6, R6;
+            weno5_cell6<WW>(S(v, c1), S(v, c1 + 1), S(v, c1 + 2), S(v, c1 + 3), S(v, c1 + 4), eps4, L6, R6);
+            du[v] = R6 - UL(v, c1);
+            Db[v] = (S(7 + v, c1 + 1) - S(7 + v, c1 + 2)) * ih12;
+        }
+        state_adjoint(c1 + 1, Db, du, ab, bb);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+            A(v, c1 + 1) += ab[v];
+            A(v, c1 + 2) += bb[v];
+        }
+    }
+    __syncthreads();
+    if (ok && ta < 4) {
+        const uint32_t q = cell(s1 - 2 + ta);
+        double old[5], out[5];
+        load5(ubar, q, old);
+        finish(c1 + ta, out);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) *elem(ubar, n3, v, q) = old[v] + out[v];
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Viscous adjoint in one pass.  With Gbar_d = -D_d rbar (rows 1-4: momentum x, y, z and
 // energy) the viscous fluxes give at every point
 //   the stencil fields f_d, the adjoints that the transposed gradients D_d carry back:
@@ -497,10 +561,6 @@ constexpr int kAvRX = kAvTX + 8, kAvRY = kAvTY + 8;    // rbar box, origin (x0-4
 constexpr int kAvHalo = 4 * kAvTY + 4 * kAvTX;         // x-halo then y-halo points of the tile
 constexpr int kAvExt = 16 + 4 * kAvTY + 4 * kAvTX;     // further rbar points: corners, x and y extensions
 static_assert(kAvHalo <= kPointThreads && kAvExt <= kPointThreads && kAvTX * kAvTY == kPointThreads, "tile");
-
-// planes per block: the two planes of lookahead on either side are formed again by the
-// next block along z, so long columns take more planes
-__host__ __device__ __forceinline__ int adj_visc_planes(int nz) { return nz >= 256 ? 32 : 16; }
 
 // position in the rbar box of halo point h (x-halo: columns x0-2, x0-1, x0+TX, x0+TX+1
 // of the tile's rows; y-halo: rows y0-2, y0-1, y0+TY, y0+TY+1 of the tile's columns)
@@ -563,7 +623,8 @@ __device__ __forceinline__ AvFields av_fields(const double Gbar[3][4], const dou
 
 __global__ __launch_bounds__(kPointThreads, 2) void k_adj_visc(AdjGeom g, const double *__restrict__ u,
                                                                const double *__restrict__ rbar,
-                                                               double *__restrict__ ubar, AdjEpilogue ep) {
+                                                               double *__restrict__ ubar, AdjEpilogue ep,
+                                                               int zp) {
     constexpr int TX = kAvTX, TY = kAvTY, RX = kAvRX, RY = kAvRY;
     __shared__ double sR[4][RY][RX];             // rbar rows 1-4 of the plane
     __shared__ double sV[3][TY + 4][TX + 4];     // velocity of the plane, tile and +-2 halo
@@ -572,7 +633,7 @@ __global__ __launch_bounds__(kPointThreads, 2) void k_adj_visc(AdjGeom g, const 
     __shared__ double hR[5][4][kAvHalo];         // rbar of the halo points, slot (plane - z0 + 4) mod 5
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     const size_t n3 = g.n3, sz = (size_t)nx * ny;
-    const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY, zp = adj_visc_planes(nz);
+    const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY;
     const long long lb = blockIdx.x;
     const int x0 = (int)(lb % ntx) * TX, y0 = (int)((lb / ntx) % nty) * TY;
     const int z0 = (int)(lb / ((long long)ntx * nty)) * zp, z1 = min(z0 + zp, nz);
@@ -893,18 +954,43 @@ static MarchSplit march_split(size_t nlines, int n) {
     return best;
 }
 
+// Segments per line of k_adj_cells by the same estimate, in chunks of 16 cells
+static int cells_split(size_t nlines, int n) {
+    int best = 1;
+    double cost = 0.0;
+    for (int nseg = 1; nseg <= kAcSeg && nseg <= n / 4; nseg *= 2) {
+        const size_t lb = kAcSeg / nseg, k = ((nlines + lb - 1) / lb + 255) / 256;
+        const int len = (n + nseg - 1) / nseg;
+        const double c = ((len + kAcTA - 1) / kAcTA + 0.4) * ((double)(k / 2) * 2.0 + (k % 2 ? 1.4 : 0.0));
+        if (nseg == 1 || c < cost) best = nseg, cost = c;
+    }
+    return best;
+}
+
 template <int WW>
 static void adj_conv(const BoxDesc &b, hipStream_t s, const AdjGeom &g, const double *u, const double *rbar,
                      double *ubar) {
-    // blocks of the x kernel: 4 rows each
-    const unsigned bx = (unsigned)(((size_t)b.ny * b.nz + 3) / 4);
-    hipLaunchKernelGGL((k_adj_conv<0, WW>), dim3(bx), dim3(256), 0, s, g, u, rbar, ubar, 0);
-    const size_t ly = (size_t)b.nx * b.nz, lz = (size_t)b.nx * b.ny;
-    const MarchSplit my = march_split(ly, b.ny), mz = march_split(lz, b.nz);
-    hipLaunchKernelGGL((k_adj_march<1, WW>), dim3((unsigned)((ly + my.Lb - 1) / my.Lb)), dim3(kAmThreads), 0, s, g, u, rbar,
-                       ubar, my.Lb, my.nseg);
-    hipLaunchKernelGGL((k_adj_march<2, WW>), dim3((unsigned)((lz + mz.Lb - 1) / mz.Lb)), dim3(kAmThreads), 0, s, g, u, rbar,
-                       ubar, mz.Lb, mz.nseg);
+    const size_t lx = (size_t)b.ny * b.nz, ly = (size_t)b.nx * b.nz, lz = (size_t)b.nx * b.ny;
+    auto cells = [&](auto kernel, size_t nlines, int n) {
+        const int nseg = cells_split(nlines, n), lb = kAcSeg / nseg;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((nlines + lb - 1) / lb)), dim3(256), 0, s, g, u, rbar, ubar, nseg);
+    };
+    auto march = [&](auto kernel, size_t nlines, int n) {
+        const MarchSplit m = march_split(nlines, n);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((nlines + m.Lb - 1) / m.Lb)), dim3(kAmThreads), 0, s, g, u, rbar, ubar,
+                           m.Lb, m.nseg);
+    };
+    cells(k_adj_cells<0, WW>, lx, b.nx);
+    // The march fills the chip from about 64^3 points on (32 us along y there, 128^3 167); below,
+    // its shortest segments of four cells in turn take longer than a chunk of cells side by side
+    // (32^3: 24.4 us against 13.0).
+    if (b.n3 < (1u << 18)) {
+        cells(k_adj_cells<1, WW>, ly, b.ny);
+        cells(k_adj_cells<2, WW>, lz, b.nz);
+    } else {
+        march(k_adj_march<1, WW>, ly, b.ny);
+        march(k_adj_march<2, WW>, lz, b.nz);
+    }
 }
 
 // the stage-combination epilogue by separate launches (boxes without viscous terms)
@@ -912,6 +998,16 @@ __global__ void k_epilogue(size_t n, const double *__restrict__ fin, AdjEpilogue
     const size_t o = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
     if (o >= n) return;
     adj_epilogue_at(e, o, fin[o]);
+}
+
+// Planes per block of k_adj_visc: a block forms two planes of lookahead on either side again,
+// so it takes as many planes as leave a block for every CU (product of a 130 x 90 x 66 box:
+// 315 us with 16 planes and 300 blocks, 341 with 4, 370 with 32; 32^3: 58 us with 2, 110 with
+// 16), and 32 where that still leaves two (140^3: 2 % less than with 16).
+static int adj_visc_planes(long long cols, int nz) {
+    int zp = 32;
+    while (zp > 2 && cols * ((nz + zp - 1) / zp) < (zp == 32 ? 512 : 256)) zp /= 2;
+    return zp;
 }
 
 static void rhs_vjp(const BoxDesc &b, int weights, hipStream_t s, const double *u, const double *rbar, double *ubar,
@@ -923,9 +1019,10 @@ static void rhs_vjp(const BoxDesc &b, int weights, hipStream_t s, const double *
     AdjEpilogue e;
     if (epi) e = *epi;
     if (b.mu > 0.0) {
-        const unsigned tiles = (unsigned)(((b.nx + kAvTX - 1) / kAvTX) * (long long)((b.ny + kAvTY - 1) / kAvTY) *
-                                          ((b.nz + adj_visc_planes(b.nz) - 1) / adj_visc_planes(b.nz)));
-        hipLaunchKernelGGL(k_adj_visc, dim3(tiles), dim3(kPointThreads), 0, s, g, u, rbar, ubar, e);
+        const long long cols = (long long)((b.nx + kAvTX - 1) / kAvTX) * ((b.ny + kAvTY - 1) / kAvTY);
+        const int zp = adj_visc_planes(cols, b.nz);
+        hipLaunchKernelGGL(k_adj_visc, dim3((unsigned)(cols * ((b.nz + zp - 1) / zp))), dim3(kPointThreads), 0, s, g, u, rbar,
+                           ubar, e, zp);
     } else if (epi) {
         // ubar holds the finished product; the epilogue reads it from there
         const size_t n5 = 5 * b.n3;

@@ -1,7 +1,7 @@
 // cns_device_adj.h -- hand-written reverse-mode (vector-Jacobian) products of the
 // device arithmetic in cns_device.h, FP64.  Each *_vjp function recomputes the
-// forward values it needs and ADDS the input adjoints to its outputs (weno5_lr_vjp
-// sets them).
+// forward values it needs and ADDS the input adjoints to its outputs (weno5_cell_vjp and
+// roe_mean_vjp set them).
 #pragma once
 #include "cns_device.h"
 
@@ -86,123 +86,6 @@ __device__ __forceinline__ void weno_side_vjp(double s1, double s2, double s3, d
     }
 }
 
-// One Jiang-Shu side in the scaled form of the forward (weno5_lr6): candidates Q_k six
-// times the plain ones, S_k = 4 (eps + beta_k), weights w_k = g_k A_k / sum with
-// g = (1, 6, 3), A_k = t_k^2 and t_k the product of the other two S.  Given the
-// adjoint Vb6 of V6 = sum w_k Q_k: V6, the candidate adjoints Qb_k = Vb6 w_k and TWICE
-// the adjoints of S_k, from dV6/dS_k = -2 w_k (Q_k - V6) / S_k with 1/S_k = t_k / P,
-// P = S1 S2 S3 (one reciprocal, of P sum).
-__device__ __forceinline__ void js_side_vjp(double S1, double S2, double S3, double Q1, double Q2, double Q3,
-                                            double Vb6, double &V6, double Qb[3], double Sb2[3]) {
-    const double t1 = S2 * S3, t2 = S1 * S3, t3 = S1 * S2;
-    const double B1 = t1 * t1, B2 = 6.0 * (t2 * t2), B3 = 3.0 * (t3 * t3);  // g_k A_k
-    const double P = t1 * S1;
-    const double sum = B1 + B2 + B3;
-    const double num = B1 * Q1 + B2 * Q2 + B3 * Q3;
-    const double iD = rcp(P * sum);
-    const double iS = P * iD;
-    V6 = num * iS;
-    const double h = Vb6 * iS;
-    Qb[0] = h * B1;
-    Qb[1] = h * B2;
-    Qb[2] = h * B3;
-    const double g = -4.0 * Vb6 * iD;
-    Sb2[0] = g * ((Q1 - V6) * (B1 * t1));
-    Sb2[1] = g * ((Q2 - V6) * (B2 * t2));
-    Sb2[2] = g * ((Q3 - V6) * (B3 * t3));
-}
-
-// ---------------------------------------------------------------------------
-// WENO5 pair (weno5_lr with the weights WW): given the adjoints Lb, Rb of the left-
-// and right-biased values at j+1/2, SET qb[0..5] to dL/dq^T Lb + dR/dq^T Rb
-// (q = j-2 .. j+3); the values L and R themselves are returned in Lv, Rv.
-// ---------------------------------------------------------------------------
-template <int WW = CNS_WENO_JS>
-__device__ __forceinline__ void weno5_lr_vjp(const double q[6], double eps, double Lb, double Rb, double qb[6],
-                                             double &Lv, double &Rv) {
-    const double m2 = q[0], m1 = q[1], c0 = q[2], p1 = q[3], p2 = q[4], p3 = q[5];
-    if constexpr (WW == CNS_WENO_JS) {
-        // six times the candidates (the right-biased side reuses L2, L3 mirrored), the
-        // second differences and the one-sided terms, all from the first differences
-        // g_i = q_{i+1} - q_i as in the forward (the terms keep their signs here: the
-        // scatter below uses them unsquared)
-        const double g0 = m1 - m2, g1 = c0 - m1, g2 = p1 - c0, g3 = p2 - p1, g4 = p3 - p2;
-        const double c6 = 6.0 * c0;
-        const double L1 = (5.0 * g1 - 2.0 * g0) + c6;     // 2 m2 - 7 m1 + 11 c0
-        const double L2 = (g1 + 2.0 * g2) + c6;           // -m1 + 5 c0 + 2 p1
-        const double L3 = (4.0 * g2 - g3) + c6;           // 2 c0 + 5 p1 - p2
-        const double R1 = 6.0 * p1 - 5.0 * g3 + 2.0 * g4;  // 2 p3 - 7 p2 + 11 p1
-        const double da = g1 - g0, db = g2 - g1, dc = g3 - g2, dd = g4 - g3;
-        const double ea = 3.0 * g1 - g0;     // m2 - 4 m1 + 3 c0
-        const double eb = -(g1 + g2);        // m1 - p1
-        const double ec = -(3.0 * g2 - g3);  // 3 c0 - 4 p1 + p2
-        const double fa = -(3.0 * g3 - g4);  // p3 - 4 p2 + 3 p1
-        const double fb = g2 + g3;           // p2 - c0
-        const double fc = 3.0 * g2 - g1;     // 3 p1 - 4 c0 + m1
-        // S = 4 eps + (13/3) d^2 + e^2
-        const double k = 13.0 / 3.0, e4 = 4.0 * eps;
-        const double kda = k * da, kdb = k * db, kdc = k * dc, kdd = k * dd;
-        const double sb = kdb * db + e4, sc = kdc * dc + e4;
-        const double SL1 = (kda * da + e4) + ea * ea, SL2 = sb + eb * eb, SL3 = sc + ec * ec;
-        const double SR1 = (kdd * dd + e4) + fa * fa, SR2 = sc + fb * fb, SR3 = sb + fc * fc;
-        double VL, VR, QL[3], QR[3], BL[3], BR[3];
-        js_side_vjp(SL1, SL2, SL3, L1, L2, L3, Lb * (1.0 / 6.0), VL, QL, BL);
-        js_side_vjp(SR1, SR2, SR3, R1, L3, L2, Rb * (1.0 / 6.0), VR, QR, BR);
-        Lv = VL * (1.0 / 6.0);
-        Rv = VR * (1.0 / 6.0);
-        // adjoints of the candidates, and of d and e through S (dS/dd = 2 k d, dS/de = 2 e;
-        // BL, BR carry the factor 2)
-        const double cL1 = QL[0], cL2 = QL[1] + QR[2], cL3 = QL[2] + QR[1], cR1 = QR[0];
-        const double dab = kda * BL[0], dbb = kdb * (BL[1] + BR[2]), dcb = kdc * (BL[2] + BR[1]), ddb = kdd * BR[0];
-        const double eab = ea * BL[0], ebb = eb * BL[1], ecb = ec * BL[2];
-        const double fab = fa * BR[0], fbb = fb * BR[1], fcb = fc * BR[2];
-        qb[0] = dab + eab + 2.0 * cL1;
-        qb[1] = -2.0 * dab + dbb - 4.0 * eab + ebb + fcb - 7.0 * cL1 - cL2;
-        qb[2] = dab - 2.0 * dbb + dcb + 3.0 * eab + 3.0 * ecb - fbb - 4.0 * fcb + 11.0 * cL1 + 5.0 * cL2 + 2.0 * cL3;
-        qb[3] = dbb - 2.0 * dcb + ddb - ebb - 4.0 * ecb + 3.0 * fab + 3.0 * fcb + 2.0 * cL2 + 5.0 * cL3 + 11.0 * cR1;
-        qb[4] = dcb - 2.0 * ddb + ecb - 4.0 * fab + fbb - cL3 - 7.0 * cR1;
-        qb[5] = ddb + fab + 2.0 * cR1;
-        return;
-    }
-    const double r6 = 1.0 / 6.0, k13 = 13.0 / 12.0;
-    const double L1 = (2.0 * m2 - 7.0 * m1 + 11.0 * c0) * r6;
-    const double L2 = (-m1 + 5.0 * c0 + 2.0 * p1) * r6;
-    const double L3 = (2.0 * c0 + 5.0 * p1 - p2) * r6;
-    const double R1 = (2.0 * p3 - 7.0 * p2 + 11.0 * p1) * r6;
-    const double da = m2 - 2.0 * m1 + c0, db = m1 - 2.0 * c0 + p1, dc = c0 - 2.0 * p1 + p2, dd = p1 - 2.0 * p2 + p3;
-    const double ea = m2 - 4.0 * m1 + 3.0 * c0, eb = m1 - p1, ec = 3.0 * c0 - 4.0 * p1 + p2;
-    const double fa = p3 - 4.0 * p2 + 3.0 * p1, fb = p2 - c0, fc = 3.0 * p1 - 4.0 * c0 + m1;
-    const double s1 = eps + (k13 * da * da + 0.25 * ea * ea);
-    const double s2 = eps + (k13 * db * db + 0.25 * eb * eb);
-    const double s3 = eps + (k13 * dc * dc + 0.25 * ec * ec);
-    const double u1 = eps + (k13 * dd * dd + 0.25 * fa * fa);
-    const double u2 = eps + (k13 * dc * dc + 0.25 * fb * fb);
-    const double u3 = eps + (k13 * db * db + 0.25 * fc * fc);
-    double L, R, w[3], v[3], dL[3], dR[3];
-    weno_side_vjp<WW>(s1, s2, s3, L1, L2, L3, L, w, dL);  // left-biased
-    weno_side_vjp<WW>(u1, u2, u3, R1, L3, L2, R, v, dR);  // right-biased (mirrored stencils)
-
-    // candidates
-    const double cL1 = Lb * w[0], cL2 = Lb * w[1] + Rb * v[2], cL3 = Lb * w[2] + Rb * v[1], cR1 = Rb * v[0];
-    // indicators
-    const double bL1 = Lb * dL[0], bL2 = Lb * dL[1], bL3 = Lb * dL[2];
-    const double bR1 = Rb * dR[0], bR2 = Rb * dR[1], bR3 = Rb * dR[2];
-    const double dab = 2.0 * k13 * da * bL1, eab = 0.5 * ea * bL1;
-    const double dbb = 2.0 * k13 * db * (bL2 + bR3), ebb = 0.5 * eb * bL2, fcb = 0.5 * fc * bR3;
-    const double dcb = 2.0 * k13 * dc * (bL3 + bR2), ecb = 0.5 * ec * bL3, fbb = 0.5 * fb * bR2;
-    const double ddb = 2.0 * k13 * dd * bR1, fab = 0.5 * fa * bR1;
-    qb[0] = 2.0 * r6 * cL1 + dab + eab;
-    qb[1] = -7.0 * r6 * cL1 - r6 * cL2 - 2.0 * dab + dbb - 4.0 * eab + ebb + fcb;
-    qb[2] = 11.0 * r6 * cL1 + 5.0 * r6 * cL2 + 2.0 * r6 * cL3 + dab - 2.0 * dbb + dcb + 3.0 * eab + 3.0 * ecb -
-             fbb - 4.0 * fcb;
-    qb[3] = 2.0 * r6 * cL2 + 5.0 * r6 * cL3 + 11.0 * r6 * cR1 + dbb - 2.0 * dcb + ddb - ebb - 4.0 * ecb + 3.0 * fab +
-             3.0 * fcb;
-    qb[4] = -r6 * cL3 - 7.0 * r6 * cR1 + dcb - 2.0 * ddb + ecb - 4.0 * fab + fbb;
-    qb[5] = 2.0 * r6 * cR1 + ddb + fab;
-    Lv = L;
-    Rv = R;
-}
-
 // ---------------------------------------------------------------------------
 // The reconstructions of one cell transposed (weno5_cell6 with the weights WW): given the
 // adjoints Lb6, Rb6 of L6 and R6, six times the left-biased value at the cell's right face and
@@ -274,17 +157,6 @@ __device__ __forceinline__ void weno5_cell_vjp(const double q[5], double eps4, d
     qb[4] = h3;
 }
 
-// component v of the convective flux along DIR
-template <int DIR>
-__device__ __forceinline__ double euler_flux_comp(const double w[5], double gm1, int v) {
-    const double inv = rcp(w[0]);
-    const double vn = w[1 + DIR] * inv;
-    if (v == 0) return w[1 + DIR];
-    const double p = gm1 * (w[4] - 0.5 * (w[1] * (w[1] * inv) + w[2] * (w[2] * inv) + w[3] * (w[3] * inv)));
-    if (v == 4) return (w[4] + p) * vn;
-    return w[v] * vn + (v == 1 + DIR ? p : 0.0);
-}
-
 // wb += (df/dw)^T fb for the convective flux along DIR (the Euler flux Jacobian).
 // With v = m / rho, K = |v|^2 / 2, p = (gamma-1)(e - rho K), H = (e + p) / rho,
 // phi = fb[1..3], psi = fb[4] and s = (gamma-1)(phi_n + psi v_n):
@@ -321,9 +193,6 @@ __device__ __forceinline__ void euler_flux_vjp(const double w[5], double gm1, co
 struct RoeFace {
     double ra, rb, iw, wa, wb, v[3], H, q2, c, ic, ic2, l1, l2, l5;
 };
-__device__ __forceinline__ double pressure(const double w[5], double gm1) {
-    return gm1 * (w[4] - 0.5 * rcp(w[0]) * (w[1] * w[1] + w[2] * w[2] + w[3] * w[3]));
-}
 template <int DIR>
 __device__ __forceinline__ RoeFace roe_face(const double a[5], double pa, const double b[5], double pb, double gm1,
                                             double delta) {
@@ -447,86 +316,11 @@ __device__ __forceinline__ void roe_cells_vjp(const RoeFace &R, const double a[5
     cell(b, Hb, ib, R.wb, sbb * (0.5 * R.rb), bb);
 }
 
-// ---------------------------------------------------------------------------
-// Convective interface flux H = (FL + FR)/2 - D/2 (interface_flux without the viscous
-// part), transposed for the six cell states j-2 .. j+3, which sit at offsets c[0..5]
-// of the array st, components 0-4, with their point fluxes along DIR as components
-// 5-9 (component stride cs; the caller stages them in LDS).  The
-// contributions leave through two callbacks as soon as they are formed, so that no
-// 6 x 5 array of them is ever held:
-//   addF(m, v, x): x is a term of the adjoint of the POINT FLUX of cell j-2+m, component
-//     v (each reconstruction carries Hb/2); the flux Jacobian transpose that takes it to
-//     the cell state is linear in it, so the caller sums these terms over the six
-//     interfaces that read a cell and applies the transpose once per cell;
-//   addU(m, v, x): a term of the adjoint of the STATE of cell j-2+m, through the Roe
-//     dissipation and the reconstructed states.
-// For each (m, v) the terms are produced in a fixed order.  The states are read again
-// from st at each stage instead of being held, and the compiler barrier between stages
-// keeps it from merging the loads back into one live set.
-// ---------------------------------------------------------------------------
+// Ends a stage: the compiler neither merges loads nor moves arithmetic across it, so that a
+// stage's values are not all live at once.
 __device__ __forceinline__ void adj_stage_fence() {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-}
-
-template <int DIR, int WW, class AddF, class AddU>
-__device__ __forceinline__ void interface_flux_vjp(const double *st, int cs, const int c[6], const double Hb[5],
-                                                   double gamma, double eps, double delta, AddF addF, AddU addU) {
-    {
-        // component by component, the adjoints of the reconstructions of the point fluxes
-#pragma unroll
-        for (int v = 0; v < 5; ++v) {
-            const double *f = st + (5 + v) * cs;
-            double q[6], qb[6];
-#pragma unroll
-            for (int m = 0; m < 6; ++m) q[m] = f[c[m]];
-            double Lv, Rv;
-            weno5_lr_vjp<WW>(q, eps, 0.5 * Hb[v], 0.5 * Hb[v], qb, Lv, Rv);
-#pragma unroll
-            for (int m = 0; m < 6; ++m) addF(m, v, qb[m]);
-            adj_stage_fence();
-        }
-    }
-    // dissipation D = M(a, b) du at cells a = j, b = j+1: first dub = M^T Db, which needs
-    // no du; the reverse of the reconstructed states then yields du itself (UR - UL);
-    // last the adjoints of a and b through M
-    const double gm1 = gamma - 1.0;
-    double a[5], b[5], Db[5], du[5], dub[5] = {0, 0, 0, 0, 0};
-    double ab[5] = {0, 0, 0, 0, 0}, bb[5] = {0, 0, 0, 0, 0};
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-        a[v] = st[v * cs + c[2]];
-        b[v] = st[v * cs + c[3]];
-        Db[v] = -0.5 * Hb[v];
-    }
-    const RoeFace R = roe_face<DIR>(a, pressure(a, gm1), b, pressure(b, gm1), gm1, delta);
-    roe_jump_vjp<DIR>(R, gm1, Db, dub);
-    adj_stage_fence();
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-        const double *f = st + v * cs;
-        double q[6], qb[6], UL, UR;
-#pragma unroll
-        for (int m = 0; m < 6; ++m) q[m] = f[c[m]];
-        weno5_lr_vjp<WW>(q, eps, -dub[v], dub[v], qb, UL, UR);
-        du[v] = UR - UL;
-#pragma unroll
-        for (int m = 0; m < 6; ++m) addU(m, v, qb[m]);
-        adj_stage_fence();
-    }
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-        a[v] = st[v * cs + c[2]];
-        b[v] = st[v * cs + c[3]];
-    }
-    double vbar[3], Hbar;
-    roe_mean_vjp<DIR>(R, gm1, delta, du, Db, vbar, Hbar);
-    roe_cells_vjp(R, a, pressure(a, gm1), b, pressure(b, gm1), gm1, vbar, Hbar, ab, bb);
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-        addU(2, v, ab[v]);
-        addU(3, v, bb[v]);
-    }
 }
 
 }  // namespace cns
