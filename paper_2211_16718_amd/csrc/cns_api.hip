@@ -174,7 +174,27 @@ struct Core {
     // round times rounds (32^3: 1 point, 0.02 against 0.06 ms per sweep with 16); 16 is doubled
     // up to 128 while the launch still has 2^19 threads (longer segments form fewer cells
     // twice; 512^3: 128 points).
+    // Whether a stage goes through the two launches of k_small: FP64, rows in LDS, and at most
+    // 1.5 M points, where side by side the launches' ends overlap and the buffers stay in the
+    // caches.  RK4 step, separate launches -> together: 32^3 187 -> 92 us, 64^3 288 -> 223,
+    // 130 x 90 x 66 808 -> 620, 112^3 1050 -> 990, but 210 x 117 x 75 (1.8 M) 1262 -> 1322 and
+    // 128^3 1175 -> 1451, for the three sums cost 30 fields.  Without viscous terms three
+    // sweeps of one length are left: 64^3 240 -> 190, 72^3 311 -> 283, 80^3 363 -> 374.
+    bool small() const {
+        size_t n = 0;
+        bool visc = false;
+        for (const BoxDesc &b : boxes) {
+            if (b.nx > 2 * kRowThreads) return false;
+            n += b.n3;
+            visc |= b.mu > 0.0;
+        }
+        return prec == CNS_FP64 && xrows_pref && n <= (visc ? (size_t)3 << 19 : (size_t)3 << 17);
+    }
+
     void default_segs() {
+        // threads of a direction that fill the chip: alone, or with the other kernels beside it
+        // (64^3: 288 us a step with 2^17, 258 with 2^16, 230 with 2^15)
+        const double cap_threads = small() ? 1 << 15 : 1 << 17;
         for (int d = 0; d < 3; ++d) {
             auto threads = [&](int seg) {
                 double t = 0.0;
@@ -187,7 +207,7 @@ struct Core {
             int best = 16;
             double least = 1e300;
             for (int seg : {16, 8, 4, 2, 1}) {
-                const double cost = std::max(1.0, threads(seg) / (1 << 17)) * (seg + 3.5);
+                const double cost = std::max(1.0, threads(seg) / cap_threads) * (seg + 3.5);
                 if (cost < least) {
                     least = cost;
                     best = seg;
@@ -199,7 +219,8 @@ struct Core {
         }
         // planes per block of the viscous kernel: 16, or less while that does not make two
         // blocks for each CU (the two extra planes on either side of a block cost a long
-        // batch more than the idle CUs of a short one)
+        // batch more than the idle CUs of a short one), or 128 blocks beside the sweeps (72^3:
+        // 341 us a step, 385 with 256)
         auto tiles = [&](int cap) {
             long long t = 0;
             for (const BoxDesc &b : boxes) {
@@ -209,7 +230,7 @@ struct Core {
             return t;
         };
         int cap = 16;
-        while (cap > 4 && tiles(cap) < 512) cap /= 2;
+        while (cap > 2 && tiles(cap) < (small() ? 128 : 512)) cap /= 2;
         for (BoxDesc &b : boxes) b.vsz = std::max(diag_planes(b.nx, b.ny, b.nz), cap);
     }
 
@@ -298,6 +319,7 @@ struct Core {
         for (int f = 0; f < F_N; ++f) bt.grid[f] = grid[f];
         bt.stream = stream;
         bt.prof = prof.on ? &prof : nullptr;
+        bt.small = small() && block == 256;
         return bt;
     }
 
@@ -457,7 +479,12 @@ static void write_cache(const char *path, const std::map<std::string, int> &m) {
 static int autotune(Core &c, const char *cache_path) {
     int rc = c.sync_table();
     if (rc) return rc;
-    const std::string pre = arch_name() + (c.prec == CNS_FP64 ? "|fp64|" : "|mixed|");
+    // a small batch's sweeps run beside each other: timed as they run, under keys of their own
+    const bool small = c.small();
+    const std::string pre = arch_name() + (c.prec == CNS_FP64 ? "|fp64|" : "|mixed|") + (small ? "stage|" : "");
+    auto time_sweeps = [&](const Batch &bt, int reps) {
+        return small ? time_rhs_kernels(bt, reps) : time_sweeps_yz(bt, reps);
+    };
     std::map<std::string, int> cache = read_cache(cache_path);
     bool changed = false;
     // size classes
@@ -494,8 +521,8 @@ static int autotune(Core &c, const char *cache_path) {
                 c.dirty = true;
                 if ((rc = c.sync_table())) return rc;
                 Batch bt = c.batch();
-                time_sweeps_yz(bt, 1);  // warm
-                float ms = time_sweeps_yz(bt, 3);
+                time_sweeps(bt, 1);  // warm
+                float ms = time_sweeps(bt, 3);
                 if (ms < best_ms) {
                     best_ms = ms;
                     best = sgl;
@@ -571,8 +598,8 @@ static int autotune(Core &c, const char *cache_path) {
             c.dirty = true;
             if ((rc = c.sync_table())) return rc;
             Batch bt = c.batch();
-            time_sweeps_yz(bt, 1);
-            float ms = time_sweeps_yz(bt, 3);
+            time_sweeps(bt, 1);
+            float ms = time_sweeps(bt, 3);
             if (ms < best_ms) {
                 best_ms = ms;
                 best = blk;

@@ -35,7 +35,9 @@ constexpr int kViscSZ = 16;               // planes per block of the tiled kerne
 __host__ __device__ __forceinline__ int diag_planes(int nx, int ny, int nz) {
     if (nz >= 256) return 2 * kViscSZ;
     const long long t16 = (long long)((nx + kViscTX - 1) / kViscTX) * ((ny + kViscTY - 1) / kViscTY) * ((nz + 15) / 16);
-    return t16 >= 512 ? kViscSZ : 4;
+    if (t16 >= 512) return kViscSZ;
+    const long long t4 = (long long)((nx + kViscTX - 1) / kViscTX) * ((ny + kViscTY - 1) / kViscTY) * ((nz + 3) / 4);
+    return t4 > 64 ? 4 : 2;
 }
 // tiles (one per (x, y) tile and group) of a box: of the diagnostics kernel, and of the FP64
 // viscous kernel's fused diagnostics
@@ -146,6 +148,7 @@ struct Batch {
     size_t rowLds = 0;  // LDS bytes of the rows kernel (max over boxes)
     size_t esz = 8;     // bytes per state element
     size_t n3_0 = 0;    // points of the first box (single-box calls)
+    bool small = false; // a stage's kernels run side by side (k_small)
     hipStream_t stream = nullptr;
     Prof *prof = nullptr;
     const GraphParams *gp = nullptr;  // set while a run is captured for graph replay
