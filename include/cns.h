@@ -142,7 +142,7 @@ int cns_tvdrk3(cns_plan *plan, void *u_dev, double dt, int32_t nsteps, double *d
  *   moments_dev[2] = the Taylor microscale sqrt(5 moments[0] / moments[1]) of isotropic
  *   turbulence (+inf for a uniform velocity).
  * moments_dev holds three doubles.  FP64 for either precision.
- * Uses the plan's stage buffers as scratch (ordered with other calls on the plan's
+ * Uses the plan's scratch buffers (ordered with other calls on the plan's
  * stream).  nshell must equal cns_spectrum_shells(plan) (round(|k|max) + 1), else
  * CNS_EINVAL; grids with a dimension above 2047, more than 4096 shells, or more than one
  * shell per 1.2 grid points (24 bytes of scratch per shell) give CNS_EUNSUPPORTED.  Shell

@@ -895,7 +895,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void k_sweep_x_rows(Launch L0) {
 //
 // One after the other, small boxes pay four short kernels, each a fraction of the chip and as
 // long as its chain of planes or cells (32^3: 17 + 8 + 9 + 10 us); side by side a stage takes
-// the longest (32^3: 16 us) and 4.5 us for the sum.  At 64^3 the kernels share the chip: 46 us
+// the longest (32^3: 18 us) and 4.5 us for the sum.  At 64^3 the kernels share the chip: 46 us
 // and 12 us for the sum's 24-34 fields, against 75.
 // ----------------------------------------------------------------------------
 struct SmallFams {
@@ -1172,11 +1172,13 @@ __device__ __forceinline__ bool point_stats(const double s[5], double gamma, dou
 // 4th-order central derivative of the velocity, whose x and y neighbours come from an
 // LDS copy of plane k staged from the column and ring windows, and whose z neighbours
 // from the column's window of five planes in registers.  The loads of a plane are issued
-// a plane ahead of its use: 128^3 34.8 -> 29.4 us, 256^3 in the mixed form 171 -> 134 (FP64 212
-// before and after: the tiles' 1.2 GB with halos at the rate of the caches).  Four blocks
-// on a CU in FP32; in FP64 that many would spill (32.9 us).
-template <typename T>
-__global__ __launch_bounds__(kDiagThreads, sizeof(T) == 8 ? 2 : 4) void k_diag_partial(Launch L0) {
+// a plane ahead of its use: 128^3 34.8 -> 29.4 us, in the mixed form at 256^3 171 -> 134.  In a
+// large FP64 box (512^3 1.6 ms as before) the rate of the caches at which the tiles' 1.5 times the
+// state with halos come bounds it.  OCC, blocks on a CU: four hold all 1024 blocks of such a box
+// at once (with three 512^3 took 1.72 ms); where three suffice, FP64 takes the variant without
+// spills (128^3: 31.6 us with four).
+template <typename T, int OCC>
+__global__ __launch_bounds__(kDiagThreads, OCC) void k_diag_partial(Launch L0) {
     const Launch L = with_params(L0);
     __shared__ double red[kDiagThreads / 64][CNS_NDIAG];
     __shared__ double pv[3][kViscTY + 4][kViscTX + 4];
@@ -1190,12 +1192,12 @@ __global__ __launch_bounds__(kDiagThreads, sizeof(T) == 8 ? 2 : 4) void k_diag_p
         const int bi = find_box(L.off, L.nbox, vb);
         const BoxDesc &bx = L.boxes[bi];
         const int nx = bx.nx, ny = bx.ny, nz = bx.nz;
-        const size_t n3 = bx.n3, sz = (size_t)nx * ny;
+        const size_t n3 = uni64(bx.n3), sz = (size_t)nx * ny;
         const int nblk = diag_blocks(nx, ny, nz);
         const long long ntile = diag_tiles(nx, ny, nz);
         const int grp = diag_planes(nx, ny, nz);
         const int lb = (int)(vb - L.off[bi]);
-        const gptr<const T> u = glob((const T *)state_ptr(bx, L, BUF_U));
+        const gptr<const T> u = uni(glob((const T *)state_ptr(bx, L, BUF_U)));
         const double gamma = bx.gamma, ihx = bx.inv_h[0], ihy = bx.inv_h[1], ihz = bx.inv_h[2];
         const int ntx = (nx + kViscTX - 1) / kViscTX, nty = (ny + kViscTY - 1) / kViscTY;
         const int tx = threadIdx.x % kViscTX, ty = threadIdx.x / kViscTX;
@@ -1205,52 +1207,55 @@ __global__ __launch_bounds__(kDiagThreads, sizeof(T) == 8 ? 2 : 4) void k_diag_p
             const int z0 = (int)(tile / ((long long)ntx * nty)) * grp, z1 = min(z0 + grp, nz);
             const bool act = x0 + tx < nx && y0 + ty < ny;
             // a column past a ragged edge wraps periodically (halo of the columns beside it)
-            const size_t col = (size_t)wrapm(y0 + ty, ny) * nx + wrapm(x0 + tx, nx);
-            const size_t rcol = (size_t)wrapm(y0 - 2 + rhy, ny) * nx + wrapm(x0 - 2 + rhx, nx);
+            const uint32_t col = (uint32_t)wrapm(y0 + ty, ny) * nx + wrapm(x0 + tx, nx);
+            const uint32_t rcol = (uint32_t)wrapm(y0 - 2 + rhy, ny) * nx + wrapm(x0 - 2 + rhx, nx);
             double vz[5][3];    // this column's velocity at planes k-2 .. k+2
             unsigned good = 0;  // bit m: the column's point at plane k-2+m is valid
             // the loads of plane k+2 (column and ring point) are issued a plane ahead
             T sn[5], rn[4];
             auto load_col = [&](int zp, T s[5]) {
-                const size_t i = col + wrapi(zp, nz) * sz;
+                const uint32_t bo = (uint32_t)((col + wrapi(zp, nz) * sz) * sizeof(T));
 #pragma unroll
-                for (int c = 0; c < 5; ++c) s[c] = u[c * n3 + i];
+                for (int c = 0; c < 5; ++c) s[c] = *elem(u, n3, c, bo);
             };
             auto load_ring = [&](int zp, T s[4]) {
-                const size_t i = rcol + wrapi(zp, nz) * sz;
+                const uint32_t bo = (uint32_t)((rcol + wrapi(zp, nz) * sz) * sizeof(T));
 #pragma unroll
-                for (int c = 0; c < 4; ++c) s[c] = u[c * n3 + i];
+                for (int c = 0; c < 4; ++c) s[c] = *elem(u, n3, c, bo);
             };
-            {
-                T s4[4][5], r2[2][4];
+            // the four planes before them at once, or in two pairs where that would hold too much
+            constexpr int H = sizeof(T) == 8 && OCC == 4 ? 2 : 4;
 #pragma unroll
-                for (int m = 0; m < 4; ++m) load_col(z0 - 2 + m, s4[m]);
-                if (ring) {
+            for (int h = 0; h < 4; h += H) {
+                T s4[H][5], r1[H / 2][4];
 #pragma unroll
-                    for (int m = 0; m < 2; ++m) load_ring(z0 + m, r2[m]);
+                for (int m = 0; m < H; ++m) load_col(z0 - 2 + h + m, s4[m]);
+                if (ring)
+#pragma unroll
+                    for (int m = 0; m < H / 2; ++m) load_ring(z0 + h / 2 + m, r1[m]);
+                if (h + H == 4) {
+                    load_col(z0 + 2, sn);
+                    if (ring) load_ring(z0 + 2, rn);
                 }
-                load_col(z0 + 2, sn);
-                if (ring) load_ring(z0 + 2, rn);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const int zp = z0 - 2 + m;
+                for (int m = 0; m < H; ++m) {
+                    const int zp = z0 - 2 + h + m;
                     const double s[5] = {double(s4[m][0]), double(s4[m][1]), double(s4[m][2]), double(s4[m][3]),
                                          double(s4[m][4])};
                     if (act && zp >= z0 && zp < z1) {
-                        if (point_stats(s, gamma, acc, vz[m])) good |= 1u << m;
+                        if (point_stats(s, gamma, acc, vz[h + m])) good |= 1u << (h + m);
                     } else {
-                        vel_of(s, vz[m]);
+                        vel_of(s, vz[h + m]);
                     }
                 }
-                if (ring) {
+                if (ring)
 #pragma unroll
-                    for (int m = 0; m < 2; ++m) {
-                        const double ir = rcp(double(r2[m][0]));
+                    for (int m = 0; m < H / 2; ++m) {
+                        const double ir = rcp(double(r1[m][0]));
 #pragma unroll
-                        for (int c = 0; c < 3; ++c) rv[m][c][rt] = double(r2[m][1 + c]) * ir;
+                        for (int c = 0; c < 3; ++c) rv[h / 2 + m][c][rt] = double(r1[m][1 + c]) * ir;
                     }
-                }
             }
             int slot = 0;  // (k - z0) mod 3
             for (int k = z0; k < z1; ++k) {
@@ -1719,7 +1724,11 @@ static void diag_t(const Batch &bt, const void *u_ov, double *diag, long long st
     L.diag = diag;
     L.diag_box_stride = stride;
     L.step = step;
-    hipLaunchKernelGGL(k_diag_partial<T>, dim3(grid_of(bt, F_DIAG, L.total)), dim3(kDiagThreads), 0, bt.stream, L);
+    const dim3 g(grid_of(bt, F_DIAG, L.total)), b(kDiagThreads);
+    const bool three = sizeof(T) == 8 && g.x <= 768;
+    if constexpr (sizeof(T) == 8)
+        if (three) hipLaunchKernelGGL((k_diag_partial<T, 3>), g, b, 0, bt.stream, L);
+    if (!three) hipLaunchKernelGGL((k_diag_partial<T, 4>), g, b, 0, bt.stream, L);
     const Launch F = with_family(bt, L, F_BOX);
     hipLaunchKernelGGL(k_diag_final, dim3(grid_for(F.total)), dim3(kDiagThreads), 0, bt.stream, F);
 }
