@@ -35,29 +35,38 @@ sys.path.insert(0, ROOT)
 
 # Algorithmic FP64 operations per grid point of one launch (add, sub, mul, div and
 # sqrt count one each; an FMA counts two), from the kernels' formulation:
-#   point flux 18, WENO5 L+R pair 122 x 10 scalars, Roe dissipation 116,
-#   interface flux 20, viscous interface flux 24, difference 10, plus the output
-#   update (write 0 / accumulate 5 / fused RK4 stage ~30).
+#   point flux 18, the two WENO5 values of a cell 72 x 9 scalars, Roe dissipation 116,
+#   interface flux 20, difference 10, plus the output update (write 0, the viscous term 4,
+#   accumulate 5, fused RK4 stage ~30).
 FLOPS_PER_POINT = {
+    "sweep_x": 18 + 648 + 116 + 20 + 10 + 4,
+    "sweep_y": 18 + 648 + 116 + 20 + 10 + 5,
+    "sweep_z_rk4": 18 + 648 + 116 + 20 + 10 + 30,
+    "visc_flux": 13 + 12 * 5 + 40 + 12 * 7,  # primitives, 12 derivatives, tau/q/G, their differences
+    "diagnostics": 120,
+}
+# The mixed form evaluates both values at an interface (122 x 10 scalars) and differences
+# the viscous fluxes in the sweeps.
+FLOPS_PER_POINT_MIXED = {
     "sweep_x": 18 + 1220 + 5 + 116 + 20 + 24 + 10,
     "sweep_y": 18 + 1220 + 5 + 116 + 20 + 24 + 10 + 5,
     "sweep_z_rk4": 18 + 1220 + 5 + 116 + 20 + 24 + 10 + 30,
-    "visc_flux": 13 + 12 * 5 + 40,  # primitives of the point, 12 derivatives, tau/q/G
+    "visc_flux": 13 + 12 * 5 + 40,
     "diagnostics": 120,
 }
 # Algorithmic HBM bytes per grid point of one launch (FP64): each array element
 # read or written once; the fused RK4 stage is averaged over the four stages
 # (u^n read in stages 2-4, the accumulator written in stage 2 and read in stage 4).
 BYTES_PER_POINT = {
-    "sweep_x": 8 * (5 + 4 + 5),            # u, 4 viscous fluxes -> rhs
-    "sweep_y": 8 * (5 + 4 + 5 + 5),        # + rhs read-modify-write
-    "sweep_z_rk4": 8 * (5 + 4 + 5 + 5) + 8 * (15 + 5 + 5) // 4,  # u, G, rhs -> next stage; + u^n, acc
-    "visc_flux": 8 * (5 + 9),              # u -> 9 viscous-flux fields
+    "sweep_x": 8 * (5 + 4 + 5),            # u, 4 viscous terms -> rhs
+    "sweep_y": 8 * (5 + 5 + 5),            # u, rhs read-modify-write
+    "sweep_z_rk4": 8 * (5 + 5 + 5) + 8 * (15 + 5 + 5) // 4,  # u, rhs -> next stage; + u^n, acc
+    "visc_flux": 8 * (5 + 4),              # u -> 4 viscous terms
     "diagnostics": 8 * 5,
 }
-# The mixed form (FP32 state, G and rhs; FP64 accumulator, updated in every stage): u^n
-# read in stages 2-3, the accumulator written in stage 1, updated in stages 2-3 and read
-# in stage 4.
+# The mixed form (FP32 state, nine viscous fluxes and rhs; FP64 accumulator, updated in every
+# stage): u^n read in stages 2-3, the accumulator written in stage 1, updated in stages 2-3
+# and read in stage 4.
 BYTES_PER_POINT_MIXED = {
     "sweep_x": 4 * (5 + 4 + 5),
     "sweep_y": 4 * (5 + 4 + 5 + 5),
@@ -73,7 +82,8 @@ PEAK_FP32_TFLOPS = 157.3  # MI355X FP32 vector (published; its 2x over FP64 need
 PEAK_HBM_GBS = 8000.0     # MI355X HBM3E
 PEAK_VALU_LANE_INSTR = 256 * 4 * 16 * 2.4e9  # VALU lane-instructions per second (3.93e13)
 # rocprofv3 kernel names -> the library's kernel kinds
-KERNEL_KIND_OF = (("k_sweep_x_rows", "sweep_x"), ("k_sweep_x_chunks", "sweep_x"), ("k_visc_flux", "visc_flux"), ("k_diag_partial", "diagnostics"),
+KERNEL_KIND_OF = (("k_sweep_x_rows", "sweep_x"), ("k_sweep_x_chunks", "sweep_x"), ("k_visc_flux", "visc_flux"), ("k_visc<", "visc_flux"),
+                  ("k_small", "stage_kernels"), ("k_stage_sum", "stage_sum"), ("k_diag_partial", "diagnostics"),
                   ("k_diag_final", "diagnostics_final"), ("k_stream_copy", "stream_copy"),
                   ("k_init_state", "init_state"), ("k_speed_", "max_wave_speed"))
 
@@ -88,7 +98,7 @@ def kernel_source_digest():
     import hashlib
 
     h = hashlib.sha256()
-    for f in ("cns_kernels.hip", "cns_device.h", "cns_internal.h"):
+    for f in ("cns_kernels.hip", "cns_mixed.hip", "cns_device.h", "cns_batch.h", "cns_internal.h"):
         h.update(open(os.path.join(ROOT, "paper_2211_16718_amd", "csrc", f), "rb").read())
     return h.hexdigest()
 
@@ -224,7 +234,8 @@ def main():
         k["share"] = k["total_ms"] / tot
     dom = max(kernels, key=lambda k: kernels[k]["total_ms"])
     avg_s = kernels[dom]["avg_ms"] / 1e3
-    flops = FLOPS_PER_POINT[dom] * n ** 3
+    flops_pp = (FLOPS_PER_POINT if fp64 else FLOPS_PER_POINT_MIXED)[dom]
+    flops = flops_pp * n ** 3
     achieved = flops / avg_s / 1e12
     del u_start
     copy = copy_reference(args.copy_gib, stream)
@@ -270,7 +281,7 @@ def main():
         "traffic_source": traffic_note,
         "algorithmic_bytes_per_launch": bpp * n ** 3,
         "hbm_frac_algorithmic": round(bpp * n ** 3 / avg_s / 1e9 / PEAK_HBM_GBS, 4),
-        "flops_per_point": FLOPS_PER_POINT[dom],
+        "flops_per_point": flops_pp,
         "avg_launch_ms": round(kernels[dom]["avg_ms"], 5),
     }
     if traffic:
@@ -730,8 +741,10 @@ def kernel_kind(name):
     the direction and the output mode of a marching sweep)."""
     if "k_sweep<" in name and "k_sweep_x_rows" not in name:
         args = [a.strip() for a in name.split("k_sweep<", 1)[1].split(">", 1)[0].split(",")]
-        d, mode = int(args[2]), int(args[3])
-        return ("sweep_x", "sweep_y", "sweep_z_rk4" if mode == 2 else "sweep_z")[d]
+        # FP64: type, direction, mode (2-4 the stage update); mixed: two types, direction, mode
+        k = 2 if not args[1].isdigit() else 1
+        d, mode = int(args[k]), int(args[k + 1])
+        return ("sweep_x", "sweep_y", "sweep_z_rk4" if 2 <= mode <= 4 else "sweep_z")[d]
     for key, kind in KERNEL_KIND_OF:
         if key in name:
             return kind
