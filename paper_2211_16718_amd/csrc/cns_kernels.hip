@@ -400,6 +400,9 @@ __device__ __forceinline__ void visc_blocks(const Launch &L, const VbRange R, Vi
             step(std::integral_constant<int, 4>{}, k);
             if (++k >= z1 + 2) break;
         }
+        // the next virtual block may give a halo point to another wave, which fills its ring
+        // where this block's last step has just stored
+        __syncthreads();
     }
 }
 
