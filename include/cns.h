@@ -181,7 +181,10 @@ int cns_diagnostics_host(const cns_plan *plan, const void *u_dev, double *out_ho
  * every launch (an event wait after each step).  Kernel kinds, in order:
  * viscous primitives (formed inside the viscous-flux kernel: no launches, kept so the
  * indices stay stable), viscous fluxes, x sweep, y sweep, z sweep with the fused RK4
- * stage update, diagnostics.  enable != 0 clears the totals and turns timing on. */
+ * stage update, diagnostics.  enable != 0 clears the totals and turns timing on.  While it
+ * is on, a small FP64 batch runs these kernels one after the other (same results), not
+ * side by side in one launch per stage as otherwise: its totals are those of the kernels
+ * alone, and their sum is more than its steps take. */
 #define CNS_NKERNEL 6
 int cns_profile_enable(cns_plan *plan, int32_t enable);
 /* Summed milliseconds and launch counts per kernel kind since the last enable
@@ -230,15 +233,17 @@ int cns_ensemble_get_tiles(const cns_ensemble *ens, int32_t box, int32_t *seg3_h
  * be NULL): a JSON file read first (known choices are not re-timed) and rewritten with
  * new ones.  Synchronises the ensemble's stream.  Launch shapes never change results. */
 int cns_ensemble_autotune(cns_ensemble *ens, const char *cache_path);
-/* The launch shapes of box `box`: rows per block of its x rows kernel (0: the marching
- * x sweep), and the launched blocks of the marching sweeps and of the tiled kernels of the
+/* The launch shapes of box `box`: rows per block of its x rows kernel (as set; 0: the
+ * marching or the chunked x sweep), and the launched blocks of the marching sweeps and of the tiled kernels of the
  * whole ensemble (0: one block per virtual block). */
 int cns_ensemble_get_launch(const cns_ensemble *ens, int32_t box, int32_t *rows_host, int64_t *sweep_grid_host,
                             int64_t *tile_grid_host);
 /* Set launch shapes by hand: rows per block of the x rows kernel of box `box` (-1: every
  * box; 0: the default; a count that does not fit gives CNS_EINVAL), and the launched blocks
  * of the marching sweeps and of the tiled kernels (0: one per virtual block; any positive
- * count: a persistent launch whose blocks loop over the virtual blocks).  Results do not
+ * count: a persistent launch whose blocks loop over the virtual blocks; a small FP64 batch,
+ * whose stages otherwise run their kernels side by side in one launch with one block per
+ * virtual block, then runs them one after the other).  Results do not
  * depend on the launched blocks (bitwise), nor in FP64 on the rows (a count above what a
  * block's threads hold runs as that many); in the mixed form not on the rows as long as
  * the points per thread of its x rows kernel (rows * nx / 256, rounded up, the largest over

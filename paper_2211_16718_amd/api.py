@@ -247,6 +247,8 @@ class Plan:
 
     # ---- per-kernel timing -------------------------------------------------
     def profile(self, enable=True):
+        """Time every launch of the steps by kernel.  A small FP64 box then runs its kernels
+        one after the other, not side by side as otherwise."""
         check(self.lib.cns_profile_enable(self.h, 1 if enable else 0), "cns_profile_enable")
 
     def profile_read(self):
@@ -340,7 +342,8 @@ class Ensemble:
         return r.value, gs.value, gt.value
 
     def set_launch(self, box=-1, rows=0, sweep_grid=0, tile_grid=0):
-        """Launch shapes by hand (see :meth:`get_launch`); results do not change."""
+        """Launch shapes by hand (see :meth:`get_launch`); results do not change.  With launched
+        blocks given, a small FP64 batch runs its kernels one after the other."""
         check(self.lib.cns_ensemble_set_launch(self.h, int(box), int(rows), int(sweep_grid), int(tile_grid)),
               "cns_ensemble_set_launch")
 

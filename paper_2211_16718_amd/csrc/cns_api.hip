@@ -319,7 +319,8 @@ struct Core {
         for (int f = 0; f < F_N; ++f) bt.grid[f] = grid[f];
         bt.stream = stream;
         bt.prof = prof.on ? &prof : nullptr;
-        bt.small = small() && block == 256;
+        // launched blocks asked for by hand are those of the kernels one after the other
+        bt.small = small() && block == 256 && !grid[F_SWEEP_Y] && !grid[F_VISC];
         return bt;
     }
 
@@ -477,6 +478,11 @@ static void write_cache(const char *path, const std::map<std::string, int> &m) {
 }
 
 static int autotune(Core &c, const char *cache_path) {
+    if (c.small()) {  // the side-by-side launches it would run with
+        c.block = 256;
+        for (long long &g : c.grid) g = 0;
+        c.dirty = true;
+    }
     int rc = c.sync_table();
     if (rc) return rc;
     // a small batch's sweeps run beside each other: timed as they run, under keys of their own

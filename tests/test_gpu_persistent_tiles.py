@@ -3,6 +3,7 @@ tile counts let the wave that holds a halo point change from one virtual block t
 Every virtual block computes the same whichever launched block runs it, so the results are
 those of one launched block per virtual block, bit for bit."""
 import bisect
+import time
 
 import numpy as np
 import pytest
@@ -61,3 +62,28 @@ def test_looping_viscous_blocks_give_the_same_bits(grid, diag):
         assert torch.equal(a, b)
     if diag:
         assert torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("grids", [(1, 0), (0, 1), (1, 1)])
+def test_launched_blocks_take_effect_in_a_small_batch(grids):
+    """A 48^3 box (its stages side by side by default) with one launched block per kernel:
+    one CU of 256 does the work of a sweep or of the viscous kernel, so a step takes many
+    times as long, and gives the same bits."""
+    print(f"[case] launched blocks {grids} of a small batch", flush=True)
+    shape, stream = (48, 48, 48), torch.cuda.Stream()
+    out, took = [], []
+    for sweep_grid, tile_grid in ((0, 0), grids):
+        ens = Ensemble([dict(shape=shape, mu_eff=0.02, dt=1e-4)], stream=stream)
+        ens.set_launch(sweep_grid=sweep_grid, tile_grid=tile_grid)
+        with torch.cuda.stream(stream):
+            rho, vel, p, _ = I.smooth_primitives(shape, seed=3, amp=0.3, kmax=3)
+            Plan(shape, mu_eff=0.02, stream=stream).init_state(rho, vel, p, out=ens.state(0))
+            ens.run(1, diag=False, graph=False)
+            stream.synchronize()
+            t = time.perf_counter()
+            ens.run(4, diag=False, graph=False)
+            stream.synchronize()
+            took.append(time.perf_counter() - t)
+        out.append(ens.state(0).clone())
+    assert torch.equal(out[0], out[1])
+    assert took[1] > 4.0 * took[0], took
