@@ -229,7 +229,8 @@ int cns_ensemble_get_tiles(const cns_ensemble *ens, int32_t box, int32_t *seg3_h
  * keeps 90 % of a block's threads busy); for the batch, the threads per block of the marching sweeps and the launched
  * grids (one block per virtual block, or persistent grids of one or two rounds of the
  * blocks the chip holds at once, for the sweeps and for the tiled viscous-flux and
- * diagnostics kernels).  Only scratch buffers are written while timing.  cache_path (may
+ * diagnostics kernels; a small FP64 batch that runs its stages side by side keeps one block
+ * per virtual block).  Only scratch buffers are written while timing.  cache_path (may
  * be NULL): a JSON file read first (known choices are not re-timed) and rewritten with
  * new ones.  Synchronises the ensemble's stream.  Launch shapes never change results. */
 int cns_ensemble_autotune(cns_ensemble *ens, const char *cache_path);

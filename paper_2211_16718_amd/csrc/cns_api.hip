@@ -485,9 +485,12 @@ static int autotune(Core &c, const char *cache_path) {
     }
     int rc = c.sync_table();
     if (rc) return rc;
-    // a small batch's sweeps run beside each other: timed as they run, under keys of their own
+    // A small batch's sweeps run beside each other and are timed as they run, under keys of
+    // their own: these times cover every kernel of the stage and, since a launch of a few
+    // boxes leaves CUs idle, depend on how many boxes of the size there are.
     const bool small = c.small();
-    const std::string pre = arch_name() + (c.prec == CNS_FP64 ? "|fp64|" : "|mixed|") + (small ? "stage|" : "");
+    const std::string pre = arch_name() + (c.prec == CNS_FP64 ? "|fp64|" : "|mixed|") +
+                            (small ? (c.any_visc ? "stage-visc|" : "stage-euler|") : "");
     auto time_sweeps = [&](const Batch &bt, int reps) {
         return small ? time_rhs_kernels(bt, reps) : time_sweeps_yz(bt, reps);
     };
@@ -508,10 +511,11 @@ static int autotune(Core &c, const char *cache_path) {
         for (int i = 0; i < c.nbox(); ++i)
             c.active[i] = std::find(members.begin(), members.end(), i) != members.end();
     };
+    auto count = [&](const std::vector<int> &members) { return small ? "x" + std::to_string(members.size()) : ""; };
     // 1. segment length of the marching y/z sweeps per size class
     const int segs[] = {2, 4, 8, 16, 32, 64};
     for (auto &kv : cls) {
-        const std::string key = pre + kv.first + "|seg";
+        const std::string key = pre + kv.first + count(kv.second) + "|seg";
         int best = -1;
         auto it = cache.find(key);
         const BoxDesc &bk = c.boxes[kv.second[0]];
@@ -549,7 +553,7 @@ static int autotune(Core &c, const char *cache_path) {
     // points per thread keep results bitwise independent of the choice.
     for (auto &kv : cls) {
         const int nx = c.boxes[kv.second[0]].nx;
-        const std::string key = pre + kv.first + "|rows";
+        const std::string key = pre + kv.first + count(kv.second) + "|rows";
         auto it = cache.find(key);
         int best = 0;
         if (it != cache.end() && it->second >= 0 && (it->second == 0 || rows_fit(nx, it->second, c.esz))) {
@@ -617,7 +621,8 @@ static int autotune(Core &c, const char *cache_path) {
     }
     // 4. launched grids: one block per virtual block, or persistent grids of one or two
     // rounds of the blocks the chip holds at once, for the marching sweeps and for the
-    // tiled viscous-flux and diagnostics kernels (code 10 * sweeps + tiles)
+    // tiled viscous-flux and diagnostics kernels (code 10 * sweeps + tiles).  Side-by-side
+    // stages have one block per virtual block: nothing to time, code 0.
     c.dirty = true;
     if ((rc = c.sync_table())) return rc;
     {
@@ -626,7 +631,10 @@ static int autotune(Core &c, const char *cache_path) {
         const std::string gkey = pre + "grid|b" + std::to_string(c.block) + all;
         auto git = cache.find(gkey);
         int best = 0;
-        if (git != cache.end() && git->second >= 0 && git->second <= 22 && git->second % 10 <= 2) {
+        if (bt0.small) {
+            changed |= git == cache.end() || git->second != 0;
+            cache[gkey] = 0;
+        } else if (git != cache.end() && git->second >= 0 && git->second <= 22 && git->second % 10 <= 2) {
             best = git->second;
         } else {
             float best_ms = 1e30f;
