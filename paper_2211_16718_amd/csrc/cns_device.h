@@ -120,8 +120,11 @@ __device__ __forceinline__ double weno_map(double w1, double w2, double w3, doub
 // Jiang-Shu alpha_k = c_k / S_k^2; CNS_WENO_Z, the WENO-Z weights of Borges et al. (2008),
 // alpha_k = c_k (1 + (tau5/S_k)^2), tau5 = |S_1 - S_3|; CNS_WENO_M, the mapped weights
 // above.  The alpha are scaled by S_1^2 S_2^2 S_3^2, so a normalisation takes one
-// reciprocal; where the range allows the two sides share it, 1/D_L = D_R / (D_L D_R) (a
-// product of eight S factors, inside the FP64 range for the eps a plan admits).
+// reciprocal.  Range, with S about the square of a jump of the scalar: the two Jiang-Shu
+// sides share one, 1/D_L = D_R / (D_L D_R), a product of eight S factors (jumps to about
+// 1e18); WENO-Z has products of six S factors for each side (1e25) and the mapped weights
+// of four (1e37), so these take a reciprocal for each side.  From below the eps a plan
+// admits bounds every S.
 template <int WW>
 __device__ __forceinline__ void weno5_cell6(double m2, double m1, double c0, double p1, double p2, double eps4,
                                             double &L6, double &R6) {
@@ -148,7 +151,7 @@ __device__ __forceinline__ void weno5_cell6(double m2, double m1, double c0, dou
     const double b1 = 3.0 * a1, b3 = 3.0 * a3;
     double xL, xR;
     if constexpr (WW == CNS_WENO_M) {
-        const double r = rcp(dL * dR), iL = dR * r, iR = dL * r;
+        const double iL = rcp(dL), iR = rcp(dR);
         double gL[3], gR[3];
         const double GL = weno_map(a1 * iL, t2 * iL, b3 * iL, gL), GR = weno_map(a3 * iR, t2 * iR, b1 * iR, gR);
         const double q = rcp(GL * GR);
@@ -160,7 +163,7 @@ __device__ __forceinline__ void weno5_cell6(double m2, double m1, double c0, dou
             const double r = rcp(dL * dR);
             xL = nL * (dR * r);
             xR = nR * (dL * r);
-        } else {  // products of six S factors: a reciprocal for each side
+        } else {
             xL = nL * rcp(dL);
             xR = nR * rcp(dR);
         }

@@ -121,8 +121,9 @@ __device__ __forceinline__ void weno5_cell_vjp(const double q[5], double eps4, d
         const double B1 = 3.0 * A1, B2 = 6.0 * A2, B3 = 3.0 * A3;
         const double s = (A1 + A3) + B2;
         const double dL = 2.0 * A3 + s, dR = 2.0 * A1 + s;
-        const double rr = rcp(dL * dR), iL = dR * rr, iR = dL * rr;
-        const double iP4 = -4.0 * rcp(t1 * S1);
+        // 1/P shares the left side's reciprocal (seven S factors), not the two sides one (eight)
+        const double P = t1 * S1, r = rcp(dL * P), iL = P * r, iR = rcp(dR);
+        const double iP4 = -4.0 * (dL * r);
         xL = (A1 * l1 + (B2 * l2 + B3 * l3)) * iL;
         xR = (A3 * r3 + (B2 * r2 + B1 * r1)) * iR;
         const double hL = Lb6 * iL, hR = -Rb6 * iR;
