@@ -1135,16 +1135,22 @@ static_assert(kDiagThreads == kViscTX * kViscTY, "one thread to each column of a
 
 // velocity m/rho of a state
 __device__ __forceinline__ void vel_of(const double s[5], double v[3]) {
+#pragma clang fp contract(off)
     const double ir = rcp(s[0]);
     v[0] = s[1] * ir;
     v[1] = s[2] * ir;
     v[2] = s[3] * ir;
 }
 
+// The point quantities and sums of a record state every operation (contraction off), here, in
+// the kernels below and in the viscous kernel (prim_stats), so that a record has the same bits
+// from every kernel and variant that forms it.
+
 // Point quantities of one state (kinetic energy, mass, momentum, energy, the largest
 // wave speed |v_d| + c, the bad-point count) added to acc; returns whether the point is
 // valid (finite, rho > 0, p > 0) and its velocity in v.
 __device__ __forceinline__ bool point_stats(const double s[5], double gamma, double acc[CNS_NDIAG], double v[3]) {
+#pragma clang fp contract(off)
     const double r = s[0], mx = s[1], my = s[2], mz = s[3], e = s[4];
     const double inv = rcp(r);
     v[0] = mx * inv;
@@ -1182,6 +1188,7 @@ __device__ __forceinline__ bool point_stats(const double s[5], double gamma, dou
 // spills (128^3: 31.6 us with four).
 template <typename T, int OCC>
 __global__ __launch_bounds__(kDiagThreads, OCC) void k_diag_partial(Launch L0) {
+#pragma clang fp contract(off)
     const Launch L = with_params(L0);
     __shared__ double red[kDiagThreads / 64][CNS_NDIAG];
     __shared__ double pv[3][kViscTY + 4][kViscTX + 4];
@@ -1201,7 +1208,9 @@ __global__ __launch_bounds__(kDiagThreads, OCC) void k_diag_partial(Launch L0) {
         const int grp = diag_planes(nx, ny, nz);
         const int lb = (int)(vb - L.off[bi]);
         const gptr<const T> u = uni(glob((const T *)state_ptr(bx, L, BUF_U)));
-        const double gamma = bx.gamma, ihx = bx.inv_h[0], ihy = bx.inv_h[1], ihz = bx.inv_h[2];
+        const double gamma = bx.gamma;
+        // the 1/12 of the central differences is folded into the spacings
+        const double ihx = bx.inv_h[0] / 12.0, ihy = bx.inv_h[1] / 12.0, ihz = bx.inv_h[2] / 12.0;
         const int ntx = (nx + kViscTX - 1) / kViscTX, nty = (ny + kViscTY - 1) / kViscTY;
         const int tx = threadIdx.x % kViscTX, ty = threadIdx.x / kViscTX;
         double acc[CNS_NDIAG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -1291,12 +1300,12 @@ __global__ __launch_bounds__(kDiagThreads, OCC) void k_diag_partial(Launch L0) {
                 if (act && (good & 4u)) {
                     // vorticity with the 4th-order central derivative
                     const int X = tx + 2, Y = ty + 2;
-                    const double dvzdy = dcen(pv[2][Y - 2][X], pv[2][Y - 1][X], pv[2][Y + 1][X], pv[2][Y + 2][X]) * ihy;
-                    const double dvydz = dcen(vz[0][1], vz[1][1], vz[3][1], vz[4][1]) * ihz;
-                    const double dvxdz = dcen(vz[0][0], vz[1][0], vz[3][0], vz[4][0]) * ihz;
-                    const double dvzdx = dcen(pv[2][Y][X - 2], pv[2][Y][X - 1], pv[2][Y][X + 1], pv[2][Y][X + 2]) * ihx;
-                    const double dvydx = dcen(pv[1][Y][X - 2], pv[1][Y][X - 1], pv[1][Y][X + 1], pv[1][Y][X + 2]) * ihx;
-                    const double dvxdy = dcen(pv[0][Y - 2][X], pv[0][Y - 1][X], pv[0][Y + 1][X], pv[0][Y + 2][X]) * ihy;
+                    const double dvzdy = dcen12(pv[2][Y - 2][X], pv[2][Y - 1][X], pv[2][Y + 1][X], pv[2][Y + 2][X]) * ihy;
+                    const double dvydz = dcen12(vz[0][1], vz[1][1], vz[3][1], vz[4][1]) * ihz;
+                    const double dvxdz = dcen12(vz[0][0], vz[1][0], vz[3][0], vz[4][0]) * ihz;
+                    const double dvzdx = dcen12(pv[2][Y][X - 2], pv[2][Y][X - 1], pv[2][Y][X + 1], pv[2][Y][X + 2]) * ihx;
+                    const double dvydx = dcen12(pv[1][Y][X - 2], pv[1][Y][X - 1], pv[1][Y][X + 1], pv[1][Y][X + 2]) * ihx;
+                    const double dvxdy = dcen12(pv[0][Y - 2][X], pv[0][Y - 1][X], pv[0][Y + 1][X], pv[0][Y + 2][X]) * ihy;
                     const double ox = dvzdy - dvydz, oy = dvxdz - dvzdx, oz = dvydx - dvxdy;
                     if (isfinite(ox) && isfinite(oy) && isfinite(oz)) acc[1] += 0.5 * (ox * ox + oy * oy + oz * oz);
                 }
@@ -1341,6 +1350,7 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_final(Launch L0) {
 // ----------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(kDiagThreads) void k_speed_partial(Launch L0) {
+#pragma clang fp contract(off)
     const Launch L = with_params(L0);
     __shared__ double red[kDiagThreads / 64][2];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
