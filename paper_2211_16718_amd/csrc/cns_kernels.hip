@@ -402,7 +402,7 @@ __device__ __forceinline__ void visc_blocks(const Launch &L, const VbRange R, Vi
         }
         // the next virtual block may give a halo point to another wave, which fills its ring
         // where this block's last step has just stored
-        __syncthreads();
+        if (vb + R.stride < R.end) __syncthreads();
     }
 }
 
