@@ -223,10 +223,7 @@ struct Core {
         // 341 us a step, 385 with 256)
         auto tiles = [&](int cap) {
             long long t = 0;
-            for (const BoxDesc &b : boxes) {
-                const int v = std::max(diag_planes(b.nx, b.ny, b.nz), cap);
-                t += (long long)((b.nx + kViscTX - 1) / kViscTX) * ((b.ny + kViscTY - 1) / kViscTY) * ((b.nz + v - 1) / v);
-            }
+            for (const BoxDesc &b : boxes) t += plane_tiles(b.nx, b.ny, b.nz, std::max(diag_planes(b.nx, b.ny, b.nz), cap));
             return t;
         };
         int cap = 16;
@@ -315,7 +312,7 @@ struct Core {
         // with one point per thread the mixed form's rows kernel lays its fields 256 points apart
         bt.rowLds = prec != CNS_FP64 && rowP == 1 && rowLds > 0 ? (size_t)14 * kRowThreads * esz : rowLds;
         bt.esz = esz;
-        bt.n3_0 = boxes[0].n3;
+        bt.box0 = boxes.data();
         for (int f = 0; f < F_N; ++f) bt.grid[f] = grid[f];
         bt.stream = stream;
         bt.prof = prof.on ? &prof : nullptr;

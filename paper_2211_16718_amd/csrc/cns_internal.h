@@ -29,21 +29,22 @@ constexpr int kViscTX = 32, kViscTY = 8;  // (x, y) tile of the viscous, diagnos
 constexpr int kViscSZ = 16;               // planes per block of the tiled kernels
 // Planes per group of the diagnostics: a partial sum covers one (x, y) tile and one group, so
 // the sums do not depend on how many groups a block of the viscous kernel marches over.
-// 32 in boxes at least 256 deep and 16 where that still makes 512 tiles, which keeps the
-// partials few and the +-2-plane halo of a block small; else 4, so that a small box can be
-// cut into many short blocks.
+// 32 in boxes at least 256 deep, else 16, where that still makes 512 tiles, which keeps the
+// partials few and the +-2-plane halo of a block small; else 4 or 2, so that a small box can be
+// cut into many short blocks (viscous terms of a 40 x 16 x 300 box: 73 us in blocks of 32
+// planes, 23 of 4).
+__host__ __device__ __forceinline__ long long plane_tiles(int nx, int ny, int nz, int planes) {
+    return (long long)((nx + kViscTX - 1) / kViscTX) * ((ny + kViscTY - 1) / kViscTY) * ((nz + planes - 1) / planes);
+}
 __host__ __device__ __forceinline__ int diag_planes(int nx, int ny, int nz) {
-    if (nz >= 256) return 2 * kViscSZ;
-    const long long t16 = (long long)((nx + kViscTX - 1) / kViscTX) * ((ny + kViscTY - 1) / kViscTY) * ((nz + 15) / 16);
-    if (t16 >= 512) return kViscSZ;
-    const long long t4 = (long long)((nx + kViscTX - 1) / kViscTX) * ((ny + kViscTY - 1) / kViscTY) * ((nz + 3) / 4);
-    return t4 > 64 ? 4 : 2;
+    const int deep = nz >= 256 ? 2 * kViscSZ : kViscSZ;
+    if (plane_tiles(nx, ny, nz, deep) >= 512) return deep;
+    return plane_tiles(nx, ny, nz, 4) > 64 ? 4 : 2;
 }
 // tiles (one per (x, y) tile and group) of a box: of the diagnostics kernel, and of the FP64
 // viscous kernel's fused diagnostics
 __host__ __device__ __forceinline__ long long diag_tiles(int nx, int ny, int nz) {
-    const int g = diag_planes(nx, ny, nz);
-    return (long long)((nx + kViscTX - 1) / kViscTX) * ((ny + kViscTY - 1) / kViscTY) * ((nz + g - 1) / g);
+    return plane_tiles(nx, ny, nz, diag_planes(nx, ny, nz));
 }
 // Partial-sum slots of a box's diagnostics: one per block of the diagnostics kernel (at
 // most kDiagBlocksMax) or one per tile when the diagnostics ride on the viscous kernel.
@@ -92,6 +93,7 @@ struct Launch {
     int scheme;       // CNS_RK4 or CNS_TVDRK3 for the fused update
     int step;         // diagnostics record index
     // single-box overrides (used when non-null / positive)
+    int vsz_ov;        // replaces the box's planes per block of the viscous kernel
     const void *u_ov;  // replaces the box's state u
     void *a_ov, *b_ov;  // replace the box's stage buffers A, B
     void *out_ov;      // replaces rhs as the output of WRITE/ACCUM sweeps
@@ -147,7 +149,7 @@ struct Batch {
     int rowP = 1;       // points per thread of the mixed form's rows kernel (max over boxes)
     size_t rowLds = 0;  // LDS bytes of the rows kernel (max over boxes)
     size_t esz = 8;     // bytes per state element
-    size_t n3_0 = 0;    // points of the first box (single-box calls)
+    const BoxDesc *box0 = nullptr;  // host copy of the first box (single-box calls)
     bool small = false; // a stage's kernels run side by side (k_small)
     hipStream_t stream = nullptr;
     Prof *prof = nullptr;

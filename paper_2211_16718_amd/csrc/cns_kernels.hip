@@ -202,7 +202,7 @@ __device__ __forceinline__ void visc_blocks(const Launch &L, const VbRange R, Vi
         if (own_e) Tile::ext_pos(e, ebx, eby);
         const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY;
         const int x0 = (int)(lb % ntx) * TX, y0 = (int)((lb / ntx) % nty) * TY;
-        const int vsz = b.vsz;
+        const int vsz = L.vsz_ov ? L.vsz_ov : b.vsz;
         const int z0 = (int)(lb / ((long long)ntx * nty)) * vsz, z1 = min(z0 + vsz, nz);
         const bool act = x0 + tx < nx && y0 + ty < ny;
         // a column past a ragged edge wraps periodically: its primitives are halo values
@@ -1485,8 +1485,7 @@ long long family_blocks(const BoxDesc &b, int fam, int block) {
             return cdiv((long long)g.npq * cdiv(g.nline, b.seg[d]), block);
         }
         case F_DIAG: return diag_blocks(b.nx, b.ny, b.nz);
-        case F_VISC:
-            return cdiv(b.nx, kViscTX) * cdiv(b.ny, kViscTY) * cdiv(b.nz, b.vsz);
+        case F_VISC: return plane_tiles(b.nx, b.ny, b.nz, b.vsz);
         case F_BOX: return 1;
     }
     return 0;
@@ -1717,10 +1716,17 @@ static void viscous_t(const Batch &bt, const void *u_ov, void *out_ov) {
         mixed::viscous(bt, L);
     } else {
         // rows 1-4 of the output; the density row has no viscous term
-        const size_t n3 = bt.n3_0;
-        L.v_ov = (T *)out_ov + n3;
-        launch_fill(bt.prec, n3, out_ov, bt.stream);
-        visc_fields<T>(bt, L);
+        const BoxDesc &b = *bt.box0;
+        L.v_ov = (T *)out_ov + b.n3;
+        launch_fill(bt.prec, b.n3, out_ov, bt.stream);
+        // alone on the chip, with no sweeps beside it: fewer planes per block than in a stage
+        // while that leaves CUs without one (8 x 128 x 128: 42 us with 16 planes, 26 with 8;
+        // 112^3: 58 us with 16, 66 with 8)
+        L = with_family(bt, L, F_VISC);
+        L.vsz_ov = b.vsz;
+        while (L.vsz_ov > 2 && plane_tiles(b.nx, b.ny, b.nz, L.vsz_ov) < 256) L.vsz_ov /= 2;
+        L.total = plane_tiles(b.nx, b.ny, b.nz, L.vsz_ov);
+        hipLaunchKernelGGL((k_visc<T, false>), dim3(grid_for(L.total)), dim3(ViscTile<T>::kThreads), 0, bt.stream, L);
     }
 }
 
