@@ -293,6 +293,12 @@ __global__ __launch_bounds__(kAmThreads, 2) void k_adj_march(AdjGeom g, const do
 // slot per face, and the states, pressures and rbar of the chunk, whose next cells are
 // loaded a chunk ahead.
 //
+// SPARE: where a segment's last chunk leaves lanes idle, the one past its end forms the last
+// face with the chunk, as the lane of a cell whose reconstructions carry nothing; otherwise
+// one lane forms it after the chunks.  In small boxes, whose launches last as long as one
+// segment, that is a quarter of the time (16^3, three directions 39.8 -> 28.2 us); large ones do
+// not wait for it and would pay the products by zero (128^3, WENO-Z: 712 -> 730 us).
+//
 // Bound by FP64 issue (75 % of the rate) and LDS (47 % busy), two waves per SIMD.  128^3 along
 // x: 181 us against 215 with a lane per interface; 130 x 90 x 66: 92 against 117.
 // ---------------------------------------------------------------------------
@@ -302,7 +308,7 @@ constexpr int kAcKA = kAcTA + 4;                // summed cells I-2 .. I+TA+1
 constexpr int kAcSeg = 4 * kAcLW;               // segments of a block
 constexpr int kAcWave = (12 * kAcNC + 9 * kAcKA + 10 * (kAcTA + 1)) * kAcLW;
 
-template <int DIR, int WW>
+template <int DIR, int WW, bool SPARE>
 __global__ __launch_bounds__(256, 2) void k_adj_cells(AdjGeom g, const double *u_, const double *rbar_, double *ubar_,
                                                       int nseg) {
     constexpr int TA = kAcTA, LW = kAcLW, NC = kAcNC, KA = kAcKA;
@@ -404,7 +410,8 @@ __global__ __launch_bounds__(256, 2) void k_adj_cells(AdjGeom g, const double *u
     // the segments of a wave may differ by one cell, and so by one chunk
     for (bool live = ok; __any(live);) {
         adj_stage_fence();
-        const bool act = live && I + ta < s1, more = live && I + TA < s1;
+        const bool act = live && I + ta < (SPARE ? s1 + 1 : s1), more = live && I + TA < s1;
+        const double own = !SPARE || I + ta < s1 ? 1.0 : 0.0;
         double un[5], rn[5];
         if (more) {
             load5(u, cell(I + TA + 3 + ta), un);
@@ -417,7 +424,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_cells(AdjGeom g, const double *u
             for (int v = 0; v < 5; ++v) {
                 const double r0 = S(7 + v, ta + 2);
                 Hl[v] = (r0 - S(7 + v, ta + 1)) * ih12;
-                Hr[v] = (S(7 + v, ta + 3) - r0) * ih12;
+                Hr[v] = own * ((S(7 + v, ta + 3) - r0) * ih12);
                 pin(Hl[v]), pin(Hr[v]);
             }
             {
@@ -434,7 +441,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_cells(AdjGeom g, const double *u
                         if (v < 4) xn[m] = S(v + 1, ta + m);
                     }
                     adj_stage_fence();
-                    weno5_cell_vjp<WW>(x, eps4, Hr[v], Hl[v], xb, L6, R6);
+                    weno5_cell_vjp<WW>(x, eps4, Hr[v], own * Hl[v], xb, L6, R6);
 #pragma unroll
                     for (int m = 0; m < 5; ++m) atomicAdd(&A(4 + v, ta + m), xb[m]);
                     adj_stage_fence();
@@ -451,8 +458,8 @@ __global__ __launch_bounds__(256, 2) void k_adj_cells(AdjGeom g, const double *u
             for (int v = 0; v < 5; ++v) {
 #pragma unroll
                 for (int m = 0; m < 5; ++m) x[m] = xn[m];
-                double Lb = -dub[v], Rb = dl;
-                if (v == 1 + DIR) Lb += Hr[0], Rb += Hl[0];
+                double Lb = -dub[v], Rb = own * dl;
+                if (v == 1 + DIR) Lb += Hr[0], Rb += own * Hl[0];
                 if (v < 4) {
 #pragma unroll
                     for (int m = 0; m < 5; ++m) xn[m] = S(v + 1, ta + m);
@@ -513,7 +520,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_cells(AdjGeom g, const double *u
     }
     adj_stage_fence();
     const int c1 = s1 - I;  // staged and summed cell of cell s1-2
-    if (ok && ta == 0) {
+    if (ok && ta == 0 && (!SPARE || c1 == TA)) {  // the last face
         double du[5], Db[5], ab[5], bb[5];
 #pragma unroll
         for (int v = 0; v < 5; ++v) {
@@ -956,14 +963,22 @@ static MarchSplit march_split(size_t nlines, int n) {
 
 // Segments per line of k_adj_cells by the same estimate, in chunks of 16 cells
 static int cells_split(size_t nlines, int n) {
+    auto rounds = [&](int nseg) {
+        const size_t lb = kAcSeg / nseg;
+        return ((nlines + lb - 1) / lb + 255) / 256;
+    };
     int best = 1;
     double cost = 0.0;
     for (int nseg = 1; nseg <= kAcSeg && nseg <= n / 4; nseg *= 2) {
-        const size_t lb = kAcSeg / nseg, k = ((nlines + lb - 1) / lb + 255) / 256;
+        const size_t k = rounds(nseg);
         const int len = (n + nseg - 1) / nseg;
         const double c = ((len + kAcTA - 1) / kAcTA + 0.4) * ((double)(k / 2) * 2.0 + (k % 2 ? 1.4 : 0.0));
         if (nseg == 1 || c < cost) best = nseg, cost = c;
     }
+    // a segment of full chunks has no spare lane for its last face: halved where that takes no
+    // further round
+    const int twice = 2 * best;
+    if (twice <= kAcSeg && twice <= n / 4 && (n + best - 1) / best % kAcTA == 0 && rounds(twice) == rounds(best)) best = twice;
     return best;
 }
 
@@ -971,22 +986,25 @@ template <int WW>
 static void adj_conv(const BoxDesc &b, hipStream_t s, const AdjGeom &g, const double *u, const double *rbar,
                      double *ubar) {
     const size_t lx = (size_t)b.ny * b.nz, ly = (size_t)b.nx * b.nz, lz = (size_t)b.nx * b.ny;
-    auto cells = [&](auto kernel, size_t nlines, int n) {
+    // The march fills the chip from about 64^3 points on (32 us along y there, 128^3 167); below,
+    // its shortest segments of four cells in turn take longer than a chunk of cells side by side
+    // (32^3: 24.4 us against 13.0).
+    const bool small = b.n3 < (1u << 18);
+    auto cells = [&](auto kernel, auto spare, size_t nlines, int n) {
         const int nseg = cells_split(nlines, n), lb = kAcSeg / nseg;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((nlines + lb - 1) / lb)), dim3(256), 0, s, g, u, rbar, ubar, nseg);
+        const bool idle = n / nseg % kAcTA != 0 && (n + nseg - 1) / nseg % kAcTA != 0;  // in every segment's last chunk
+        hipLaunchKernelGGL((small && idle ? spare : kernel), dim3((unsigned)((nlines + lb - 1) / lb)), dim3(256), 0, s, g, u,
+                           rbar, ubar, nseg);
     };
     auto march = [&](auto kernel, size_t nlines, int n) {
         const MarchSplit m = march_split(nlines, n);
         hipLaunchKernelGGL(kernel, dim3((unsigned)((nlines + m.Lb - 1) / m.Lb)), dim3(kAmThreads), 0, s, g, u, rbar, ubar,
                            m.Lb, m.nseg);
     };
-    cells(k_adj_cells<0, WW>, lx, b.nx);
-    // The march fills the chip from about 64^3 points on (32 us along y there, 128^3 167); below,
-    // its shortest segments of four cells in turn take longer than a chunk of cells side by side
-    // (32^3: 24.4 us against 13.0).
-    if (b.n3 < (1u << 18)) {
-        cells(k_adj_cells<1, WW>, ly, b.ny);
-        cells(k_adj_cells<2, WW>, lz, b.nz);
+    cells(k_adj_cells<0, WW, false>, k_adj_cells<0, WW, true>, lx, b.nx);
+    if (small) {
+        cells(k_adj_cells<1, WW, false>, k_adj_cells<1, WW, true>, ly, b.ny);
+        cells(k_adj_cells<2, WW, false>, k_adj_cells<2, WW, true>, lz, b.nz);
     } else {
         march(k_adj_march<1, WW>, ly, b.ny);
         march(k_adj_march<2, WW>, lz, b.nz);
