@@ -751,6 +751,26 @@ def kernel_kind(name):
     return name.split("(")[0].replace("void ", "").replace("cns::", "")
 
 
+def kind_totals(fetch, write, dur):
+    """Per kernel kind, from the bytes of every counted dispatch and the durations (ns) of every
+    traced one by kernel name: the means over all its dispatches, whichever kernels the kind
+    is made of (the stage updates of the z sweep are three)."""
+    counted, ns = {}, {}
+    for name in set(fetch) & set(write):
+        k = counted.setdefault(kernel_kind(name), {"fetch": [], "write": []})
+        k["fetch"] += fetch[name]
+        k["write"] += write[name]
+    for name, d in dur.items():
+        ns.setdefault(kernel_kind(name), []).extend(d)
+    out = {}
+    for kind, k in counted.items():
+        fb, wb = (sum(k[c]) / len(k[c]) for c in ("fetch", "write"))
+        t = ns.get(kind)
+        out[kind] = {"bytes_per_launch": int(fb + wb), "fetch_bytes": int(fb), "write_bytes": int(wb),
+                     "avg_launch_ns": sum(t) / len(t) if t else None, "dispatches": len(k["fetch"])}
+    return out
+
+
 def summarize(d, title):
     """Per-kernel bytes and rates from rocprofv3 CSV output under d: kt/ (kernel trace),
     fetch/ (FETCH_SIZE) and write/ (WRITE_SIZE).  d/meta.json gives the grid size, the
@@ -778,17 +798,21 @@ def summarize(d, title):
     copy_ns = sorted(dur.get(copy_name, [0]))[len(dur.get(copy_name, [0])) // 2]
     copy_GBs = 2 * copy_bytes / copy_ns if copy_ns else None
     bpp = BYTES_PER_POINT if prec == "fp64" else BYTES_PER_POINT_MIXED
-    kinds, rows = {}, []
+    rows = []
+    kinds = kind_totals({k: [b * fetch_scale for b in v] for k, v in fetch.items()},
+                        {k: [b * write_scale for b in v] for k, v in write.items()}, dur)
     for name in sorted(set(fetch) & set(write), key=lambda k: -sum(dur.get(k, [0]))):
         kind = kernel_kind(name)
         fb = sum(fetch[name]) / len(fetch[name]) * fetch_scale
         wb = sum(write[name]) / len(write[name]) * write_scale
         ns = sum(dur[name]) / len(dur[name]) if name in dur else None
-        alg = bpp.get(kind, 0) * n ** 3 if kind in bpp else None
-        rows.append((name, kind, ns, fb, wb, alg))
-        if kind not in kinds or (ns or 0) > (kinds[kind]["avg_launch_ns"] or 0):
-            kinds[kind] = {"bytes_per_launch": int(fb + wb), "fetch_bytes": int(fb), "write_bytes": int(wb),
-                           "avg_launch_ns": ns, "dispatches": len(fetch[name])}
+        short = name.split("(")[0].replace("void ", "").replace("cns::", "")
+        whole = kinds[kind]["dispatches"] == len(fetch[name])  # the kind's only kernel
+        rows.append((f"`{short}`", kind, ns, fb, wb, bpp[kind] * n ** 3 if whole and kind in bpp else None))
+    for kind, k in kinds.items():
+        if sum(r[1] == kind for r in rows) > 1:
+            rows.append((f"{kind}, mean of its kernels", kind, k["avg_launch_ns"], k["fetch_bytes"], k["write_bytes"],
+                         bpp[kind] * n ** 3 if kind in bpp else None))
     out = {"n": n, "precision": prec, "kernel_source_sha256": kernel_source_digest(), "fetch_scale": fetch_scale,
            "write_scale": write_scale, "copy_reference_GBs": copy_GBs, "kernels": kinds}
     # the benchmark line reads the counters of its own workload (512^3 FP64) only
@@ -809,8 +833,7 @@ def summarize(d, title):
         if ns is None:
             continue
         tbs = (fb + wb) / ns / 1e3
-        short = name.split("(")[0].replace("void ", "").replace("cns::", "")
-        lines.append(f"| `{short}` | {ns / 1e6:.3f} | {fb / 1e9:.2f} | {wb / 1e9:.2f} | {tbs:.2f} | "
+        lines.append(f"| {name} | {ns / 1e6:.3f} | {fb / 1e9:.2f} | {wb / 1e9:.2f} | {tbs:.2f} | "
                      f"{tbs * 1e3 / PEAK_HBM_GBS:.2f} | " + (f"{tbs * 1e3 / copy_GBs:.2f}" if copy_GBs else "-") +
                      " | " + (f"{alg / 1e9:.2f} | {alg / (fb + wb):.2f} |" if alg else "- | - |"))
     traced_only = sorted(set(dur) - set(fetch), key=lambda k: -sum(dur[k]))
@@ -872,10 +895,10 @@ def summarize_sq(d, n, dur):
     out = {}
     for (kind, cname), v in sums.items():
         out.setdefault(kind, {})[cname] = v / cnt[(kind, cname)]
-    for name, ds in dur.items():
-        kind = kernel_kind(name)
-        if kind in out:
-            out[kind]["_avg_ns"] = sum(ds) / len(ds)
+    for kind, c in out.items():
+        ds = [t for name, d in dur.items() if kernel_kind(name) == kind for t in d]
+        if ds:
+            c["_avg_ns"] = sum(ds) / len(ds)
     return out
 
 
