@@ -265,9 +265,11 @@ __global__ __launch_bounds__(kAmThreads, 2) void k_adj_march(AdjGeom g, const do
         double du[5];
 #pragma unroll
         for (int v = 0; v < 5; ++v) {
-            double L6, R6;
-            weno5_cell6<WW>(at(slot_of(0), v), at(slot_of(1), v), at(slot_of(2), v), at(slot_of(3), v), at(slot_of(4), v),
-                            eps4, L6, R6);
+            // (the values of the product itself: its range is wider than the forward form's)
+            double x[5], xb[5], L6, R6;
+#pragma unroll
+            for (int m = 0; m < 5; ++m) x[m] = at(slot_of(m), v);
+            weno5_cell_vjp<WW>(x, eps4, 0.0, 0.0, xb, L6, R6);
             du[v] = R6 - UL[v];
         }
         state_adjoint(slot_of(1), slot_of(2), -1.0, du, AU[1], AU[2]);
@@ -524,8 +526,10 @@ __global__ __launch_bounds__(256, 2) void k_adj_cells(AdjGeom g, const double *u
         double du[5], Db[5], ab[5], bb[5];
 #pragma unroll
         for (int v = 0; v < 5; ++v) {
-            double L6, R6;
-            weno5_cell6<WW>(S(v, c1), S(v, c1 + 1), S(v, c1 + 2), S(v, c1 + 3), S(v, c1 + 4), eps4, L6, R6);
+            double x[5], xb[5], L6, R6;
+#pragma unroll
+            for (int m = 0; m < 5; ++m) x[m] = S(v, c1 + m);
+            weno5_cell_vjp<WW>(x, eps4, 0.0, 0.0, xb, L6, R6);
             du[v] = R6 - UL(v, c1);
             Db[v] = (S(7 + v, c1 + 1) - S(7 + v, c1 + 2)) * ih12;
         }

@@ -56,3 +56,20 @@ def test_jiang_shu_product_at_large_jumps(orc, shape):
     plan = Plan(shape, mu_eff=0.01 * a)
     got = plan.rhs_vjp(plan.init_state(rho, vel, p), torch.from_numpy(rbar).cuda()).cpu().numpy()
     assert rel_max(rows(got, 1.0, 1.0 / a), rows(ref, 1.0, 1.0 / a)) <= 1e-11
+
+
+@pytest.mark.parametrize("shape", [(10, 12, 37), (66, 64, 65)])
+def test_weno_z_product_at_large_jumps(orc, shape):
+    """The WENO-Z product forms no products of indicator factors, so jumps of the state beyond
+    products of six (1e26) are in its range, also at the ends of segments, whose right-biased
+    values are formed apart."""
+    print(f"[case] weno-z product at large jumps {shape}", flush=True)
+    a = 2.0 ** 44
+    rho, vel, p = prims(shape, a)
+    rbar = rows(np.random.default_rng(1).standard_normal((5,) + shape), a, a)
+    ref = tr.rhs_vjp(torch.from_numpy(orc.init_state(rho, vel, p)), torch.from_numpy(rbar),
+                     tr.make_phys(mu=0.01 * a, delta=1e-6, weights="z")).numpy()
+    assert np.isfinite(ref).all()
+    plan = Plan(shape, mu_eff=0.01 * a, weno="z")
+    got = plan.rhs_vjp(plan.init_state(rho, vel, p), torch.from_numpy(rbar).cuda()).cpu().numpy()
+    assert rel_max(rows(got, 1.0, 1.0 / a), rows(ref, 1.0, 1.0 / a)) <= 1e-11
