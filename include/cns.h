@@ -205,9 +205,10 @@ int64_t cns_plan_graph_captures(const cns_plan *plan);
 /* ---- ensembles: independent periodic boxes of uneven sizes advanced together ----
  * Every kernel launch covers all boxes (virtual blocks mapped to boxes by prefix
  * sums), so one RK4 step of the whole ensemble is 18 launches (viscous fluxes and three
- * sweeps per stage, two for the diagnostics), optionally replayed
+ * sweeps per stage, two for the diagnostics), of a small FP64 one 9 (its kernels side by side
+ * and their sum per stage, one for the diagnostics), optionally replayed
  * from a captured hipGraph.  A box advanced in an ensemble gives bitwise the result
- * of its own single-box plan (same kernels, same arithmetic).  Extension beyond the
+ * of its own single-box plan (same arithmetic in the same order).  Extension beyond the
  * paper, which advances one domain. */
 typedef struct cns_ensemble cns_ensemble;
 /* grids[nbox], phys[nbox], dt[nbox]: host arrays.  u_packed: device buffer holding
@@ -225,8 +226,9 @@ int cns_ensemble_set_tiles(cns_ensemble *ens, int32_t box, int32_t seg_x, int32_
 int cns_ensemble_get_tiles(const cns_ensemble *ens, int32_t box, int32_t *seg3_host, int32_t *block_host);
 /* Choose launch shapes by timing them on the device, keeping the fastest: per box size,
  * the segment length of the y/z marching sweeps and the rows per block of the x rows
- * kernel (the default power of two and every count with the same points per thread that
- * keeps 90 % of a block's threads busy); for the batch, the threads per block of the marching sweeps and the launched
+ * kernel (FP64: as many as a block holds, a half, a quarter and an eighth of them; mixed: the
+ * default power of two and every count with the same points per thread that keeps 90 % of a
+ * block's threads busy); for the batch, the threads per block of the marching sweeps and the launched
  * grids (one block per virtual block, or persistent grids of one or two rounds of the
  * blocks the chip holds at once, for the sweeps and for the tiled viscous-flux and
  * diagnostics kernels; a small FP64 batch that runs its stages side by side keeps one block

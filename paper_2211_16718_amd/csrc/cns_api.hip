@@ -58,9 +58,9 @@ static int validate(const cns_grid *g, const cns_physics *ph) {
     if (!(ph->gamma > 1.0) || !std::isfinite(ph->gamma)) return set_err(CNS_EINVAL, "gamma must exceed 1");
     if (!(ph->mu_eff >= 0.0) || !std::isfinite(ph->mu_eff)) return set_err(CNS_EINVAL, "mu_eff must be >= 0");
     if (ph->mu_eff > 0.0 && !(ph->prandtl > 0.0)) return set_err(CNS_EINVAL, "prandtl must be > 0");
-    // products of up to eight (eps + beta) factors are formed in FP64 (the two weight
-    // denominators of an interface share one reciprocal; eps is rounded to FP32 in the
-    // mixed form): eps outside [1e-30, 1e30] would leave their range
+    // products of up to eight (eps + beta) factors are formed in FP64 (the Jiang-Shu weight
+    // denominators of the two sides share one reciprocal; eps is rounded to FP32 in the mixed
+    // form): eps outside [1e-30, 1e30] would leave their range
     if (!(ph->weno_eps >= 1e-30 && ph->weno_eps <= 1e30))
         return set_err(CNS_EINVAL, "weno_eps must lie in [1e-30, 1e30] (got %g)", ph->weno_eps);
     if (!(ph->harten_delta >= 0.0)) return set_err(CNS_EINVAL, "harten_delta must be >= 0");
@@ -168,12 +168,6 @@ struct Core {
         return b;
     }
 
-    // Default marching-segment lengths, from the whole batch.  A thread of a sweep runs seg + 2
-    // cell steps and a start of about one and a half, and the chip holds 2^17 threads at once
-    // (two waves per SIMD over 256 CUs): up to 16 points, the length with the least steps per
-    // round times rounds (32^3: 1 point, 0.02 against 0.06 ms per sweep with 16); 16 is doubled
-    // up to 128 while the launch still has 2^19 threads (longer segments form fewer cells
-    // twice; 512^3: 128 points).
     // Whether a stage goes through the two launches of k_small: FP64, rows in LDS, and at most
     // 1.5 M points, where side by side the launches' ends overlap and the buffers stay in the
     // caches.  RK4 step, separate launches -> together: 32^3 187 -> 92 us, 64^3 288 -> 223,
@@ -191,6 +185,15 @@ struct Core {
         return prec == CNS_FP64 && xrows_pref && n <= (visc ? (size_t)3 << 19 : (size_t)3 << 17);
     }
 
+    // Default marching-segment lengths, from the whole batch.  A thread of a sweep runs seg + 2
+    // cell steps and a start of about one and a half, and the chip holds 2^17 threads at once
+    // (two waves per SIMD over 256 CUs): up to 16 points, the length with the least steps per
+    // round times rounds (32^3: 1 point, 0.02 against 0.06 ms per sweep with 16); 16 is doubled
+    // up to 128 while the launch still has 2^19 threads (longer segments form fewer cells
+    // twice; 512^3: 128 points).  The mixed form (a step per
+    // interface, a start of six points) takes the same lengths and planes: RK4 step with 16
+    // points and 16 planes -> now 32^3 612 -> 155 us, 64^3 661 -> 281, 112^3 1110 -> 990, 128^3
+    // 1209 -> 1204.
     void default_segs() {
         // threads of a direction that fill the chip: alone, or with the other kernels beside it
         // (64^3: 288 us a step with 2^17, 258 with 2^16, 230 with 2^15)

@@ -1,6 +1,6 @@
 // cns_device.h -- device arithmetic of the WENO5-Roe / central-viscous discretisation
 // for gfx950, FP64 (the mixed form's FP32 arithmetic is in cns_mixed.hip, which shares the
-// reciprocals, Harten's fix and the central difference).
+// reciprocals and the central difference).
 //
 // Formulation choices (same operator as Sec. 2.2 of the paper, different
 // arithmetic order):
@@ -60,13 +60,7 @@ __device__ __forceinline__ float rsq(float x) {
     return fmaf(0.5f * y, r, y);
 }
 
-template <typename T>
-__device__ __forceinline__ T harten_abs(T lam, T delta) {
-    // |lam| if |lam| >= delta, else (lam^2 + delta^2) / (2 delta)  (Harten's entropy fix)
-    T a = fabs(lam);
-    return (a >= delta) ? a : (lam * lam + delta * delta) / (T(2) * delta);
-}
-// the same with h = 1 / (2 delta) given (no division inside the flux loop)
+// Harten's entropy fix: |lam| if |lam| >= delta, else (lam^2 + delta^2) h, h = 1 / (2 delta)
 template <typename T>
 __device__ __forceinline__ T harten_abs(T lam, T delta, T h) {
 #pragma clang fp contract(off)

@@ -5,8 +5,10 @@
 // BoxDesc entries.  A kernel's blocks are virtual: for each kernel family a prefix
 // array off[0..nbox] gives the first virtual block of every box; a block finds its
 // box by binary search and runs the single-box code on its local block index.  A
-// single-box plan is a batch of one, so a box advanced inside an ensemble executes
-// exactly the machine code of its single-box run.
+// single-box plan is a batch of one.  A box advanced inside an ensemble gives the bits of its
+// single-box run also where the two take different kernels (a small FP64 batch runs a stage's
+// kernels side by side, a larger one in turn): the FP64 kernels state every rounding, and both
+// ways take the terms of a point in the same order.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -64,7 +66,10 @@ struct BoxDesc {
     size_t n3;
     double inv_h[3];  // 1/dx, 1/dy, 1/dz
     double gamma, prandtl, mu, eps, delta, dt;
-    void *u, *A, *B, *rhs, *G;  // state and scratch (element type of the plan); G: viscous terms [4][n3]
+    // state and scratch (element type of the plan).  G is [9][n3]: the mixed form's viscous fluxes;
+    // in FP64 the viscous terms in planes 0-3 and, side by side, the raw y differences in 4-8; the
+    // spectrum's fields after its y pass
+    void *u, *A, *B, *rhs, *G;
     double *acc, *part;             // RK4 accumulator [5][n3], diagnostics partials
 };
 

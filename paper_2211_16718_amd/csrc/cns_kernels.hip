@@ -416,9 +416,10 @@ __global__ __launch_bounds__(ViscTile<T>::kThreads, 2) void k_visc(Launch L0) {
 // ----------------------------------------------------------------------------
 // marching WENO5-Roe sweep along one direction
 // ----------------------------------------------------------------------------
-// MODE_RAW: the flux differences themselves, for k_stage_sum.  MODE_RK1/2/3: the fused Runge-Kutta update, by what it reads besides rhs and the stage
-// state: nothing (first stages), u^n, or u^n and the accumulator (RK4 stage 4).  One kernel
-// with a run-time choice holds the operands of all three and spills 25 registers.
+// MODE_RAW: the flux differences themselves, for k_stage_sum.  MODE_RK1/2/3: the fused
+// Runge-Kutta update, by what it reads besides rhs and the stage state: nothing (first stages),
+// u^n, or u^n and the accumulator (RK4 stage 4).  One kernel with a run-time choice holds the
+// operands of all three and spills 25 registers.
 enum { MODE_WRITE = 0, MODE_ACCUM = 1, MODE_RK1 = 2, MODE_RK2 = 3, MODE_RK3 = 4, MODE_RAW = 5 };
 constexpr bool is_rk(int mode) { return mode >= MODE_RK1 && mode <= MODE_RK3; }
 
@@ -1463,6 +1464,8 @@ int rows_max(int nx) {
 
 size_t xrows_lds(int nx, int rows, size_t esz) { return rows_lds_bytes(nx, rows, esz); }
 
+// (the bound of the mixed form's kernel, four points per thread and its 14 staged fields; the FP64
+// kernel takes what a caller sets within it down to rows_max)
 bool rows_fit(int nx, int rows, size_t esz) {
     const long long per = (long long)rows * nx;
     return rows >= 1 && per <= 4 * kRowThreads && (size_t)14 * per * esz <= (size_t)kRowLdsMax;
@@ -1744,7 +1747,7 @@ static void diag_t(const Batch &bt, const void *u_ov, double *diag, long long st
     L.diag_box_stride = stride;
     L.step = step;
     const dim3 g(grid_of(bt, F_DIAG, L.total)), b(kDiagThreads);
-    const bool three = sizeof(T) == 8 && g.x <= 768;
+    const bool three = sizeof(T) == 8 && g.x <= 3 * 256;  // three on each of 256 CUs
     if constexpr (sizeof(T) == 8)
         if (three) hipLaunchKernelGGL((k_diag_partial<T, 3>), g, b, 0, bt.stream, L);
     if (!three) hipLaunchKernelGGL((k_diag_partial<T, 4>), g, b, 0, bt.stream, L);

@@ -6,7 +6,7 @@
 // every intermediate shows in the results: the cell-by-cell evaluation and the one-pass
 // viscous terms of the FP64 kernels ran 1.3 x faster here as well (256^3 step 6.5 against
 // 8.5 ms) and no further from the FP64 solution, but they move the diagnostics, which are
-// FP64 numbers, by 5e-9 and single states by an ulp.
+// FP64 numbers, by 4.5e-8 relative and single states by an ulp.
 //
 // One RHS: k_visc_flux (u -> G = (tau_xx, tau_yy, tau_zz, tau_xy, tau_xz, tau_yz, E_x, E_y,
 // E_z), E_d = v.tau_d - q_d), the x sweep (u, G -> rhs), the y and z sweeps (accumulate; z
@@ -845,7 +845,7 @@ __global__ __launch_bounds__(kRowThreads, 2) void k_sweep_x_rows(Launch L0) {
 // The flux difference of point i takes the interface fluxes at i-1/2 and i+1/2; the first
 // point of a chunk takes i-1/2 from the previous chunk (carried in LDS), and the row's
 // first point waits for the last chunk.  Compared with staging the whole row, the LDS of
-// a block no longer grows with the row (29 KB in FP64), so the CU holds twice the blocks
+// a block does not grow with the row (15 KB), so the CU holds twice the blocks
 // at 512 points per row; each chunk re-reads five stencil points of its neighbour.
 // ----------------------------------------------------------------------------
 constexpr int kChunkPts = kRowThreads + 5;  // points staged per chunk
