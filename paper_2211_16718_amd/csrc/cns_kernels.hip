@@ -80,7 +80,7 @@ __device__ __forceinline__ bool prim_stats(const double s[5], const double W[4],
 #pragma clang fp contract(off)
     const double r = s[0], mx = s[1], my = s[2], mz = s[3], e = s[4];
     const double inv = rcp(r);
-    const double ke = 0.5 * (mx * W[0] + my * W[1] + mz * W[2]);
+    const double ke = 0.5 * fma(mz, W[2], fma(my, W[1], mx * W[0]));
     const double p = (gamma - 1.0) * (e - ke);
     const bool finite = isfinite(r) && isfinite(mx) && isfinite(my) && isfinite(mz) && isfinite(e);
     if (!finite || !(r > 0.0) || !(p > 0.0)) {
@@ -309,7 +309,7 @@ __device__ __forceinline__ void visc_blocks(const Launch &L, const VbRange R, Vi
                     if (full && (good & 4u)) {
                         // vorticity of the velocity, as the diagnostics kernel forms it
                         const double ox = g[2][1] - g[1][2], oy = g[0][2] - g[2][0], oz = g[1][0] - g[0][1];
-                        if (isfinite(ox) && isfinite(oy) && isfinite(oz)) acc[1] += 0.5 * (ox * ox + oy * oy + oz * oz);
+                        if (isfinite(ox) && isfinite(oy) && isfinite(oz)) acc[1] = fma(0.5, fma(oz, oz, fma(oy, oy, ox * ox)), acc[1]);
                     }
                     if (full && (k + 1 == z1 || (k + 1) % grp == 0)) flush(k, true);
                 }
@@ -1157,7 +1157,7 @@ __device__ __forceinline__ bool point_stats(const double s[5], double gamma, dou
     v[0] = mx * inv;
     v[1] = my * inv;
     v[2] = mz * inv;
-    const double ke = 0.5 * (mx * v[0] + my * v[1] + mz * v[2]);
+    const double ke = 0.5 * fma(mz, v[2], fma(my, v[1], mx * v[0]));
     const double p = (gamma - 1.0) * (e - ke);
     const bool finite = isfinite(r) && isfinite(mx) && isfinite(my) && isfinite(mz) && isfinite(e);
     if (!finite || !(r > 0.0) || !(p > 0.0)) {
@@ -1308,7 +1308,7 @@ __global__ __launch_bounds__(kDiagThreads, OCC) void k_diag_partial(Launch L0) {
                     const double dvydx = dcen12(pv[1][Y][X - 2], pv[1][Y][X - 1], pv[1][Y][X + 1], pv[1][Y][X + 2]) * ihx;
                     const double dvxdy = dcen12(pv[0][Y - 2][X], pv[0][Y - 1][X], pv[0][Y + 1][X], pv[0][Y + 2][X]) * ihy;
                     const double ox = dvzdy - dvydz, oy = dvxdz - dvzdx, oz = dvydx - dvxdy;
-                    if (isfinite(ox) && isfinite(oy) && isfinite(oz)) acc[1] += 0.5 * (ox * ox + oy * oy + oz * oz);
+                    if (isfinite(ox) && isfinite(oy) && isfinite(oz)) acc[1] = fma(0.5, fma(oz, oz, fma(oy, oy, ox * ox)), acc[1]);
                 }
                 __syncthreads();  // the next plane overwrites the LDS tile
 #pragma unroll
@@ -1370,7 +1370,7 @@ __global__ __launch_bounds__(kDiagThreads) void k_speed_partial(Launch L0) {
                          mz = double(u[3 * n3 + i]), e = double(u[4 * n3 + i]);
             const double inv = rcp(r);
             const double vx = mx * inv, vy = my * inv, vzc = mz * inv;
-            const double ke = 0.5 * (mx * vx + my * vy + mz * vzc);
+            const double ke = 0.5 * fma(mz, vzc, fma(my, vy, mx * vx));
             const double p = (gamma - 1.0) * (e - ke);
             const bool finite = isfinite(r) && isfinite(mx) && isfinite(my) && isfinite(mz) && isfinite(e);
             if (!finite || !(r > 0.0) || !(p > 0.0)) {
