@@ -85,7 +85,8 @@ PEAK_VALU_LANE_INSTR = 256 * 4 * 16 * 2.4e9  # VALU lane-instructions per second
 KERNEL_KIND_OF = (("k_sweep_x_rows", "sweep_x"), ("k_sweep_x_chunks", "sweep_x"), ("k_visc_flux", "visc_flux"), ("k_visc<", "visc_flux"),
                   ("k_small", "stage_kernels"), ("k_stage_sum", "stage_sum"), ("k_diag_partial", "diagnostics"),
                   ("k_diag_final", "diagnostics_final"), ("k_stream_copy", "stream_copy"),
-                  ("k_init_state", "init_state"), ("k_speed_", "max_wave_speed"))
+                  ("k_init_state", "init_state"), ("k_speed_partial", "max_wave_speed"),
+                  ("k_speed_final", "max_wave_speed_final"))
 
 
 def log(msg):
